@@ -37,6 +37,7 @@
 // The landmark queries' gradient and the landmark-value backward use atomic
 // adds whose order varies from run to run, so dq, dk, dv are reproducible
 // only to rounding (a few ulp), not bit for bit.
+#include "backward_keys.hpp"
 #include "cdna4.hpp"
 #include "check.hpp"
 #include "flash.hpp"
@@ -97,9 +98,11 @@ struct BwdArgs {
   float *dq;               // [BH, N, d] ATT: the queries' direct gradient (written)
   float *dk, *dv;          // [BH, N, d] accumulators (atomic adds)
   float *dq_lm, *dv_lm_out;  // [BH, M, d] accumulators (atomic adds)
-  float *q_lse, *q_D;      // [BH, N] ATT: each query's log-sum-exp (log2 units) and dO . o (written)
+  float *q_lse, *q_D;      // [BH, N] ATT: each query's log-sum-exp (log2 units) and dO . o (written), by item
+                           // (position in perm; token without routing)
   const void *dv_lm16;     // [BH, M, d] bf16 copy of dv_lm (the DMA-tiled landmark-value pass)
   const float *D_lm;       // [BH, M] dv_lm . v_lm (the DMA-tiled landmark-value pass)
+  float *dq_part;          // [BH, chunks, M, d] the DMA-tiled landmark-value pass's sums per key chunk
   int N, M, topk, chunk;
   float scale;
 };
@@ -310,8 +313,8 @@ __global__ __launch_bounds__(256) void bwd_kernel(BwdArgs a) {
     lc += __shfl_xor(lc, 32);
     lse = mc + __log2f(lc);
     if (g == 0 && qok) {
-      a.q_lse[bh * N + qrow[myq]] = lse;
-      a.q_D[bh * N + qrow[myq]] = Dq[myq];
+      a.q_lse[bh * N + q_begin + myq] = lse;
+      a.q_D[bh * N + q_begin + myq] = Dq[myq];
     }
   } else {
     lse = qok ? a.lse_lm[bh * M + q_begin + myq] : 0.f;
@@ -441,18 +444,28 @@ __global__ __launch_bounds__(256) void bwd_kernel(BwdArgs a) {
 // LDS DMA, double buffered, one barrier per tile, K and V row-major with the
 // 16-byte swizzle, K^T read by ds_read_b64_tr_b16 for dQ. Per group and key
 // tile (lane (g, p): keys 16 kb + 4 g + r of query p):
-//   pass 1 (K tiles only): S^T = K Q^T, each lane's running (max, sum) of
-//     exp2(S^T scale log2 e); the four lane groups merge into the query's
-//     log-sum-exp (log2 units);
-//   pass 2 (K and V tiles): P = exp2(S^T scale log2 e - lse), dP^T = V dO^T,
-//     dZ = P (dP - D) (rounded to bf16 for the MFMA), dQ^T += K^T dZ^T;
-// then dQ * scale, the log-sum-exp and D = dO . o (fp32, over the lane's 16
-// dimensions and then the four lane groups) are written per query, as
-// bwd_kernel does. S and P take the unscaled bf16 queries and an fp32
-// multiply by scale log2 e, as the key-owned kernel does.
+//   P = exp2(S^T scale log2 e - ref), S^T = K Q^T, dP^T = V dO^T,
+//   dZ = P (dP - D) (rounded to bf16 for the MFMA), dQ^T += K^T dZ^T,
+//   l += P (fp32);
+// then dQ * scale / l, the log-sum-exp ref + log2 l and D = dO . o (fp32, over
+// the lane's 16 dimensions and then the four lane groups) are written per
+// query. S and P take the unscaled bf16 queries and an fp32 multiply by
+// scale log2 e, as the key-owned kernel does.
+// One sweep over the keys, as in the forward: ref is the column maximum of
+// the first tile, and the weights, their sum and dQ stay unnormalised (the
+// rounding of dZ to bf16 is relative, so the common factor does not matter).
+// They overflow only when a later score exceeds the first tile's maximum by
+// about 2^7 (log2 units); if some query's sums are then not finite, the
+// workgroup sweeps the keys again for the log-sum-exps (K tiles only) and
+// runs the pass with ref = lse, l = 1. At 16384 tokens, M = 128, k = 512,
+// 24 heads the pass takes 154 us against 202 us with the two sweeps
+// always.
+// The landmark mode (LMV) has its log-sum-exps from the score pass and writes
+// the key chunk's partial sums to dq_part (summed by the landmark-value key
+// pass's spare blocks).
 // ---------------------------------------------------------------------------
 constexpr int BWD16_TK = 32;
-constexpr int BWD16_LMV_CHUNK = 2048;  // keys per workgroup of the landmark queries' gradient
+constexpr int BWD16_LMV_CHUNK = 2048;  // most keys per workgroup of the landmark queries' gradient
 template <int D> constexpr int BWD16_GROUPS = D == 64 ? 2 : 1;
 template <int D> constexpr size_t bwd16_tiles_lds() { return 4 * (size_t)DmaTile<D, BWD16_TK>::BYTES; }
 
@@ -589,8 +602,9 @@ __global__ __launch_bounds__(256 / NG) __attribute__((amdgpu_waves_per_eu(4))) v
     }
   };
   // One sweep over the key tiles (DMA pipeline as in attend16_kernel);
-  // body(Kc, Vc, nvalid, masked_c) runs each tile's arithmetic.
-  auto sweep = [&](auto with_v_c, auto body) {
+  // body(Kc, Vc, nvalid, masked_c) runs each tile's arithmetic,
+  // first(Kc, nvalid, masked_c) comes before it on the first tile.
+  auto sweep = [&](auto with_v_c, auto first, auto body) {
     constexpr bool WV = decltype(with_v_c)::value;
     auto issue = [&](int j, bf16_t *Kn, bf16_t *Vn) {
       if (j < nfull) {
@@ -609,6 +623,7 @@ __global__ __launch_bounds__(256 / NG) __attribute__((amdgpu_waves_per_eu(4))) v
       issue(0, Ks(0), Vt(0));
       wait_loads();
       __syncthreads();
+      first(Ks(0), TK, std::false_type{});
       int i = 0;
       for (; i + 1 < nfull; i += 2) {
         step(i, 0);
@@ -625,21 +640,24 @@ __global__ __launch_bounds__(256 / NG) __attribute__((amdgpu_waves_per_eu(4))) v
         dma_tile<D, false, TK, NW, WV>(Ks(0), Vt(0), rkb, rvb, rows + nsh + nB * TK, nr);
       wait_loads();
       __syncthreads();
+      if (nfull == 0 && (part == 0 || pA == 0)) first(Ks(0), nr, std::true_type{});
       body(Ks(0), Vt(0), nr, std::true_type{});
       __syncthreads();
     }
   };
+  // the sum over the four lane groups of a column, in a fixed order
+  auto column_sum = [](float x) {
+    const auto a4 = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    const float pair = __uint_as_float(a4[0]) + __uint_as_float(a4[1]);
+    const auto b4 = __builtin_amdgcn_permlane32_swap(__float_as_uint(pair), __float_as_uint(pair), false, false);
+    return __uint_as_float(b4[0]) + __uint_as_float(b4[1]);
+  };
 
-  // ------------------------------------------------------------ pass 1: lse
+  // the log-sum-exps alone (after an overflow)
   float lm[NG], ll[NG];
-#pragma unroll
-  for (int c = 0; c < NG; ++c) {
-    lm[c] = -INFINITY;
-    ll[c] = 0.f;
-  }
   auto pass1 = [&](auto ngb_c) {
     constexpr int NGB = decltype(ngb_c)::value;
-    sweep(std::false_type{}, [&](const bf16_t *Kc, const bf16_t *, int nv, auto masked_c) {
+    sweep(std::false_type{}, [](const bf16_t *, int, auto) {}, [&](const bf16_t *Kc, const bf16_t *, int nv, auto masked_c) {
       constexpr bool MK = decltype(masked_c)::value;
       if (NGB == 0) return;
       f32x4 acc[NG][2];
@@ -665,39 +683,24 @@ __global__ __launch_bounds__(256 / NG) __attribute__((amdgpu_waves_per_eu(4))) v
       }
     });
   };
-  // (LMV: each landmark row's log-sum-exp comes from the score pass)
-  if (LMV)
-    ;
-  else if (NG == 2 && nbusy == 2)
-    pass1(std::integral_constant<int, NG>{});
-  else if (nbusy >= 1)
-    pass1(std::integral_constant<int, 1>{});
-  else
-    pass1(std::integral_constant<int, 0>{});
-  float lse[NG];
+  // ref: the weights' reference (log2 units), ll: the lane's sum of the
+  // weights; LMV: the landmark row's log-sum-exp from the score pass
+  float ref[NG];
 #pragma unroll
-  for (int c = 0; c < NG; ++c) {
-    if (LMV) {
-      lse[c] = qvalid[c] ? a.lse_lm[bh * M + tok[c]] : 0.f;
-      continue;
-    }
-    const float mc = max_lane_groups(lm[c]);
-    const float lc = lm[c] == -INFINITY ? 0.f : ll[c] * __builtin_amdgcn_exp2f(lm[c] - mc);
-    const auto x = __builtin_amdgcn_permlane16_swap(__float_as_uint(lc), __float_as_uint(lc), false, false);
-    const float pair = __uint_as_float(x[0]) + __uint_as_float(x[1]);
-    const auto y = __builtin_amdgcn_permlane32_swap(__float_as_uint(pair), __float_as_uint(pair), false, false);
-    lse[c] = qvalid[c] ? mc + __log2f(__uint_as_float(y[0]) + __uint_as_float(y[1])) : 0.f;
-  }
-
-  // ------------------------------------------------------------ pass 2: dQ
+  for (int c = 0; c < NG; ++c) ref[c] = LMV && qvalid[c] ? a.lse_lm[bh * M + tok[c]] : 0.f;
   f32x4 dqa[NG][D / 16];
-#pragma unroll
-  for (int c = 0; c < NG; ++c)
-#pragma unroll
-    for (int db = 0; db < D / 16; ++db) dqa[c][db] = f32x4{0.f, 0.f, 0.f, 0.f};
+  bool redo = false;  // uniform for the workgroup
   auto pass2 = [&](auto ngb_c) {
     constexpr int NGB = decltype(ngb_c)::value;
-    sweep(std::true_type{}, [&](const bf16_t *Kc, const bf16_t *Vc, int nv, auto masked_c) {
+    auto first = [&](const bf16_t *Kc, int nv, auto masked_c) {
+      constexpr bool MK = decltype(masked_c)::value;
+      if (LMV || NGB == 0 || redo) return;
+      f32x4 acc[NG][2];
+      scores(acc, Kc, ngb_c);
+#pragma unroll
+      for (int c = 0; c < NGB; ++c) ref[c] = max_lane_groups(att16_lane_max<MK>(acc[c], nv)) * sl2;
+    };
+    sweep(std::true_type{}, first, [&](const bf16_t *Kc, const bf16_t *Vc, int nv, auto masked_c) {
       constexpr bool MK = decltype(masked_c)::value;
       if (NGB == 0) return;
       f32x4 acc[NG][2], dp[NG][2];
@@ -723,8 +726,9 @@ __global__ __launch_bounds__(256 / NG) __attribute__((amdgpu_waves_per_eu(4))) v
         for (int kb2 = 0; kb2 < 2; ++kb2)
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
-            float pr = __builtin_amdgcn_exp2f(__builtin_fmaf(acc[c][kb2][r], sl2, -lse[c]));
+            float pr = __builtin_amdgcn_exp2f(__builtin_fmaf(acc[c][kb2][r], sl2, -ref[c]));
             if (MK && 16 * kb2 + 4 * g + r >= nv) pr = 0.f;
+            if (!LMV) ll[c] += pr;
             zz[4 * kb2 + r] = pr * (dp[c][kb2][r] - Dq[c]);
           }
         z[c].from_f32(zz);
@@ -745,38 +749,87 @@ __global__ __launch_bounds__(256 / NG) __attribute__((amdgpu_waves_per_eu(4))) v
       }
     });
   };
-  if (NG == 2 && nbusy == 2)
-    pass2(std::integral_constant<int, NG>{});
-  else if (nbusy >= 1)
-    pass2(std::integral_constant<int, 1>{});
-  else
-    pass2(std::integral_constant<int, 0>{});
-
-  // ------------------------------------------------------------ outputs
-  if (LMV) {  // the chunk's part of the landmark queries' gradient
+  auto run = [&](auto pass) {
+    if (NG == 2 && nbusy == 2)
+      pass(std::integral_constant<int, NG>{});
+    else if (nbusy >= 1)
+      pass(std::integral_constant<int, 1>{});
+    else
+      pass(std::integral_constant<int, 0>{});
+  };
+  __shared__ uint32_t overflow;
+  if (!LMV && threadIdx.x == 0) overflow = 0u;
+  float lsum[NG];
+  while (true) {
+    if (!LMV && redo) {
+#pragma unroll
+      for (int c = 0; c < NG; ++c) {
+        lm[c] = -INFINITY;
+        ll[c] = 0.f;
+      }
+      run(pass1);
+#pragma unroll
+      for (int c = 0; c < NG; ++c) {
+        const float mc = max_lane_groups(lm[c]);
+        ref[c] = mc + __log2f(column_sum(lm[c] == -INFINITY ? 0.f : ll[c] * __builtin_amdgcn_exp2f(lm[c] - mc)));
+      }
+    }
 #pragma unroll
     for (int c = 0; c < NG; ++c) {
-      if (!qvalid[c]) continue;
-      float *drow = a.dq_lm + (bh * M + tok[c]) * D;
+      ll[c] = 0.f;
+#pragma unroll
+      for (int db = 0; db < D / 16; ++db) dqa[c][db] = f32x4{0.f, 0.f, 0.f, 0.f};
+    }
+    run(pass2);
+    if (LMV) break;
+#pragma unroll
+    for (int c = 0; c < NG; ++c) lsum[c] = redo ? 1.f : column_sum(ll[c]);
+    if (redo) break;
+    bool ok = true;
+#pragma unroll
+    for (int c = 0; c < NG; ++c) {
+      // (a sum beyond 2^100 would also take scale / l into the subnormals)
+      bool fin = lsum[c] < 0x1p100f;
 #pragma unroll
       for (int db = 0; db < D / 16; ++db)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) unsafeAtomicAdd(drow + db * 16 + 4 * g + r, dqa[c][db][r] * a.scale);
+        for (int r = 0; r < 4; ++r) fin = fin && __builtin_isfinite(dqa[c][db][r]);
+      ok = ok && (fin || c >= nbusy);
+    }
+    if (__ballot(!ok) && lane == 0) atomicOr(&overflow, 1u);
+    __syncthreads();
+    if (overflow == 0u) break;  // uniform
+    redo = true;
+  }
+
+  // ------------------------------------------------------------ outputs
+  if (LMV) {  // the chunk's part of the landmark queries' gradient
+    const int nlb = (M + BWD_TQ - 1) / BWD_TQ, nch = (int)gridDim.x / nlb, ch = (int)blockIdx.x / nlb;
+#pragma unroll
+    for (int c = 0; c < NG; ++c) {
+      if (!qvalid[c]) continue;
+      float *drow = a.dq_part + ((bh * nch + ch) * M + tok[c]) * D;
+#pragma unroll
+      for (int db = 0; db < D / 16; ++db)
+        *reinterpret_cast<float4 *>(drow + db * 16 + 4 * g) =
+            make_float4(dqa[c][db][0] * a.scale, dqa[c][db][1] * a.scale, dqa[c][db][2] * a.scale,
+                        dqa[c][db][3] * a.scale);
     }
     return;
   }
 #pragma unroll
   for (int c = 0; c < NG; ++c) {
     if (!qvalid[c]) continue;
+    const float f = a.scale / lsum[c];
     float *drow = a.dq + (bh * N + tok[c]) * D;
 #pragma unroll
     for (int db = 0; db < D / 16; ++db)
       *reinterpret_cast<float4 *>(drow + db * 16 + 4 * g) =
-          make_float4(dqa[c][db][0] * a.scale, dqa[c][db][1] * a.scale, dqa[c][db][2] * a.scale,
-                      dqa[c][db][3] * a.scale);
+          make_float4(dqa[c][db][0] * f, dqa[c][db][1] * f, dqa[c][db][2] * f, dqa[c][db][3] * f);
     if (g == 0) {
-      a.q_lse[bh * N + tok[c]] = lse[c];
-      a.q_D[bh * N + tok[c]] = Dq[c];
+      const int64_t item = bh * N + q_begin + 16 * (NG * w + c) + p;
+      a.q_lse[item] = ref[c] + __log2f(lsum[c]);
+      a.q_D[item] = Dq[c];
     }
   }
 }
@@ -793,39 +846,19 @@ __global__ __launch_bounds__(256 / NG) __attribute__((amdgpu_waves_per_eu(4))) v
 //   ROUTED: block x = (expert e, key block b); keys idx[e][64 b ..], queries
 //           the expert's group (perm[offsets[e] ..]); the expert's sums are
 //           written to the staging rows [e][64 b ..] (plain stores).
-//   SHARED: block x = (landmark block, chunk of BWD_QCHUNK queries in token
-//           order); keys q_lm / v_lm rows; the sums are added atomically to
-//           the landmark rows.
+//   SHARED: block x = (landmark block, chunk of qchunk queries); keys q_lm /
+//           v_lm rows; the chunk's sums are written to part_k, part_v (their
+//           sum over the chunks is taken by bwd_prep_kernel).
 // Blocks are spread over the XCDs as the attention work list is, so the key
 // blocks of one expert (same queries) share an L2.
 // ---------------------------------------------------------------------------
 constexpr int BWD_KB = 64;
-constexpr int BWD_QCHUNK = 2048;
 
 template <typename T, int D> struct KvLds {
   static constexpr int PAD = 16 / (int)sizeof(T);
   static constexpr bool TRANS = sizeof(T) == 2 && D == 64;
   static constexpr int QS = D + PAD, TS = BWD_TQ + PAD, WS = BWD_TQ + PAD;
   static constexpr int NQ = BWD_TQ * QS, NQT = TRANS ? D * TS : 1, NW = 4 * 16 * WS;
-};
-
-struct KvArgs {
-  const void *q, *k, *v, *dO, *q_lm, *v_lm;
-  const int32_t *idx, *perm, *offsets;
-  const float *q_lse, *q_D;   // [BH, N]
-  const void *dv_lm16;        // LMV keys: [BH, M, d] bf16 gradient of the landmark values
-  const float *lse_lm, *D_lm; // LMV keys: [BH, M] the landmark rows' log-sum-exp and dV~ . V~
-  float *dk_acc, *dv_acc;     // LMV keys without the fused finish: [BH, N, d] accumulators (added to)
-  // LMV keys with the fused finish (dk_out != NULL): the routed keys' staged
-  // per-expert rows (inverse index inv_start / inv_slot, NULL without
-  // routing) are summed in, and dk, dv written in bf16
-  const int32_t *inv_start, *inv_slot;
-  void *dk_out, *dv_out;
-  float *stage_k, *stage_v;   // ROUTED: [BH, M, k, d]
-  float *dq_lm, *dv_lm;       // SHARED: [BH, M, d] accumulators
-  int N, M, topk, nblk;       // nblk: key blocks per expert (ROUTED) or landmark blocks (SHARED)
-  int ntotal;                 // blocks with work (the grid is rounded up to a multiple of 8)
-  float scale;
 };
 
 template <typename T, int D, bool ROUTED>
@@ -862,10 +895,10 @@ __global__ __launch_bounds__(256) void bwd_kv_kernel(KvArgs a) {
   } else {
     kb0 = (x % a.nblk) * BWD_KB;
     nkeys = min(BWD_KB, M - kb0);
-    q0 = (x / a.nblk) * BWD_QCHUNK;
-    nq = min(BWD_QCHUNK, N - q0);
+    q0 = (x / a.nblk) * a.qchunk;
+    nq = min(a.qchunk, N - q0);
   }
-  // (an expert without queries still writes its staging rows: zeros)
+  if (nq == 0) return;  // uniform: no staged rows (the inverse index has none)
   // this wave's 16 keys: K and V fragments (row p of the wave's block)
   const int mykey = 16 * w + p;
   const bool kvalid = mykey < nkeys;
@@ -896,10 +929,12 @@ __global__ __launch_bounds__(256) void bwd_kv_kernel(KvArgs a) {
     __syncthreads();
     if (tid < BWD_TQ) {
       int tok = -1;
-      if (t0 + tid < nq) tok = ROUTED ? a.perm[bh * N + q0 + t0 + tid] : q0 + t0 + tid;
+      const int64_t item = bh * N + q0 + t0 + tid;
+      const bool in = t0 + tid < nq;
+      if (in) tok = a.perm ? a.perm[item] : q0 + t0 + tid;
       qtok[tid] = tok;
-      lse_s[tid] = tok >= 0 ? a.q_lse[bh * N + tok] : 0.f;
-      D_s[tid] = tok >= 0 ? a.q_D[bh * N + tok] : 0.f;
+      lse_s[tid] = in ? a.q_lse[item] : 0.f;
+      D_s[tid] = in ? a.q_D[item] : 0.f;
     }
     __syncthreads();
     for (int c = tid; c < BWD_TQ * (D / VE); c += 256) {
@@ -976,399 +1011,89 @@ __global__ __launch_bounds__(256) void bwd_kv_kernel(KvArgs a) {
 #pragma unroll
     for (int db = 0; db < D / 16; ++db) {
       if (ROUTED) {
-        const int64_t at = ((bh * M + e) * (int64_t)K + kb0 + key) * D + 16 * db + p;
-        a.stage_k[at] = dk[db][r] * a.scale;
-        a.stage_v[at] = dv[db][r];
+        const int64_t at = ((bh * M + e) * (int64_t)K + kb0 + key) * (2 * D) + 16 * db + p;
+        a.stage[at] = dk[db][r] * a.scale;
+        a.stage[at + D] = dv[db][r];
       } else {
-        const int64_t at = (bh * M + kb0 + key) * D + 16 * db + p;
-        unsafeAtomicAdd(a.dq_lm + at, dk[db][r] * a.scale);
-        unsafeAtomicAdd(a.dv_lm + at, dv[db][r]);
+        const int nch = a.ntotal / a.nblk;
+        const int64_t at = ((bh * nch + x / a.nblk) * M + kb0 + key) * D + 16 * db + p;
+        a.part_k[at] = dk[db][r] * a.scale;
+        a.part_v[at] = dv[db][r];
       }
     }
   }
 }
 
-// ---------------------------------------------------------------------------
-// The key-owned backward for bf16 on the same tile machinery, with the roles
-// of queries and keys exchanged: each wave owns NG 16-key column groups of
-// the block's 64 keys (their K and V rows as MFMA B fragments in registers)
-// and streams the block's queries in 32-row tiles (Q and dO rows by LDS
-// DMA, double buffered, row-major with the 16-byte swizzle). Per group and
-// query tile (lane (g, p): queries 16 qb + 4 g + r of key p):
-//   S = Q K^T, dP = dO V^T; P = exp2(S scale log2 e - lse_q),
-//   dZ = P (dP - D_q) (both rounded to bf16 for the MFMA);
-//   dV^T += dO^T P, dK^T += Q^T dZ, with dO^T and Q^T read by transposing
-//   LDS reads of the tiles (the P and dZ fragments are already the B
-//   operand, in the key order of the transposing reads).
-// The queries' rows, log-sum-exps and D come in chunks of QC queries
-// (offsets and values staged in LDS per chunk). The sums go where
-// bwd_kv_kernel puts them (staging rows, or atomic adds for the landmarks).
-// ---------------------------------------------------------------------------
-constexpr int KV16_QC = 512;  // queries per staged chunk
-// key blocks of bwd_kv16_kernel: an expert's routed keys (its queries),
-// landmark keys (a chunk of all queries), or tokens as the keys of the
-// landmark values (the landmark rows as queries; each token row is owned by
-// one block, so the sums are added to the accumulators without atomics)
-constexpr int KV_ROUTED = 0, KV_SHARED = 1, KV_LMV = 2;
-
-template <int D, int KM, int NG>
-__device__ __forceinline__ void bwd_kv16_body(KvArgs a) {
-  constexpr bool ROUTED = KM == KV_ROUTED;
-  constexpr int NW = 4 / NG;
-  constexpr int NT = 64 * NW;
-  constexpr int TQ = BWD16_TK;  // queries per tile
-  static_assert(NG * NW * 16 == BWD_KB, "64 keys per workgroup");
-  using DT = DmaTile<D, TQ, NW>;
-  constexpr int RB = 2 * D;
-  __shared__ __align__(16) char tiles0[2 * DT::BYTES];
-  __shared__ __align__(16) char tiles1[2 * DT::BYTES];
-  __shared__ uint32_t qoff[KV16_QC];
-  __shared__ float lse_s[KV16_QC], D_s[KV16_QC];
-  auto Qt = [&](int b) { return reinterpret_cast<bf16_t *>(b ? tiles1 : tiles0); };
-  auto Dt = [&](int b) { return reinterpret_cast<bf16_t *>((b ? tiles1 : tiles0) + DT::BYTES); };
-  const int64_t bh = blockIdx.y;
-  const int w = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
-  const int lane = threadIdx.x & 63, g = lane >> 4, p = lane & 15;
-  const int N = a.N, M = a.M, K = a.topk;
-  // the block, spread over the XCDs
-  const int nb = (int)gridDim.x;
-  const int C = (nb + NXCD - 1) / NXCD;
-  const int x = ((int)blockIdx.x % NXCD) * C + (int)blockIdx.x / NXCD;
-  if (x >= a.ntotal) return;  // uniform
-  int e = 0, kb0, nkeys, q0, nq;
-  if (KM == KV_ROUTED) {
-    e = x / a.nblk;
-    kb0 = (x % a.nblk) * BWD_KB;
-    nkeys = min(BWD_KB, K - kb0);
-    q0 = a.offsets[bh * (M + 1) + e];
-    nq = a.offsets[bh * (M + 1) + e + 1] - q0;
-  } else if (KM == KV_SHARED) {
-    kb0 = (x % a.nblk) * BWD_KB;
-    nkeys = min(BWD_KB, M - kb0);
-    q0 = (x / a.nblk) * BWD_QCHUNK;
-    nq = min(BWD_QCHUNK, N - q0);
-  } else {
-    kb0 = x * BWD_KB;
-    nkeys = min(BWD_KB, N - kb0);
-    q0 = 0;
-    nq = M;
-  }
-  // (an expert without queries still writes its staging rows: zeros)
-  const bool tok_keys = KM != KV_SHARED;  // keys are token rows of k, v
-  const bf16_t *kbase = tok_keys ? (const bf16_t *)a.k + bh * (int64_t)N * D : (const bf16_t *)a.q_lm + bh * (int64_t)M * D;
-  const bf16_t *vbase = tok_keys ? (const bf16_t *)a.v + bh * (int64_t)N * D : (const bf16_t *)a.v_lm + bh * (int64_t)M * D;
-  Frag<bf16_t> kf[NG][D / 32], vf[NG][D / 32];
-#pragma unroll
-  for (int c = 0; c < NG; ++c) {
-    const int key = 16 * (NG * w + c) + p;
-    const bool kvalid = key < nkeys;
-    const int krow = kvalid ? (ROUTED ? a.idx[(bh * M + e) * (int64_t)K + kb0 + key] : kb0 + key) : 0;
-#pragma unroll
-    for (int ks = 0; ks < D / 32; ++ks) {
-      if (kvalid) {
-        kf[c][ks].load(kbase + (int64_t)krow * D + 32 * ks + 8 * g);
-        vf[c][ks].load(vbase + (int64_t)krow * D + 32 * ks + 8 * g);
-      } else {
-        kf[c][ks].zero();
-        vf[c][ks].zero();
-      }
-    }
-  }
-  f32x4 dka[NG][D / 16], dva[NG][D / 16];
-#pragma unroll
-  for (int c = 0; c < NG; ++c)
-#pragma unroll
-    for (int db = 0; db < D / 16; ++db) {
-      dka[c][db] = f32x4{0.f, 0.f, 0.f, 0.f};
-      dva[c][db] = f32x4{0.f, 0.f, 0.f, 0.f};
-    }
-  DmaLane<D, TQ, NW> dl;
-  dl.init(w, lane);
-  Att16Addr<D> ad;
-  ad.init();
-  const float sl2 = a.scale * LOG2E;
-  // the streamed queries: tokens (q, dO), or for LMV keys the landmark rows
-  // (q_lm and the landmark values' gradient)
-  const bf16_t *qg = KM == KV_LMV ? (const bf16_t *)a.q_lm + bh * (int64_t)M * D
-                                  : (const bf16_t *)a.q + bh * (int64_t)N * D;
-  const bf16_t *dOg = KM == KV_LMV ? (const bf16_t *)a.dv_lm16 + bh * (int64_t)M * D
-                                   : (const bf16_t *)a.dO + bh * (int64_t)N * D;
-
-  // one query tile: nv valid rows at chunk position j0
-  auto tile = [&](const bf16_t *Qc, const bf16_t *Dc, int j0, int nv, auto masked_c) {
-    constexpr bool MK = decltype(masked_c)::value;
-    const char *qbase = reinterpret_cast<const char *>(Qc), *dbase = reinterpret_cast<const char *>(Dc);
-    f32x4 s[NG][2], dp[NG][2];
-#pragma unroll
-    for (int qb = 0; qb < 2; ++qb) {
-#pragma unroll
-      for (int c = 0; c < NG; ++c) {
-        s[c][qb] = f32x4{0.f, 0.f, 0.f, 0.f};
-        dp[c][qb] = f32x4{0.f, 0.f, 0.f, 0.f};
-      }
-#pragma unroll
-      for (int ks = 0; ks < D / 32; ++ks) {
-        Frag<bf16_t> A, B;
-        A.v = *reinterpret_cast<const uint4 *>(qbase + ad.k[ks] + qb * 16 * RB);
-        B.v = *reinterpret_cast<const uint4 *>(dbase + ad.k[ks] + qb * 16 * RB);
-#pragma unroll
-        for (int c = 0; c < NG; ++c) {
-          s[c][qb] = mma(A, kf[c][ks], s[c][qb]);
-          dp[c][qb] = mma(B, vf[c][ks], dp[c][qb]);
-        }
-      }
-    }
-    // the rows' log-sum-exps and D (queries 16 qb + 4 g + r of the tile)
-    float lq[2][4], dq[2][4];
-#pragma unroll
-    for (int qb = 0; qb < 2; ++qb) {
-      const float4 l4 = *reinterpret_cast<const float4 *>(&lse_s[j0 + 16 * qb + 4 * g]);
-      const float4 d4 = *reinterpret_cast<const float4 *>(&D_s[j0 + 16 * qb + 4 * g]);
-      lq[qb][0] = l4.x; lq[qb][1] = l4.y; lq[qb][2] = l4.z; lq[qb][3] = l4.w;
-      dq[qb][0] = d4.x; dq[qb][1] = d4.y; dq[qb][2] = d4.z; dq[qb][3] = d4.w;
-    }
-    Frag<bf16_t> pf[NG], zf[NG];
-#pragma unroll
-    for (int c = 0; c < NG; ++c) {
-      float pp[8], zz[8];
-#pragma unroll
-      for (int qb = 0; qb < 2; ++qb)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          float pr = __builtin_amdgcn_exp2f(__builtin_fmaf(s[c][qb][r], sl2, -lq[qb][r]));
-          float zr = pr * (dp[c][qb][r] - dq[qb][r]);
-          // rows past the chunk's last query: their log-sum-exp and D slots
-          // in LDS were not written for this chunk and may hold any bits
-          // (0 * NaN would spread into every key's dK), so both weights are
-          // set, not scaled, to zero
-          if (MK && 16 * qb + 4 * g + r >= nv) pr = zr = 0.f;
-          pp[4 * qb + r] = pr;
-          zz[4 * qb + r] = zr;
-        }
-      pf[c].from_f32(pp);
-      zf[c].from_f32(zz);
-    }
-#pragma unroll
-    for (int db = 0; db < D / 16; ++db) {
-      uint2 hq[2], hd[2];
-#pragma unroll
-      for (int h2 = 0; h2 < 2; ++h2) {
-        hq[h2] = __builtin_bit_cast(
-            uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16_t *)(qbase + ad.v[db] + h2 * 16 * RB)));
-        hd[h2] = __builtin_bit_cast(
-            uint2, __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4i16_t *)(dbase + ad.v[db] + h2 * 16 * RB)));
-      }
-      Frag<bf16_t> AQ, AD;
-      AQ.v = make_uint4(hq[0].x, hq[0].y, hq[1].x, hq[1].y);
-      AD.v = make_uint4(hd[0].x, hd[0].y, hd[1].x, hd[1].y);
-#pragma unroll
-      for (int c = 0; c < NG; ++c) {
-        dva[c][db] = mma(AD, pf[c], dva[c][db]);
-        dka[c][db] = mma(AQ, zf[c], dka[c][db]);
-      }
-    }
-  };
-
-  for (int c0 = 0; c0 < nq; c0 += KV16_QC) {
-    const int nc = min(KV16_QC, nq - c0);
-    __syncthreads();  // the previous chunk's tiles and arrays are done
-    for (int j = threadIdx.x; j < nc; j += NT) {
-      const int tok = ROUTED ? a.perm[bh * N + q0 + c0 + j] : q0 + c0 + j;
-      qoff[j] = (uint32_t)tok * RB;
-      lse_s[j] = KM == KV_LMV ? a.lse_lm[bh * M + tok] : a.q_lse[bh * N + tok];
-      D_s[j] = KM == KV_LMV ? a.D_lm[bh * M + tok] : a.q_D[bh * N + tok];
-    }
-    __syncthreads();
-    const int nfull = nc / TQ, part = nc % TQ;
-    auto issue = [&](int j, int b) {
-      if (j < nfull) dma_tile_lane<D, TQ, NW>(Qt(b), Dt(b), qg, dOg, qoff + j * TQ, dl);
-    };
-    auto step = [&](int i, int b) {
-      issue(i + 1, b ^ 1);
-      __builtin_amdgcn_sched_barrier(0);
-      tile(Qt(b), Dt(b), i * TQ, TQ, std::false_type{});
-      wait_loads();
-      __syncthreads();
-    };
-    if (nfull > 0) {
-      issue(0, 0);
-      wait_loads();
-      __syncthreads();
-      int i = 0;
-      for (; i + 1 < nfull; i += 2) {
-        step(i, 0);
-        step(i + 1, 1);
-      }
-      if (i < nfull) step(i, 0);
-    }
-    if (part > 0) {
-      dma_tile<D, false, TQ, NW>(Qt(0), Dt(0), qg, dOg, qoff + nfull * TQ, part);
-      wait_loads();
-      __syncthreads();
-      tile(Qt(0), Dt(0), nfull * TQ, part, std::true_type{});
-    }
-  }
-  // LMV keys with the fused finish: each key's staged per-expert rows (the
-  // first FS slots loaded together: the index, then every row's dims) are
-  // added to the landmark-value sums, and dk, dv written in bf16
-  if (KM == KV_LMV && a.dk_out) {
-    constexpr int FS = 8;
-    const int64_t per_head = (int64_t)M * K;
-#pragma unroll
-    for (int c = 0; c < NG; ++c) {
-      const int key = 16 * (NG * w + c) + p;
-      if (key >= nkeys) continue;
-      float4 k4[D / 16], v4[D / 16];
-#pragma unroll
-      for (int db = 0; db < D / 16; ++db) {
-        k4[db] = make_float4(dka[c][db][0] * a.scale, dka[c][db][1] * a.scale, dka[c][db][2] * a.scale,
-                             dka[c][db][3] * a.scale);
-        v4[db] = make_float4(dva[c][db][0], dva[c][db][1], dva[c][db][2], dva[c][db][3]);
-      }
-      if (a.inv_start) {
-        const int s0 = a.inv_start[bh * (N + 1) + kb0 + key], s1 = a.inv_start[bh * (N + 1) + kb0 + key + 1];
-        const int n = s1 - s0;
-        int64_t src[FS];
-#pragma unroll
-        for (int i = 0; i < FS; ++i) src[i] = i < n ? (bh * per_head + a.inv_slot[bh * per_head + s0 + i]) * D : 0;
-        auto add = [&](int64_t sr) {
-#pragma unroll
-          for (int db = 0; db < D / 16; ++db) {
-            const float4 yk = *reinterpret_cast<const float4 *>(a.stage_k + sr + 16 * db + 4 * g);
-            const float4 yv = *reinterpret_cast<const float4 *>(a.stage_v + sr + 16 * db + 4 * g);
-            k4[db].x += yk.x; k4[db].y += yk.y; k4[db].z += yk.z; k4[db].w += yk.w;
-            v4[db].x += yv.x; v4[db].y += yv.y; v4[db].z += yv.z; v4[db].w += yv.w;
-          }
-        };
-        if constexpr (D == 64) {
-          // two rows' loads in flight before either is added (slot order
-          // kept; the registers come from running two waves per SIMD)
-          auto add2 = [&](int64_t r0, int64_t r1) {
-            float4 yk[2][D / 16], yv[2][D / 16];
-#pragma unroll
-            for (int db = 0; db < D / 16; ++db) {
-              yk[0][db] = *reinterpret_cast<const float4 *>(a.stage_k + r0 + 16 * db + 4 * g);
-              yv[0][db] = *reinterpret_cast<const float4 *>(a.stage_v + r0 + 16 * db + 4 * g);
-              yk[1][db] = *reinterpret_cast<const float4 *>(a.stage_k + r1 + 16 * db + 4 * g);
-              yv[1][db] = *reinterpret_cast<const float4 *>(a.stage_v + r1 + 16 * db + 4 * g);
-            }
-#pragma unroll
-            for (int b = 0; b < 2; ++b)
-#pragma unroll
-              for (int db = 0; db < D / 16; ++db) {
-                k4[db].x += yk[b][db].x; k4[db].y += yk[b][db].y; k4[db].z += yk[b][db].z; k4[db].w += yk[b][db].w;
-                v4[db].x += yv[b][db].x; v4[db].y += yv[b][db].y; v4[db].z += yv[b][db].z; v4[db].w += yv[b][db].w;
-              }
-          };
-          int i = 0;
-#pragma unroll
-          for (int j = 0; j < FS; j += 2)
-            if (j + 1 < n) add2(src[j], src[j + 1]), i = j + 2;
-          for (; i + 1 < n; i += 2)
-            add2((bh * per_head + a.inv_slot[bh * per_head + s0 + i]) * D,
-                 (bh * per_head + a.inv_slot[bh * per_head + s0 + i + 1]) * D);
-          if (i < n) add(i < FS ? src[i] : (bh * per_head + a.inv_slot[bh * per_head + s0 + i]) * D);
-        } else {
-#pragma unroll
-          for (int i = 0; i < FS; ++i)
-            if (i < n) add(src[i]);
-          for (int i = FS; i < n; ++i) add((bh * per_head + a.inv_slot[bh * per_head + s0 + i]) * D);
-        }
-      }
-      const int64_t at = (bh * N + kb0 + key) * D + 4 * g;
-#pragma unroll
-      for (int db = 0; db < D / 16; ++db) {
-        const bf16_t kb4[4] = {from_f32<bf16_t>(k4[db].x), from_f32<bf16_t>(k4[db].y), from_f32<bf16_t>(k4[db].z),
-                               from_f32<bf16_t>(k4[db].w)};
-        const bf16_t vb4[4] = {from_f32<bf16_t>(v4[db].x), from_f32<bf16_t>(v4[db].y), from_f32<bf16_t>(v4[db].z),
-                               from_f32<bf16_t>(v4[db].w)};
-        *reinterpret_cast<uint2 *>((bf16_t *)a.dk_out + at + 16 * db) = *reinterpret_cast<const uint2 *>(kb4);
-        *reinterpret_cast<uint2 *>((bf16_t *)a.dv_out + at + 16 * db) = *reinterpret_cast<const uint2 *>(vb4);
-      }
-    }
-    return;
-  }
-  // dK^T, dV^T: dims 16 db + 4 g + r of key p of group c
-#pragma unroll
-  for (int c = 0; c < NG; ++c) {
-    const int key = 16 * (NG * w + c) + p;
-    if (key >= nkeys) continue;
-#pragma unroll
-    for (int db = 0; db < D / 16; ++db) {
-      const float4 kq = make_float4(dka[c][db][0] * a.scale, dka[c][db][1] * a.scale, dka[c][db][2] * a.scale,
-                                    dka[c][db][3] * a.scale);
-      const float4 vq = make_float4(dva[c][db][0], dva[c][db][1], dva[c][db][2], dva[c][db][3]);
-      if (KM == KV_ROUTED) {
-        const int64_t at = ((bh * M + e) * (int64_t)K + kb0 + key) * D + 16 * db + 4 * g;
-        *reinterpret_cast<float4 *>(a.stage_k + at) = kq;
-        *reinterpret_cast<float4 *>(a.stage_v + at) = vq;
-      } else if (KM == KV_LMV) {
-        const int64_t at = (bh * N + kb0 + key) * D + 16 * db + 4 * g;
-        float4 k4 = kq, v4 = vq;
-        const float4 ak = *reinterpret_cast<const float4 *>(a.dk_acc + at);
-        const float4 av = *reinterpret_cast<const float4 *>(a.dv_acc + at);
-        k4.x += ak.x; k4.y += ak.y; k4.z += ak.z; k4.w += ak.w;
-        v4.x += av.x; v4.y += av.y; v4.z += av.z; v4.w += av.w;
-        *reinterpret_cast<float4 *>(a.dk_acc + at) = k4;
-        *reinterpret_cast<float4 *>(a.dv_acc + at) = v4;
-      } else {
-        const int64_t at = (bh * M + kb0 + key) * D + 16 * db + 4 * g;
-        unsafeAtomicAdd(a.dq_lm + at, kq.x);
-        unsafeAtomicAdd(a.dq_lm + at + 1, kq.y);
-        unsafeAtomicAdd(a.dq_lm + at + 2, kq.z);
-        unsafeAtomicAdd(a.dq_lm + at + 3, kq.w);
-        unsafeAtomicAdd(a.dv_lm + at, vq.x);
-        unsafeAtomicAdd(a.dv_lm + at + 1, vq.y);
-        unsafeAtomicAdd(a.dv_lm + at + 2, vq.z);
-        unsafeAtomicAdd(a.dv_lm + at + 3, vq.w);
-      }
-    }
-  }
+// What the landmark-value backward needs of each landmark row, one wave per
+// row (lane = 4 dims of the row and, of the chunks, every (256 / D)-th; the
+// parts are then summed across lanes):
+//  - dv_lm and dq_lm = the sums of the shared keys' partial sums over the
+//    query chunks;
+//  - for the DMA-tiled kernels (dv16 given) dv_lm in bf16 (the MFMA operand)
+//    and D = dV~ . V~ (fp32) instead of dv_lm;
+//  - the row's log-sum-exp (log2 units) from the score pass's per-chunk (max,
+//    sum) partials, every 64th per lane.
+__device__ __forceinline__ void lse_combine(float &m, float &l, float2 x) {
+  const float mn = fmaxf(m, x.x);
+  if (mn == -INFINITY) return;  // (nothing but empty partials so far)
+  l = l * __builtin_amdgcn_exp2f(m - mn) + x.y * __builtin_amdgcn_exp2f(x.x - mn);
+  m = mn;
 }
-
-// Three waves per SIMD; the landmark-value mode at d = 64 runs two, whose
-// registers hold two staged rows in flight in its finish (measured at 16384
-// tokens, 12 heads, 2 batches: that pass 379 -> 353 us, while the routed pass
-// with two waves went 361 -> 391 us).
-template <int D, int KM, int NG>
-__global__ __launch_bounds__(256 / NG) __attribute__((amdgpu_waves_per_eu(3))) void bwd_kv16_kernel(KvArgs a) {
-  bwd_kv16_body<D, KM, NG>(a);
-}
-template <int NG>
-__global__ __launch_bounds__(256 / NG) __attribute__((amdgpu_waves_per_eu(2))) void bwd_kv16_lmv64_kernel(KvArgs a) {
-  bwd_kv16_body<64, KV_LMV, NG>(a);
-}
-
-// The landmark values' gradient in bf16 (the MFMA operand of the DMA-tiled
-// landmark-value kernels) and each landmark row's D = dV~ . V~ (fp32): D / 8
-// consecutive lanes per row, 8 dims each, their partial dots summed by a
-// butterfly over those lanes.
-template <int D>
-__global__ __launch_bounds__(256) void lmv_prep_kernel(const float *__restrict__ dv_lm, const bf16_t *__restrict__ v_lm,
-                                                       bf16_t *__restrict__ dv16, float *__restrict__ D_lm,
-                                                       int64_t rows) {
-  constexpr int L = D / 8;  // lanes per row (8 or 16: rows never straddle a wave)
-  const int64_t t = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int64_t row = t / L;
-  const int c = 8 * (int)(t % L);
+template <typename T, int D>
+__global__ __launch_bounds__(256) void bwd_prep_kernel(const float *__restrict__ part_k,
+                                                       const float *__restrict__ part_v, int nchunk,
+                                                       const T *__restrict__ v_lm, float *__restrict__ dq_lm,
+                                                       float *__restrict__ dv_lm, bf16_t *__restrict__ dv16,
+                                                       float *__restrict__ D_lm, const float2 *__restrict__ part_ml,
+                                                       float *__restrict__ lse, int64_t rows, int M, int nch) {
+  constexpr int L = D / 4, P = 64 / L;  // lanes per row copy, parts of the chunks
+  const int lane = threadIdx.x & 63, c = 4 * (lane % L);
+  const int64_t row = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
+  if (row >= rows) return;  // the whole wave
+  const int64_t bh = row / M;
+  const int lm = (int)(row - bh * M);
+  float4 fk = make_float4(0.f, 0.f, 0.f, 0.f), fv = fk;
+  const int64_t at0 = (bh * nchunk * M + lm) * D + c;
+#pragma unroll 4
+  for (int ch = lane / L; ch < nchunk; ch += P) {
+    const float4 x = *reinterpret_cast<const float4 *>(part_k + at0 + (int64_t)ch * M * D);
+    const float4 y = *reinterpret_cast<const float4 *>(part_v + at0 + (int64_t)ch * M * D);
+    fk.x += x.x; fk.y += x.y; fk.z += x.z; fk.w += x.w;
+    fv.x += y.x; fv.y += y.y; fv.z += y.z; fv.w += y.w;
+  }
+  float m = -INFINITY, l = 0.f;
+  const float2 *ml = part_ml + bh * nch * M + lm;
+  for (int i = lane; i < nch; i += 64) lse_combine(m, l, ml[(int64_t)i * M]);
+#pragma unroll
+  for (int o = L; o < 64; o <<= 1) {
+    fk.x += __shfl_xor(fk.x, o); fk.y += __shfl_xor(fk.y, o); fk.z += __shfl_xor(fk.z, o); fk.w += __shfl_xor(fk.w, o);
+    fv.x += __shfl_xor(fv.x, o); fv.y += __shfl_xor(fv.y, o); fv.z += __shfl_xor(fv.z, o); fv.w += __shfl_xor(fv.w, o);
+  }
   float dsum = 0.f;
-  if (row < rows) {
-    const float4 f0 = *reinterpret_cast<const float4 *>(dv_lm + row * D + c);
-    const float4 f1 = *reinterpret_cast<const float4 *>(dv_lm + row * D + c + 4);
-    const float f[8] = {f0.x, f0.y, f0.z, f0.w, f1.x, f1.y, f1.z, f1.w};
-    float vv[8];
-    load16_f32(v_lm + row * D + c, vv);
-    bf16_t tt[8];
+  if (dv16) {
+    const T *vp = v_lm + row * D + c;
+    const float f[4] = {fv.x, fv.y, fv.z, fv.w};
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      dsum = __builtin_fmaf(vv[i], f[i], dsum);
-      tt[i] = from_f32<bf16_t>(f[i]);
-    }
-    *reinterpret_cast<uint4 *>(dv16 + row * D + c) = *reinterpret_cast<const uint4 *>(tt);
+    for (int i = 0; i < 4; ++i) dsum = __builtin_fmaf(to_f32<T>(vp[i]), f[i], dsum);
   }
 #pragma unroll
-  for (int o = L / 2; o > 0; o >>= 1) dsum += __shfl_xor(dsum, o);
-  if (row < rows && c == 0) D_lm[row] = dsum;
+  for (int o = 1; o < L; o <<= 1) dsum += __shfl_xor(dsum, o);
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) {
+    const float2 other = make_float2(__shfl_xor(m, o), __shfl_xor(l, o));
+    lse_combine(m, l, other);
+  }
+  if (lane < L) {
+    *reinterpret_cast<float4 *>(dq_lm + row * D + c) = fk;
+    if (dv16)
+      *reinterpret_cast<uint2 *>(dv16 + row * D + c) = make_uint2(pack_bf16x2(fv.x, fv.y), pack_bf16x2(fv.z, fv.w));
+    else
+      *reinterpret_cast<float4 *>(dv_lm + row * D + c) = fv;
+  }
+  if (lane == 0) {
+    if (dv16) D_lm[row] = dsum;
+    lse[row] = m + __log2f(l);
+  }
 }
 
 // Inverse index of the top-k sets: for each token, the slots e * k + j with
@@ -1378,35 +1103,49 @@ __global__ __launch_bounds__(256) void lmv_prep_kernel(const float *__restrict__
 // tokens and those of the tokens below its range (the range's base), scans
 // its counts from that base, and places its slots on a second read. The
 // order of a token's slots is that of the LDS atomics. Entries outside
-// [0, N) are left out of the index.
+// [0, N), and those of experts without queries (no staged rows; about 40% of
+// the experts on clustered inputs), are left out of the index.
 constexpr int INV_THREADS = 1024, INV_WAVES = INV_THREADS / 64;
 constexpr int INV_TMAX = 15360;  // tokens per workgroup: 60 KiB of counters (+ 384 B)
 
+// Is expert i among the head's experts with queries (bit i of live)? The
+// expert of entry e is e / k: the estimate by rk = floor(2^32 / k) is the
+// quotient or one less (e < 2^31).
+__device__ __forceinline__ bool inv_live(const uint32_t *live, uint32_t e, uint32_t k, uint32_t rk) {
+  uint32_t i = __umulhi(e, rk);
+  if (e - i * k >= k) ++i;
+  return (live[i >> 5] >> (i & 31)) & 1u;
+}
+
 // f(e, tok) for the head's per_head entries, strided over the workgroup, 16
 // per thread and call (e[i] the entry, tok[i] its token; -1 pads a short
-// batch): up to sixteen 16-byte loads in flight where the rows allow them,
-// and the callee's LDS atomics of a batch issued before their results are
-// used.
+// batch and stands for the entries of experts without queries): up to
+// sixteen 16-byte loads in flight where the rows allow them (k a multiple of
+// four: the four entries of a load are one expert's), and the callee's LDS
+// atomics of a batch issued before their results are used.
 template <class F>
-__device__ __forceinline__ void inv_entries(const int32_t *__restrict__ ih, int per_head, F &&f) {
+__device__ __forceinline__ void inv_entries(const int32_t *__restrict__ ih, int per_head, uint32_t k, uint32_t rk,
+                                            const uint32_t *live, F &&f) {
   int e[16], t[16];
   int i = threadIdx.x;
-  if ((per_head & 3) == 0 && ((uintptr_t)ih & 15) == 0) {
+  if ((k & 3) == 0 && ((uintptr_t)ih & 15) == 0) {
     const int4 *v = reinterpret_cast<const int4 *>(ih);
     const int n4 = per_head >> 2;
-    // sixteen loads in flight (a whole head of 64Ki entries in one round trip)
-    for (; i + 15 * INV_THREADS < n4; i += 16 * INV_THREADS) {
-      int4 x[16];
+    // eight loads in flight (with sixteen the registers of the live test spill)
+    for (; i + 7 * INV_THREADS < n4; i += 8 * INV_THREADS) {
+      int4 x[8];
 #pragma unroll
-      for (int u = 0; u < 16; ++u) x[u] = v[i + u * INV_THREADS];
+      for (int u = 0; u < 8; ++u) x[u] = v[i + u * INV_THREADS];
 #pragma unroll
-      for (int b = 0; b < 4; ++b) {
+      for (int b = 0; b < 2; ++b) {
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
           const int e0 = 4 * (i + (4 * b + u) * INV_THREADS);
           const int4 y = x[4 * b + u];
+          const bool ok = inv_live(live, (uint32_t)e0, k, rk);
           e[4 * u] = e0, e[4 * u + 1] = e0 + 1, e[4 * u + 2] = e0 + 2, e[4 * u + 3] = e0 + 3;
-          t[4 * u] = y.x, t[4 * u + 1] = y.y, t[4 * u + 2] = y.z, t[4 * u + 3] = y.w;
+          t[4 * u] = ok ? y.x : -1, t[4 * u + 1] = ok ? y.y : -1, t[4 * u + 2] = ok ? y.z : -1,
+                t[4 * u + 3] = ok ? y.w : -1;
         }
         f(e, t);
       }
@@ -1418,8 +1157,10 @@ __device__ __forceinline__ void inv_entries(const int32_t *__restrict__ ih, int 
 #pragma unroll
       for (int u = 0; u < 4; ++u) {
         const int e0 = 4 * (i + u * INV_THREADS);
+        const bool ok = inv_live(live, (uint32_t)e0, k, rk);
         e[4 * u] = e0, e[4 * u + 1] = e0 + 1, e[4 * u + 2] = e0 + 2, e[4 * u + 3] = e0 + 3;
-        t[4 * u] = x[u].x, t[4 * u + 1] = x[u].y, t[4 * u + 2] = x[u].z, t[4 * u + 3] = x[u].w;
+        t[4 * u] = ok ? x[u].x : -1, t[4 * u + 1] = ok ? x[u].y : -1, t[4 * u + 2] = ok ? x[u].z : -1,
+              t[4 * u + 3] = ok ? x[u].w : -1;
       }
       f(e, t);
     }
@@ -1427,16 +1168,22 @@ __device__ __forceinline__ void inv_entries(const int32_t *__restrict__ ih, int 
     for (int q = 4; q < 16; ++q) e[q] = 0, t[q] = -1;
     for (; i < n4; i += INV_THREADS) {
       const int4 x = v[i];
+      const bool ok = inv_live(live, 4 * (uint32_t)i, k, rk);
       e[0] = 4 * i, e[1] = 4 * i + 1, e[2] = 4 * i + 2, e[3] = 4 * i + 3;
-      t[0] = x.x, t[1] = x.y, t[2] = x.z, t[3] = x.w;
+      t[0] = ok ? x.x : -1, t[1] = ok ? x.y : -1, t[2] = ok ? x.z : -1, t[3] = ok ? x.w : -1;
       f(e, t);
     }
     return;
   }
+  for (; i < per_head; i += 16 * INV_THREADS) {
 #pragma unroll
-  for (int q = 1; q < 16; ++q) e[q] = 0, t[q] = -1;
-  for (; i < per_head; i += INV_THREADS) {
-    e[0] = i, t[0] = ih[i];
+    for (int q = 0; q < 16; ++q) {
+      e[q] = i + q * INV_THREADS;
+      t[q] = e[q] < per_head ? ih[e[q]] : -1;
+    }
+#pragma unroll
+    for (int q = 0; q < 16; ++q)
+      if (e[q] < per_head && !inv_live(live, (uint32_t)e[q], k, rk)) t[q] = -1;
     f(e, t);
   }
 }
@@ -1445,9 +1192,12 @@ __device__ __forceinline__ void inv_entries(const int32_t *__restrict__ ih, int 
 // parts, parts = ceil(N / T); dynamic LDS (T + 2 * INV_WAVES + 64) * 4 bytes.
 __global__ __launch_bounds__(INV_THREADS) void inv_index_kernel(const int32_t *__restrict__ idx,
                                                                 int32_t *__restrict__ start,
-                                                                int32_t *__restrict__ slot, int per_head, int N,
-                                                                int T, int parts, int64_t nwork) {
+                                                                int32_t *__restrict__ slot,
+                                                                const int32_t *__restrict__ offsets, int M, int K,
+                                                                uint32_t rk, int N, int T, int parts, int64_t nwork) {
   extern __shared__ uint32_t inv_lds[];  // counters, wave sums, a spare word per lane
+  __shared__ uint32_t live[1024 / 32];   // the experts with queries (M <= 1024 = INV_THREADS)
+  const int per_head = M * K;
   uint32_t *cnt = inv_lds, *wsum = inv_lds + T;
   // a head's ranges on consecutive slots of one XCD, which share its sets in L2
   const int64_t w = xcd_slot((int)blockIdx.x, (int)(gridDim.x / NXCD));
@@ -1457,12 +1207,21 @@ __global__ __launch_bounds__(INV_THREADS) void inv_index_kernel(const int32_t *_
   const uint32_t nt = (uint32_t)min(N - t0, T);
   const int32_t *ih = idx + bh * per_head;
   for (uint32_t i = threadIdx.x; i < nt; i += INV_THREADS) cnt[i] = 0;
+  {
+    const int32_t *of = offsets + bh * (M + 1);
+    const int i = (int)threadIdx.x;
+    const uint64_t m = __ballot(i < M && of[min(i + 1, M)] > of[min(i, M)]);
+    if ((i & 63) == 0) {
+      live[i >> 5] = (uint32_t)m;
+      live[(i >> 5) + 1] = (uint32_t)(m >> 32);
+    }
+  }
   __syncthreads();
   uint32_t below = 0;
   // (entries of other tokens count into a word of their lane past the
   // counters: atomics without branches, whose results wait only once)
   uint32_t *const spare = inv_lds + T + 2 * INV_WAVES + (threadIdx.x & 63);
-  inv_entries(ih, per_head, [&](const int(&)[16], const int(&t)[16]) {
+  inv_entries(ih, per_head, (uint32_t)K, rk, live, [&](const int(&)[16], const int(&t)[16]) {
 #pragma unroll
     for (int q = 0; q < 16; ++q) {
       const uint32_t r = (uint32_t)t[q] - (uint32_t)t0;
@@ -1503,7 +1262,7 @@ __global__ __launch_bounds__(INV_THREADS) void inv_index_kernel(const int32_t *_
   __syncthreads();  // (the copy above reads the starts before the atomics move them)
   // place: cnt holds each token's next free position (< base + all <= per_head)
   int32_t *sl = slot + bh * per_head;
-  inv_entries(ih, per_head, [&](const int(&e)[16], const int(&t)[16]) {
+  inv_entries(ih, per_head, (uint32_t)K, rk, live, [&](const int(&e)[16], const int(&t)[16]) {
     uint32_t r[16], pos[16];
 #pragma unroll
     for (int q = 0; q < 16; ++q) {
@@ -1547,8 +1306,7 @@ __global__ __launch_bounds__(1024) void inv_scan_kernel(const int32_t *__restric
 // dk_acc, dv_acc of every token = the sum of its staged per-expert rows
 // (written, not added: the first contribution). One thread per 4 dims.
 template <int D>
-__global__ __launch_bounds__(256) void inv_gather_kernel(const float *__restrict__ stage_k,
-                                                         const float *__restrict__ stage_v,
+__global__ __launch_bounds__(256) void inv_gather_kernel(const float *__restrict__ stage,
                                                          const int32_t *__restrict__ start,
                                                          const int32_t *__restrict__ slot, float *__restrict__ dk,
                                                          float *__restrict__ dv, int64_t rows, int N, int per_head) {
@@ -1562,55 +1320,14 @@ __global__ __launch_bounds__(256) void inv_gather_kernel(const float *__restrict
   const int s0 = start[bh * (N + 1) + tok], s1 = start[bh * (N + 1) + tok + 1];
   float4 xk = make_float4(0.f, 0.f, 0.f, 0.f), xv = xk;
   for (int i = s0; i < s1; ++i) {
-    const int64_t src = (bh * (int64_t)per_head + slot[bh * (int64_t)per_head + i]) * D + 4 * c;
-    const float4 yk = *reinterpret_cast<const float4 *>(stage_k + src);
-    const float4 yv = *reinterpret_cast<const float4 *>(stage_v + src);
+    const int64_t src = (bh * (int64_t)per_head + slot[bh * (int64_t)per_head + i]) * (2 * D) + 4 * c;
+    const float4 yk = *reinterpret_cast<const float4 *>(stage + src);
+    const float4 yv = *reinterpret_cast<const float4 *>(stage + src + D);
     xk.x += yk.x; xk.y += yk.y; xk.z += yk.z; xk.w += yk.w;
     xv.x += yv.x; xv.y += yv.y; xv.z += yv.z; xv.w += yv.w;
   }
   *reinterpret_cast<float4 *>(dk + row * D + 4 * c) = xk;
   *reinterpret_cast<float4 *>(dv + row * D + 4 * c) = xv;
-}
-
-// Log-sum-exp (log2 units) of every landmark row's scores, from the score
-// pass's per-chunk (max, sum) partials: LSE_S waves per 64 consecutive rows
-// (a lane per row), wave w combining chunks w, w + LSE_S, ..., then the
-// LSE_S partial pairs of each row combined through LDS.
-constexpr int LSE_S = 16;
-__device__ __forceinline__ void lse_combine(float &m, float &l, float2 x) {
-  const float mn = fmaxf(m, x.x);
-  if (mn == -INFINITY) return;  // (nothing but empty partials so far)
-  l = l * __builtin_amdgcn_exp2f(m - mn) + x.y * __builtin_amdgcn_exp2f(x.x - mn);
-  m = mn;
-}
-__global__ __launch_bounds__(64 * LSE_S) void lse_rows_kernel(const float2 *__restrict__ part_ml,
-                                                              float *__restrict__ lse, int64_t rows, int M,
-                                                              int nch) {
-  __shared__ float2 part[LSE_S][64];
-  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  const int64_t t = (int64_t)blockIdx.x * 64 + lane;
-  float m = -INFINITY, l = 0.f;
-  if (t < rows) {
-    const int64_t bh = t / M;
-    const float2 *src = part_ml + bh * nch * M + (t - bh * M);
-    int c = w;
-    for (; c + 3 * LSE_S < nch; c += 4 * LSE_S) {
-      float2 x[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) x[u] = src[(int64_t)(c + u * LSE_S) * M];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) lse_combine(m, l, x[u]);
-    }
-    for (; c < nch; c += LSE_S) lse_combine(m, l, src[(int64_t)c * M]);
-  }
-  part[w][lane] = make_float2(m, l);
-  __syncthreads();
-  if (w == 0 && t < rows) {
-    m = -INFINITY, l = 0.f;
-#pragma unroll
-    for (int i = 0; i < LSE_S; ++i) lse_combine(m, l, part[i][lane]);
-    lse[t] = m + __log2f(l);
-  }
 }
 
 // The gradients in the io type: dq = the direct part + the pooling backward
@@ -1700,6 +1417,17 @@ __global__ __launch_bounds__(256) void bwd_finish_kernel(const float *__restrict
 // ---------------------------------------------------------------------------
 // launchers
 // ---------------------------------------------------------------------------
+// Rows per chunk for a pass of `blocks` blocks per head and chunk that writes
+// M rows of partial sums per chunk: a multiple of `unit` (at least two units),
+// at most `most`, such that the launch has about `target` workgroups and the
+// head's partial sums fit the N rows of their buffer.
+static int bwd_chunk(const mita_cfg_t &c, int blocks, int unit, int most, int64_t target) {
+  const int64_t want = (BH(c) * blocks * c.N + target - 1) / target;
+  int64_t n = std::min<int64_t>(std::max<int64_t>(2 * unit, (want + unit - 1) / unit * unit), most);
+  while (n < c.N && (c.N + n - 1) / n * c.M > c.N) n += unit;
+  return (int)n;
+}
+
 template <typename T, int D>
 static hipError_t bwd_t(const mita_cfg_t &c, const BwdBufs &b, hipStream_t st) {
   BwdArgs a{};
@@ -1726,16 +1454,9 @@ static hipError_t bwd_t(const mita_cfg_t &c, const BwdBufs &b, hipStream_t st) {
   a.N = c.N;
   a.M = c.M;
   a.topk = c.k;
-  a.chunk = BWD_CHUNK;
   a.scale = eff_scale(c);
   const unsigned bh = (unsigned)BH(c);
   hipError_t err;
-  if (c.use_shared) {
-    const int64_t rows = BH(c) * c.M;
-    hipLaunchKernelGGL(lse_rows_kernel, dim3((unsigned)((rows + 63) / 64)), dim3(64 * LSE_S), 0, st,
-                       (const float2 *)b.part_ml, b.lse_lm, rows, c.M, score_chunks(c));
-    if ((err = launched("lse_rows_kernel", st)) != hipSuccess) return err;
-  }
   // dQ of the MiTA attention, and each query's log-sum-exp and D
   int tiles = (c.N + ATT_TQ - 1) / ATT_TQ;
   if (c.use_routed) tiles = (tiles + c.M + NXCD - 1) / NXCD * NXCD;
@@ -1778,28 +1499,83 @@ static hipError_t bwd_t(const mita_cfg_t &c, const BwdBufs &b, hipStream_t st) {
   kv.offsets = b.offsets;
   kv.q_lse = b.q_lse;
   kv.q_D = b.q_D;
-  kv.stage_k = b.stage_k;
-  kv.stage_v = b.stage_v;
+  kv.perm = c.use_routed ? b.perm : nullptr;
+  kv.offsets = c.use_routed ? b.offsets : nullptr;
+  kv.stage = b.stage;
+  // the landmark rows' partial sums, in the buffers of the keys' sums, which
+  // are not in use yet: at most N rows per head (bwd_chunk)
+  kv.part_k = b.dk_acc;
+  kv.part_v = b.dv_acc;
   kv.dq_lm = b.dq_lm_acc;
-  kv.dv_lm = b.dv_lm_acc;
   kv.N = c.N;
   kv.M = c.M;
   kv.topk = c.k;
   kv.scale = eff_scale(c);
-  // bf16 with the landmark values: their key pass owns every token row, so it
-  // also sums the routed keys' staged rows and writes dk, dv (no gather pass,
-  // no fp32 accumulators of the keys)
   const bool fused_finish = sizeof(T) == 2 && c.use_shared;
+  if (c.use_shared) {
+    // shared keys (the landmarks): partial sums per landmark block and query
+    // chunk, then their sums with the landmark rows' log-sum-exps. About one
+    // workgroup per CU slot (three 4-wave workgroups per CU; the fp32
+    // kernel's two): fewer leave CUs idle, more only add partial sums.
+    int nchunk = 0;
+    auto shared_keys = [&](int kb, int64_t target) {
+      kv.nblk = (c.M + kb - 1) / kb;
+      kv.qchunk = bwd_chunk(c, kv.nblk, 64, c.N, target);
+      nchunk = (c.N + kv.qchunk - 1) / kv.qchunk;
+      kv.ntotal = kv.nblk * nchunk;
+      return dim3((unsigned)((kv.ntotal + NXCD - 1) / NXCD * NXCD), bh);
+    };
+    if constexpr (sizeof(T) == 2) {
+      constexpr int NG = BWD16_GROUPS<D>;
+      bool two = false;
+      if constexpr (D == 64) {
+        two = c.M <= 64;  // two waves cover the block
+        if (two) {
+          const dim3 g = shared_keys(KvTile<D, NG, 2>::KB, 1536);
+          hipLaunchKernelGGL((bwd_kv16_kernel<D, KV_SHARED, NG, 2>), g, dim3(128), 0, st, kv);
+        }
+      }
+      if (!two) {
+        const dim3 g = shared_keys(KvTile<D, NG, 4>::KB, 768);
+        hipLaunchKernelGGL((bwd_kv16_kernel<D, KV_SHARED, NG, 4>), g, dim3(256), 0, st, kv);
+      }
+    } else {
+      const dim3 g = shared_keys(BWD_KB, 512);
+      hipLaunchKernelGGL((bwd_kv_kernel<T, D, false>), g, dim3(256), 0, st, kv);
+    }
+    if ((err = launched("bwd_kv_shared_kernel", st)) != hipSuccess) return err;
+    const int64_t mrows = BH(c) * c.M;
+    hipLaunchKernelGGL((bwd_prep_kernel<T, D>), dim3((unsigned)((mrows + 3) / 4)), dim3(256), 0, st,
+                       kv.part_k, kv.part_v, nchunk, (const T *)b.v_lm, b.dq_lm_acc, b.dv_lm_acc,
+                       sizeof(T) == 2 ? (bf16_t *)b.dv_lm16 : nullptr, b.D_lm, (const float2 *)b.part_ml, b.lse_lm,
+                       mrows, c.M, score_chunks(c));
+    if ((err = launched("bwd_prep_kernel", st)) != hipSuccess) return err;
+  }
   if (c.use_routed) {
     // routed keys: per-expert sums staged, then summed per token
-    kv.nblk = (c.k + BWD_KB - 1) / BWD_KB;
-    kv.ntotal = c.M * kv.nblk;
-    const unsigned nx = (unsigned)((kv.ntotal + NXCD - 1) / NXCD * NXCD);
-    if constexpr (sizeof(T) == 2)
-      hipLaunchKernelGGL((bwd_kv16_kernel<D, KV_ROUTED, BWD16_GROUPS<D>>), dim3(nx, bh), dim3(256 / BWD16_GROUPS<D>), 0, st,
-                         kv);
-    else
-      hipLaunchKernelGGL((bwd_kv_kernel<T, D, true>), dim3(nx, bh), dim3(256), 0, st, kv);
+    auto routed_keys = [&](int kb) {
+      kv.nblk = (c.k + kb - 1) / kb;
+      kv.ntotal = c.M * kv.nblk;
+      return dim3((unsigned)((kv.ntotal + NXCD - 1) / NXCD * NXCD), bh);
+    };
+    if constexpr (sizeof(T) == 2) {
+      constexpr int NG = BWD16_GROUPS<D>;
+      bool two = false;
+      if constexpr (D == 64) {
+        two = c.k <= 64;  // two waves cover the block
+        if (two) {
+          const dim3 g = routed_keys(KvTile<D, NG, 2>::KB);
+          hipLaunchKernelGGL((bwd_kv16_kernel<D, KV_ROUTED, NG, 2>), g, dim3(128), 0, st, kv);
+        }
+      }
+      if (!two) {
+        const dim3 g = routed_keys(KvTile<D, NG, 4>::KB);
+        hipLaunchKernelGGL((bwd_kv16_kernel<D, KV_ROUTED, NG, 4>), g, dim3(256), 0, st, kv);
+      }
+    } else {
+      const dim3 g = routed_keys(BWD_KB);
+      hipLaunchKernelGGL((bwd_kv_kernel<T, D, true>), g, dim3(256), 0, st, kv);
+    }
     if ((err = launched("bwd_kv_kernel", st)) != hipSuccess) return err;
     const int per_head = c.M * c.k;
     // token ranges per head: about one workgroup per CU over all heads (a
@@ -1811,65 +1587,57 @@ static hipError_t bwd_t(const mita_cfg_t &c, const BwdBufs &b, hipStream_t st) {
     const int span = (c.N + parts - 1) / parts;
     parts = (c.N + span - 1) / span;
     const int64_t nwork = heads * parts;
+    const uint32_t rk = (uint32_t)std::min<uint64_t>(UINT32_MAX, (1ull << 32) / (uint64_t)c.k);
     hipLaunchKernelGGL(inv_index_kernel, dim3((unsigned)((nwork + NXCD - 1) / NXCD * NXCD)), dim3(INV_THREADS),
-                       (size_t)(span + 2 * INV_WAVES + 64) * 4, st, b.idx, b.inv_start, b.inv_slot, per_head, c.N, span, parts,
-                       nwork);
+                       (size_t)(span + 2 * INV_WAVES + 64) * 4, st, b.idx, b.inv_start, b.inv_slot, b.offsets, c.M, c.k,
+                       rk, c.N, span, parts, nwork);
     if ((err = launched("inv_index_kernel", st)) != hipSuccess) return err;
     if (!fused_finish) {  // (else the landmark-value key pass sums the staged rows)
       const int64_t rows = BH(c) * c.N;
       hipLaunchKernelGGL((inv_gather_kernel<D>), dim3((unsigned)((rows * (D / 4) + 255) / 256)), dim3(256), 0, st,
-                         b.stage_k, b.stage_v, b.inv_start, b.inv_slot, b.dk_acc, b.dv_acc, rows, c.N, per_head);
+                         b.stage, b.inv_start, b.inv_slot, b.dk_acc, b.dv_acc, rows, c.N, per_head);
       if ((err = launched("inv_gather_kernel", st)) != hipSuccess) return err;
     }
+  } else if (!fused_finish) {  // no routed keys: the landmark values' sums are added to zero
+    const int64_t nd = BH(c) * c.N * c.d;
+    if ((err = launch_zero2((int32_t *)b.dk_acc, nd, (int32_t *)b.dv_acc, nd, st)) != hipSuccess) return err;
   }
   if (c.use_shared) {
-    // shared keys (the landmarks): atomic adds per landmark block and query chunk
-    kv.nblk = (c.M + BWD_KB - 1) / BWD_KB;
-    kv.ntotal = kv.nblk * ((c.N + BWD_QCHUNK - 1) / BWD_QCHUNK);
-    const unsigned nx = (unsigned)((kv.ntotal + NXCD - 1) / NXCD * NXCD);
-    if constexpr (sizeof(T) == 2)
-      hipLaunchKernelGGL((bwd_kv16_kernel<D, KV_SHARED, BWD16_GROUPS<D>>), dim3(nx, bh), dim3(256 / BWD16_GROUPS<D>), 0,
-                         st, kv);
-    else
-      hipLaunchKernelGGL((bwd_kv_kernel<T, D, false>), dim3(nx, bh), dim3(256), 0, st, kv);
-    if ((err = launched("bwd_kv_shared_kernel", st)) != hipSuccess) return err;
-    // the landmark values (Eq. landmark-value), once their gradient is complete
-    const int nlb = (c.M + BWD_TQ - 1) / BWD_TQ, nch = (c.N + BWD_CHUNK - 1) / BWD_CHUNK;
+    // the landmark values (Eq. landmark-value)
+    const int nlb = (c.M + BWD_TQ - 1) / BWD_TQ;
     if constexpr (sizeof(T) == 2) {
       // bf16: the landmark queries' gradient by landmark blocks and key
-      // chunks (atomic adds per chunk), then the keys' gradient by token
-      // blocks with all landmark rows streamed (each row added once)
-      const int64_t mrows = BH(c) * c.M;
-      hipLaunchKernelGGL((lmv_prep_kernel<D>), dim3((unsigned)((mrows * (D / 8) + 255) / 256)), dim3(256), 0, st,
-                         b.dv_lm_acc, (const bf16_t *)b.v_lm, (bf16_t *)b.dv_lm16, b.D_lm, mrows);
-      if ((err = launched("lmv_prep_kernel", st)) != hipSuccess) return err;
+      // chunks (partial sums per chunk), then the keys' gradient by token
+      // blocks with all landmark rows streamed; that kernel's spare blocks add
+      // up the partial sums, and it also sums the routed keys' staged rows and
+      // writes dk, dv (no gather pass, no fp32 accumulators of the keys)
+      constexpr int NG = BWD16_GROUPS<D>;
       a.dv_lm16 = b.dv_lm16;
       a.D_lm = b.D_lm;
-      constexpr int NG = BWD16_GROUPS<D>;
-      // longer key chunks than the fp32 kernel's: fewer atomic adds of the
-      // partial sums, which all chunks of a landmark block add to the same rows
-      a.chunk = BWD16_LMV_CHUNK;
-      const int nch16 = (c.N + BWD16_LMV_CHUNK - 1) / BWD16_LMV_CHUNK;
+      a.dq_part = b.dk_acc;
+      a.chunk = bwd_chunk(c, nlb, BWD16_TK, BWD16_LMV_CHUNK, 1024);
+      const int nch16 = (c.N + a.chunk - 1) / a.chunk;
       hipLaunchKernelGGL((bwd_att16_kernel<D, false, false, NG, true>), dim3((unsigned)(nlb * nch16), bh),
-                         dim3(256 / NG), (size_t)BWD16_LMV_CHUNK * sizeof(uint32_t), st, a);
+                         dim3(256 / NG), (size_t)a.chunk * sizeof(uint32_t), st, a);
       if ((err = launched("bwd_landmark_kernel", st)) != hipSuccess) return err;
       kv.dv_lm16 = b.dv_lm16;
       kv.lse_lm = b.lse_lm;
       kv.D_lm = b.D_lm;
-      kv.dk_acc = b.dk_acc;
-      kv.dv_acc = b.dv_acc;
       kv.inv_start = c.use_routed ? b.inv_start : nullptr;
       kv.inv_slot = c.use_routed ? b.inv_slot : nullptr;
       kv.dk_out = b.dk;
       kv.dv_out = b.dv;
-      kv.ntotal = (c.N + BWD_KB - 1) / BWD_KB;
-      const unsigned nxl = (unsigned)((kv.ntotal + NXCD - 1) / NXCD * NXCD);
-      if constexpr (D == 64)
-        hipLaunchKernelGGL((bwd_kv16_lmv64_kernel<NG>), dim3(nxl, bh), dim3(256 / NG), 0, st, kv);
-      else
-        hipLaunchKernelGGL((bwd_kv16_kernel<D, KV_LMV, NG>), dim3(nxl, bh), dim3(256 / NG), 0, st, kv);
+      kv.dq_part = b.dk_acc;
+      kv.nred = nch16;
+      kv.ntotal = (c.N + KvTile<D, NG, 4>::KB - 1) / KvTile<D, NG, 4>::KB;
+      const int nred_blocks = std::min(8, (c.M * D / 4 + 255) / 256);
+      const unsigned nxl = (unsigned)((kv.ntotal + NXCD - 1) / NXCD * NXCD + nred_blocks);
+      hipLaunchKernelGGL((bwd_kv16_kernel<D, KV_LMV, NG, 4>), dim3(nxl, bh), dim3(256), 0, st, kv);
       if ((err = launched("bwd_kv_landmark_kernel", st)) != hipSuccess) return err;
     } else {
+      // (its atomic adds to the landmark rows come once per chunk)
+      a.chunk = bwd_chunk(c, nlb, BWD_TK, BWD_CHUNK, 512);
+      const int nch = (c.N + a.chunk - 1) / a.chunk;
       hipLaunchKernelGGL((bwd_kernel<T, D, BWD_LMV, true, false>), dim3((unsigned)(nlb * nch), bh), dim3(256), 0,
                          st, a);
       if ((err = launched("bwd_landmark_kernel", st)) != hipSuccess) return err;

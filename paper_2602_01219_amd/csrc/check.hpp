@@ -301,7 +301,7 @@ inline FwdLayout forward_layout(const mita_cfg_t &c) {
 // buffers.
 struct BwdLayout {
   FwdLayout f;
-  size_t lse_lm, dq_direct, dk_acc, dv_acc, dq_lm_acc, dv_lm_acc, q_lse, q_D, stage_k, stage_v, inv_start, inv_slot,
+  size_t lse_lm, dq_direct, dk_acc, dv_acc, dq_lm_acc, dv_lm_acc, q_lse, q_D, stage, inv_start, inv_slot,
       dv_lm16, D_lm, total;
 };
 
@@ -323,9 +323,8 @@ inline BwdLayout backward_layout(const mita_cfg_t &c) {
   L.dv_lm_acc = take(md);
   L.q_lse = take(bh * c.N * 4);
   L.q_D = take(bh * c.N * 4);
-  const size_t stage = c.use_routed ? bh * c.M * (size_t)c.k * c.d * 4 : 0;
-  L.stage_k = take(stage);
-  L.stage_v = take(stage);
+  // a slot's dK row, then its dV row
+  L.stage = take(c.use_routed ? bh * c.M * (size_t)c.k * c.d * 4 * 2 : 0);
   L.inv_start = take(c.use_routed ? bh * (c.N + 1) * 4 : 0);
   L.inv_slot = take(c.use_routed ? bh * c.M * (size_t)c.k * 4 : 0);
   // the landmark values' gradient in bf16 and each landmark row's dV~ . V~

@@ -117,7 +117,7 @@ hipError_t launch_select_landmarks(const mita_cfg_t &c, const void *q, const int
 
 // Backward pass (gradients with the top-k sets and routing held fixed).
 // Inputs: the forward's tensors and the state its recomputation left in the
-// workspace; accumulators zeroed beforehand.
+// workspace.
 struct BwdBufs {
   const void *q, *k, *v, *o, *dO;  // [BH, N, d]
   const void *q_lm, *v_lm;         // [BH, M, d]
@@ -125,10 +125,12 @@ struct BwdBufs {
   const void *part_ml;             // score-pass partials (max, sum) per key chunk
   float *lse_lm;                   // [BH, M] (written)
   float *dq_direct;                // [BH, N, d] (written)
-  float *dk_acc, *dv_acc;          // [BH, N, d] (zeroed)
-  float *dq_lm_acc, *dv_lm_acc;    // [BH, M, d] (zeroed)
-  float *q_lse, *q_D;              // [BH, N] per-query log-sum-exp and dO . o (written)
-  float *stage_k, *stage_v;        // [BH, M, k, d] per-expert sums of the routed keys (written)
+  float *dk_acc, *dv_acc;          // [BH, N, d] the keys' sums (fp32, or without landmark values); before that the
+                                   // landmark rows' partial sums
+  float *dq_lm_acc, *dv_lm_acc;    // [BH, M, d] (written)
+  float *q_lse, *q_D;              // [BH, N] log-sum-exp and dO . o per item (written)
+  float *stage;                    // [BH, M, k, 2, d] per-expert sums of the routed keys (written for experts with
+                                   // queries)
   int32_t *inv_start, *inv_slot;   // inverse index of the top-k sets: [BH, N + 1], [BH, M * k]
   void *dv_lm16;                   // [BH, M, d] bf16 copy of the landmark values' gradient
   float *D_lm;                     // [BH, M] dV~ . V~ per landmark row

@@ -100,6 +100,83 @@ hipError_t mita::launched(const char *kernel, hipStream_t st) {
 
 namespace {
 
+// Everything before the attention: landmarks (q_lm_in: given, or NULL to pool
+// them), scores with landmark values, top-k sets, expert tiles when `staged`,
+// and routing, into the workspace w laid out as L (stages 0 to 4).
+int enqueue_experts(const mita_cfg_t *c, const void *q, const void *k, const void *v, const void *q_lm_in, char *w,
+                    const FwdLayout &L, bool staged, Recording &rec, hipStream_t st) {
+  void *q_lm_ws = w + L.q_lm;
+  const void *q_lm = q_lm_in ? q_lm_in : q_lm_ws;
+  void *v_lm = c->use_shared ? (void *)(w + L.v_lm) : nullptr;
+  float *S = c->use_routed ? (float *)(w + L.scores) : nullptr;
+  int32_t *idx = (int32_t *)(w + L.idx);
+  int32_t *expert = (int32_t *)(w + L.expert), *perm = (int32_t *)(w + L.perm);
+  int32_t *offsets = (int32_t *)(w + L.offsets), *tile_cnt = (int32_t *)(w + L.tile_cnt);
+  int32_t *tile_base = (int32_t *)(w + L.tile_base), *tile_start = (int32_t *)(w + L.tile_start);
+  int32_t *counts = (int32_t *)(w + L.counts);
+  const bool fused = fused_select(*c);
+  SelectBufs sel{};
+  if (fused) {
+    sel.plo = (uint32_t *)(w + L.plo);
+    sel.ccnt = (uint32_t *)(w + L.ccnt);
+    sel.cand = (uint2 *)(w + L.cand);
+    sel.fail_cnt = (uint32_t *)(w + L.fail);
+    sel.fail_list = (int32_t *)(w + L.fail) + 1;
+    sel.ns = sel_ns(*c);
+    sel.cap = sel_cap(*c);
+    sel.rank = sel_rank(*c);
+    sel.idx = sel.ns == c->N ? idx : nullptr;  // the sample is the row: the pivot launch writes the sets
+  }
+  const bool direct = fused && sel.idx;
+
+  // with the fused selection and in-place gather, the selection's finish
+  // shares launches with the routing (the "route" stage then includes it),
+  // whose placement cursors (in the tile_base buffer) start at zero
+  // s > 1 routes through its own launches (stable grouping of the pairs)
+  const bool multi = multi_route(*c);
+  const bool sel_in_route = fused && c->use_routed && !staged && !multi;
+  int32_t *group = multi ? (int32_t *)(w + L.group) : nullptr;
+  rec.stage = 0;
+  int32_t *zero_counts = c->use_routed && !multi ? counts : nullptr;
+  int32_t *zero_cursor = sel_in_route ? tile_base : nullptr;
+  if (q_lm_in) {
+    TRY(hip_status(launch_zero2(zero_counts, zero_counts ? BH(*c) * c->M : 0, zero_cursor,
+                                zero_cursor ? BH(*c) * c->M : 0, st),
+                   "landmarks"));
+  } else {
+    TRY(hip_status(launch_pool(*c, q, q_lm_ws, zero_counts, zero_cursor, st), "landmarks"));
+  }
+  rec.stage = 1;
+  // bf16: the routing logits are formed beside the sampled scores (they
+  // depend on the landmarks only), in the same launch
+  const bool logits_early = sel_in_route && !direct && pivots_with_logits(*c, sel);
+  if (logits_early)
+    TRY(hip_status(launch_pivots_logits(*c, q, q_lm, k, sel, expert, counts, st), "select pivots"));
+  else if (fused)
+    TRY(hip_status(launch_select_pivots(*c, q_lm, k, sel, st), "select pivots"));
+  // (direct selection: the score pass forms the landmark values only)
+  TRY(hip_status(launch_scores(*c, q_lm, k, v, fused ? nullptr : S, v_lm, w + L.partial,
+                               fused && !direct ? &sel : nullptr, st),
+                 "scores"));
+  rec.stage = 2;
+  if (fused && !sel_in_route)
+    TRY(hip_status(launch_select_finish(*c, q_lm, k, sel, S, idx, w + L.partial, v_lm, st), "topk"));
+  else if (!fused && c->use_routed)
+    TRY(hip_status(launch_topk(*c, S, idx, st), "topk"));
+  rec.stage = 3;
+  if (staged) TRY(hip_status(launch_gather(*c, k, v, idx, w + L.kx, w + L.vx, st), "gather"));
+  rec.stage = 4;
+  if (sel_in_route)
+    TRY(hip_status(launch_select_route(*c, q, q_lm, k, sel, S, idx, w + L.partial, v_lm, expert, perm, offsets,
+                                       tile_cnt, tile_base, counts, tile_start, logits_early, st),
+                   "route"));
+  else if (c->use_routed)
+    TRY(hip_status(
+        launch_route(*c, q, q_lm, expert, perm, offsets, tile_cnt, tile_base, counts, tile_start, group, st),
+        "route"));
+  return MITA_OK;
+}
+
 // q_lm_in: caller-supplied landmark queries (mita_forward_lm), or NULL to pool them.
 int forward_impl(const mita_cfg_t *c, const void *q, const void *k, const void *v, void *o, void *ws,
                  size_t ws_bytes, hipStream_t st, mita_timer *timer, const void *q_lm_in = nullptr) {
@@ -128,87 +205,20 @@ int forward_impl(const mita_cfg_t *c, const void *q, const void *k, const void *
     explicit Scope(Recording *r) : prev(g_rec) { g_rec = r->t ? r : nullptr; }
     ~Scope() { g_rec = prev; }
   } scope(&rec);
-  auto mark = [&](int stage) -> int {
-    rec.stage = stage;
-    return MITA_OK;
-  };
-
   const FwdLayout L = forward_layout(*c);
   char *w = (char *)ws;
-  void *q_lm_ws = w + L.q_lm;
-  const void *q_lm = q_lm_in ? q_lm_in : q_lm_ws;
+  const void *q_lm = q_lm_in ? q_lm_in : w + L.q_lm;
   void *v_lm = c->use_shared ? (void *)(w + L.v_lm) : nullptr;
-  float *S = c->use_routed ? (float *)(w + L.scores) : nullptr;
   int32_t *idx = (int32_t *)(w + L.idx);
   const bool staged = c->use_routed && (c->flags & MITA_FLAG_STAGED_GATHER);
   void *kx = w + L.kx, *vx = w + L.vx;
-  int32_t *expert = (int32_t *)(w + L.expert), *perm = (int32_t *)(w + L.perm);
-  int32_t *offsets = (int32_t *)(w + L.offsets), *tile_cnt = (int32_t *)(w + L.tile_cnt);
-  int32_t *tile_base = (int32_t *)(w + L.tile_base), *tile_start = (int32_t *)(w + L.tile_start);
-  int32_t *counts = (int32_t *)(w + L.counts);
-  const bool fused = fused_select(*c);
-  SelectBufs sel{};
-  if (fused) {
-    sel.plo = (uint32_t *)(w + L.plo);
-    sel.ccnt = (uint32_t *)(w + L.ccnt);
-    sel.cand = (uint2 *)(w + L.cand);
-    sel.fail_cnt = (uint32_t *)(w + L.fail);
-    sel.fail_list = (int32_t *)(w + L.fail) + 1;
-    sel.ns = sel_ns(*c);
-    sel.cap = sel_cap(*c);
-    sel.rank = sel_rank(*c);
-    sel.idx = sel.ns == c->N ? idx : nullptr;  // the sample is the row: the pivot launch writes the sets
-  }
-  const bool direct = fused && sel.idx;
-
-  // with the fused selection and in-place gather, the selection's finish
-  // shares launches with the routing (the "route" stage then includes it),
-  // whose placement cursors (in the tile_base buffer) start at zero
-  // s > 1 routes through its own launches (stable grouping of the pairs)
+  const int32_t *perm = (int32_t *)(w + L.perm), *offsets = (int32_t *)(w + L.offsets);
+  const int32_t *tile_start = (int32_t *)(w + L.tile_start);
   const bool multi = multi_route(*c);
-  const bool sel_in_route = fused && c->use_routed && !staged && !multi;
-  int32_t *group = multi ? (int32_t *)(w + L.group) : nullptr;
   float *pair_o = multi ? (float *)(w + L.pair_o) : nullptr;
   float *pair_lse = multi ? (float *)(w + L.pair_lse) : nullptr;
-  TRY(mark(0));
-  int32_t *zero_counts = c->use_routed && !multi ? counts : nullptr;
-  int32_t *zero_cursor = sel_in_route ? tile_base : nullptr;
-  if (q_lm_in) {
-    TRY(hip_status(launch_zero2(zero_counts, zero_counts ? BH(*c) * c->M : 0, zero_cursor,
-                                zero_cursor ? BH(*c) * c->M : 0, st),
-                   "landmarks"));
-  } else {
-    TRY(hip_status(launch_pool(*c, q, q_lm_ws, zero_counts, zero_cursor, st), "landmarks"));
-  }
-  TRY(mark(1));
-  // bf16: the routing logits are formed beside the sampled scores (they
-  // depend on the landmarks only), in the same launch
-  const bool logits_early = sel_in_route && !direct && pivots_with_logits(*c, sel);
-  if (logits_early)
-    TRY(hip_status(launch_pivots_logits(*c, q, q_lm, k, sel, expert, counts, st), "select pivots"));
-  else if (fused)
-    TRY(hip_status(launch_select_pivots(*c, q_lm, k, sel, st), "select pivots"));
-  // (direct selection: the score pass forms the landmark values only)
-  TRY(hip_status(launch_scores(*c, q_lm, k, v, fused ? nullptr : S, v_lm, w + L.partial,
-                               fused && !direct ? &sel : nullptr, st),
-                 "scores"));
-  TRY(mark(2));
-  if (fused && !sel_in_route)
-    TRY(hip_status(launch_select_finish(*c, q_lm, k, sel, S, idx, w + L.partial, v_lm, st), "topk"));
-  else if (!fused && c->use_routed)
-    TRY(hip_status(launch_topk(*c, S, idx, st), "topk"));
-  TRY(mark(3));
-  if (staged) TRY(hip_status(launch_gather(*c, k, v, idx, kx, vx, st), "gather"));
-  TRY(mark(4));
-  if (sel_in_route)
-    TRY(hip_status(launch_select_route(*c, q, q_lm, k, sel, S, idx, w + L.partial, v_lm, expert, perm, offsets,
-                                       tile_cnt, tile_base, counts, tile_start, logits_early, st),
-                   "route"));
-  else if (c->use_routed)
-    TRY(hip_status(
-        launch_route(*c, q, q_lm, expert, perm, offsets, tile_cnt, tile_base, counts, tile_start, group, st),
-        "route"));
-  TRY(mark(5));
+  TRY(enqueue_experts(c, q, k, v, q_lm_in, w, L, staged, rec, st));
+  rec.stage = 5;
   TRY(hip_status(launch_attend(*c, q, q_lm, v_lm, staged ? kx : k, staged ? vx : v, staged ? nullptr : idx, perm,
                                offsets, tile_start, o, pair_o, pair_lse, st),
                  "attend"));
@@ -254,56 +264,13 @@ int backward_impl(const mita_cfg_t *c, const void *q, const void *k, const void 
   char *w = (char *)ws;
   void *q_lm = w + L.q_lm;
   void *v_lm = c->use_shared ? (void *)(w + L.v_lm) : nullptr;
-  float *S = c->use_routed ? (float *)(w + L.scores) : nullptr;
   int32_t *idx = (int32_t *)(w + L.idx);
-  int32_t *expert = (int32_t *)(w + L.expert), *perm = (int32_t *)(w + L.perm);
-  int32_t *offsets = (int32_t *)(w + L.offsets), *tile_cnt = (int32_t *)(w + L.tile_cnt);
-  int32_t *tile_base = (int32_t *)(w + L.tile_base), *tile_start = (int32_t *)(w + L.tile_start);
-  int32_t *counts = (int32_t *)(w + L.counts);
-  const bool fused = fused_select(*c);
-  SelectBufs sel{};
-  if (fused) {
-    sel.plo = (uint32_t *)(w + L.plo);
-    sel.ccnt = (uint32_t *)(w + L.ccnt);
-    sel.cand = (uint2 *)(w + L.cand);
-    sel.fail_cnt = (uint32_t *)(w + L.fail);
-    sel.fail_list = (int32_t *)(w + L.fail) + 1;
-    sel.ns = sel_ns(*c);
-    sel.cap = sel_cap(*c);
-    sel.rank = sel_rank(*c);
-    sel.idx = sel.ns == c->N ? idx : nullptr;  // the sample is the row: the pivot launch writes the sets
-  }
-  // recomputation (stages 0 to 4)
-  rec.stage = 0;
-  TRY(hip_status(launch_pool(*c, q, q_lm, c->use_routed ? counts : nullptr, nullptr, st), "landmarks"));
-  rec.stage = 1;
-  if (c->use_routed) {
-    if (fused) {
-      TRY(hip_status(launch_select_pivots(*c, q_lm, k, sel, st), "select pivots"));
-      TRY(hip_status(launch_scores(*c, q_lm, k, v, nullptr, v_lm, w + L.partial, sel.idx ? nullptr : &sel, st),
-                     "scores"));
-      rec.stage = 2;
-      TRY(hip_status(launch_select_finish(*c, q_lm, k, sel, S, idx, w + L.partial, v_lm, st), "topk"));
-    } else {
-      TRY(hip_status(launch_scores(*c, q_lm, k, v, S, v_lm, w + L.partial, nullptr, st), "scores"));
-      rec.stage = 2;
-      TRY(hip_status(launch_topk(*c, S, idx, st), "topk"));
-    }
-    rec.stage = 4;
-    TRY(hip_status(launch_route(*c, q, q_lm, expert, perm, offsets, tile_cnt, tile_base, counts, tile_start, nullptr,
-                                st),
-                   "route"));
-  } else {
-    TRY(hip_status(launch_scores(*c, q_lm, k, v, nullptr, v_lm, w + L.partial, nullptr, st), "scores"));
-  }
+  const int32_t *perm = (int32_t *)(w + L.perm), *offsets = (int32_t *)(w + L.offsets);
+  const int32_t *tile_start = (int32_t *)(w + L.tile_start);
+  // recomputation (stages 0 to 4), with the forward's own launches
+  TRY(enqueue_experts(c, q, k, v, nullptr, w, L, false, rec, st));
   // gradients (stage 5)
   rec.stage = 5;
-  const int64_t nd = BH(*c) * c->N * c->d, md = BH(*c) * c->M * c->d;
-  if (!c->use_routed) {  // with routing, the routed keys' gather writes dk_acc and dv_acc first
-    TRY(hip_status(launch_zero2((int32_t *)(w + BL.dk_acc), nd, (int32_t *)(w + BL.dv_acc), nd, st), "backward"));
-  }
-  TRY(hip_status(launch_zero2((int32_t *)(w + BL.dq_lm_acc), md, (int32_t *)(w + BL.dv_lm_acc), md, st),
-                 "backward"));
   BwdBufs b{};
   b.q = q;
   b.k = k;
@@ -325,8 +292,7 @@ int backward_impl(const mita_cfg_t *c, const void *q, const void *k, const void 
   b.dv_lm_acc = (float *)(w + BL.dv_lm_acc);
   b.q_lse = (float *)(w + BL.q_lse);
   b.q_D = (float *)(w + BL.q_D);
-  b.stage_k = (float *)(w + BL.stage_k);
-  b.stage_v = (float *)(w + BL.stage_v);
+  b.stage = (float *)(w + BL.stage);
   b.inv_start = (int32_t *)(w + BL.inv_start);
   b.inv_slot = (int32_t *)(w + BL.inv_slot);
   b.dv_lm16 = w + BL.dv_lm16;
