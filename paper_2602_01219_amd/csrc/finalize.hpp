@@ -7,6 +7,7 @@
 #include "flash.hpp"
 #include "check.hpp"
 #include "sample.hpp"
+#include "scores.hpp"
 
 namespace mita {
 
@@ -44,7 +45,7 @@ __device__ __forceinline__ void finalize_row(FinalizeLds<T, D, CAP, MERGE> &sh, 
                                              int32_t *__restrict__ idx, uint32_t *__restrict__ fail_cnt,
                                              int32_t *__restrict__ fail_list, int k, int cap, int nch,
                                              const float2 *__restrict__ part_ml, const float *__restrict__ part_o,
-                                             T *__restrict__ v_lm, int M, float scale) {
+                                             T *__restrict__ v_lm, int M, float scale, LiveRows live) {
   auto &red = sh.red;
   auto &lst = sh.lst;
   auto &pre = sh.pre;
@@ -71,8 +72,9 @@ __device__ __forceinline__ void finalize_row(FinalizeLds<T, D, CAP, MERGE> &sh, 
     total += wsum[0][i];
   }
   if (tid <= nch) pre[tid] = before + wincl - cc;
-  if (total < (uint32_t)k || total > (uint32_t)cap) {  // uniform
-    if (tid == 0) fail_list[atomicAdd(fail_cnt, 1u)] = (int32_t)row;
+  const bool miss = total < (uint32_t)k || total > (uint32_t)cap;
+  if (miss || !live(row / M, (int)(row % M), M)) {  // uniform
+    if (miss && tid == 0) fail_list[atomicAdd(fail_cnt, 1u)] = (int32_t)row;
     if (MERGE) lmm.finish(part_ml, part_o, v_lm, row / M, (int)(row % M), M, nch, red);
     return;
   }
@@ -226,7 +228,7 @@ __device__ __forceinline__ void finalize_row_wave(FinalizeWaveLds &sh, int64_t r
                                                   uint32_t *__restrict__ fail_cnt, int32_t *__restrict__ fail_list,
                                                   int k, int cap, int nch, const float2 *__restrict__ part_ml,
                                                   const float *__restrict__ part_o, T *__restrict__ v_lm, int M,
-                                                  float scale) {
+                                                  float scale, LiveRows live) {
   const int lane = threadIdx.x & 63;
   // the landmark-value partials are loaded first; the merge uses them last
   constexpr int DL = D / 64;  // dimensions per lane
@@ -239,7 +241,9 @@ __device__ __forceinline__ void finalize_row_wave(FinalizeWaveLds &sh, int64_t r
   const uint32_t incl = wave_inclusive_scan(cc);
   const uint32_t total = (uint32_t)__shfl((int)incl, 63);
   const uint32_t excl = incl - cc;
-  if (total >= (uint32_t)k && total <= (uint32_t)cap) {
+  if (total < (uint32_t)k || total > (uint32_t)cap) {
+    if (lane == 0) fail_list[atomicAdd(fail_cnt, 1u)] = (int32_t)row;
+  } else if (live(row / M, (int)(row % M), M)) {
     // the list into LDS, the first 64 entries of four chunks loaded before any is stored
     const uint2 *crow = cand + row * nch * (int64_t)SCORE_NC;
     for (int c0 = 0; c0 < nch; c0 += 4) {
@@ -286,8 +290,6 @@ __device__ __forceinline__ void finalize_row_wave(FinalizeWaveLds &sh, int64_t r
       taken += (uint32_t)__popcll(bt);
       eq_seen += (uint32_t)__popcll(be);
     }
-  } else if (lane == 0) {
-    fail_list[atomicAdd(fail_cnt, 1u)] = (int32_t)row;
   }
   if (MERGE)
 #pragma unroll

@@ -37,6 +37,11 @@ struct SelectBufs {
   // writes the top-k sets here itself, the score pass lists nothing and the
   // finish selects nothing (direct selection)
   int32_t *idx;
+  // the routing's group sizes [BH, live_groups] when they are known before the
+  // score pass (else NULL): rows of experts without queries are counted but
+  // not selected
+  const int32_t *live;
+  int live_groups;
 };
 
 // Scores S = fl(q_lm . k) * scale (optional) and landmark values (optional):
@@ -60,6 +65,11 @@ hipError_t launch_select_pivots(const mita_cfg_t &c, const void *q_lm, const voi
 hipError_t launch_select_finish(const mita_cfg_t &c, const void *q_lm, const void *k, const SelectBufs &sel,
                                 float *S, int32_t *idx, const void *partial, void *v_lm, hipStream_t st);
 
+// Its first launch alone: the rows whose list holds the top-k, the others
+// listed as fallback rows, and the landmark-value merge.
+hipError_t launch_select_finalize(const mita_cfg_t &c, const SelectBufs &sel, int32_t *idx, const void *partial,
+                                  void *v_lm, hipStream_t st);
+
 // Score rows of the listed landmark rows only (fallback of the fused selection).
 hipError_t launch_scores_rows(const mita_cfg_t &c, const void *q_lm, const void *k, float *S,
                               const uint32_t *nrows, const int32_t *rows, hipStream_t st);
@@ -81,23 +91,27 @@ hipError_t launch_route(const mita_cfg_t &c, const void *q, const void *q_lm, in
                         int32_t *offsets, int32_t *tile_cnt, int32_t *tile_base, int32_t *counts,
                         int32_t *tile_start, int32_t *group, hipStream_t st);
 
-// The finish of the fused selection (launch_select_finish: top-k into idx,
-// fallback rows, landmark-value merge into v_lm when given) together with the
-// routing (launch_route), in two combined launches; with logits_done the
-// routing logits (expert, counts) were formed by launch_pivots_logits and the
-// first launch runs the selection's finish rows alone.
-hipError_t launch_select_route(const mita_cfg_t &c, const void *q, const void *q_lm, const void *k,
-                               const SelectBufs &sel, float *S, int32_t *idx, const void *partial, void *v_lm,
-                               int32_t *expert, int32_t *perm, int32_t *offsets, int32_t *tile_cnt, int32_t *tile_base,
-                               int32_t *counts, int32_t *tile_start, bool logits_done, hipStream_t st);
-
-// Whether launch_pivots_logits serves this configuration (bf16, sample in LDS).
-bool pivots_with_logits(const mita_cfg_t &c, const SelectBufs &sel);
 // The sampled scores and pivots (launch_select_pivots) and the routing
 // logits (expert [BH,N] and counts [BH,M], which must be zero on entry) in one
 // launch.
 hipError_t launch_pivots_logits(const mita_cfg_t &c, const void *q, const void *q_lm, const void *k,
                                 const SelectBufs &sel, int32_t *expert, int32_t *counts, hipStream_t st);
+
+// The finish of the fused selection (launch_select_finish: top-k into idx,
+// fallback rows, landmark-value merge into v_lm when given), its fallback rows
+// sharing a launch with the placement of the queries by expert (perm, offsets,
+// tile_start; cursor [BH,M] zero on entry), after launch_pivots_logits.
+hipError_t launch_select_place(const mita_cfg_t &c, const void *q_lm, const void *k, const SelectBufs &sel, float *S,
+                               int32_t *idx, const void *partial, void *v_lm, const int32_t *expert,
+                               const int32_t *counts, int32_t *cursor, int32_t *perm, int32_t *offsets,
+                               int32_t *tile_start, hipStream_t st);
+
+// Direct selection (N <= SEL_NS): the top-k sets, the landmark values (v_lm,
+// when given; partials in `partial`) and the routing (perm, offsets,
+// tile_start), which depend on the landmarks only, in one launch.
+hipError_t launch_direct(const mita_cfg_t &c, const void *q, const void *q_lm, const void *k, const void *v,
+                         const SelectBufs &sel, void *partial, void *v_lm, int32_t *perm, int32_t *offsets,
+                         int32_t *tile_start, hipStream_t st);
 
 // Attention work list from offsets: tile_start [BH, M+1].
 hipError_t launch_worklist(const mita_cfg_t &c, const int32_t *offsets, int32_t *tile_start, hipStream_t st);

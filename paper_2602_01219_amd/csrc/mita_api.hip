@@ -129,28 +129,42 @@ int enqueue_experts(const mita_cfg_t *c, const void *q, const void *k, const voi
   }
   const bool direct = fused && sel.idx;
 
-  // with the fused selection and in-place gather, the selection's finish
-  // shares launches with the routing (the "route" stage then includes it),
-  // whose placement cursors (in the tile_base buffer) start at zero
-  // s > 1 routes through its own launches (stable grouping of the pairs)
+  // s > 1 routes through its own launches (stable grouping of the pairs);
+  // otherwise, with the fused selection and in-place gather, routing and
+  // selection share launches, the grouping is not stable and its placement
+  // cursors (in the tile_base buffer) start at zero
   const bool multi = multi_route(*c);
-  const bool sel_in_route = fused && c->use_routed && !staged && !multi;
+  const bool combined = fused && !staged && !multi;
   int32_t *group = multi ? (int32_t *)(w + L.group) : nullptr;
+  const int64_t rows = BH(*c) * c->M;
+  int32_t *zero_counts = c->use_routed && !multi && !(combined && direct) ? counts : nullptr;
+  int32_t *zero_cursor = combined && !direct ? tile_base : nullptr;
   rec.stage = 0;
-  int32_t *zero_counts = c->use_routed && !multi ? counts : nullptr;
-  int32_t *zero_cursor = sel_in_route ? tile_base : nullptr;
   if (q_lm_in) {
-    TRY(hip_status(launch_zero2(zero_counts, zero_counts ? BH(*c) * c->M : 0, zero_cursor,
-                                zero_cursor ? BH(*c) * c->M : 0, st),
+    TRY(hip_status(launch_zero2(zero_counts, zero_counts ? rows : 0, zero_cursor, zero_cursor ? rows : 0, st),
                    "landmarks"));
   } else {
     TRY(hip_status(launch_pool(*c, q, q_lm_ws, zero_counts, zero_cursor, st), "landmarks"));
   }
+  if (combined && direct) {
+    rec.stage = 4;
+    return hip_status(launch_direct(*c, q, q_lm, k, v, sel, w + L.partial, v_lm, perm, offsets, tile_start, st),
+                      "select and route");
+  }
+  auto route = [&]() -> int {
+    rec.stage = 4;
+    return hip_status(
+        launch_route(*c, q, q_lm, expert, perm, offsets, tile_cnt, tile_base, counts, tile_start, group, st), "route");
+  };
+  // where the experts' sizes are known before the scores, the sets of experts
+  // without queries are not formed (the staged gather reads every set)
+  if (fused && multi) TRY(route());
+  if (combined || (fused && multi && !staged)) {
+    sel.live = counts;
+    sel.live_groups = route_groups(*c);
+  }
   rec.stage = 1;
-  // bf16: the routing logits are formed beside the sampled scores (they
-  // depend on the landmarks only), in the same launch
-  const bool logits_early = sel_in_route && !direct && pivots_with_logits(*c, sel);
-  if (logits_early)
+  if (combined)
     TRY(hip_status(launch_pivots_logits(*c, q, q_lm, k, sel, expert, counts, st), "select pivots"));
   else if (fused)
     TRY(hip_status(launch_select_pivots(*c, q_lm, k, sel, st), "select pivots"));
@@ -159,21 +173,17 @@ int enqueue_experts(const mita_cfg_t *c, const void *q, const void *k, const voi
                                fused && !direct ? &sel : nullptr, st),
                  "scores"));
   rec.stage = 2;
-  if (fused && !sel_in_route)
+  if (combined)
+    TRY(hip_status(launch_select_place(*c, q_lm, k, sel, S, idx, w + L.partial, v_lm, expert, counts, tile_base, perm,
+                                       offsets, tile_start, st),
+                   "topk"));
+  else if (fused)
     TRY(hip_status(launch_select_finish(*c, q_lm, k, sel, S, idx, w + L.partial, v_lm, st), "topk"));
-  else if (!fused && c->use_routed)
+  else if (c->use_routed)
     TRY(hip_status(launch_topk(*c, S, idx, st), "topk"));
   rec.stage = 3;
   if (staged) TRY(hip_status(launch_gather(*c, k, v, idx, w + L.kx, w + L.vx, st), "gather"));
-  rec.stage = 4;
-  if (sel_in_route)
-    TRY(hip_status(launch_select_route(*c, q, q_lm, k, sel, S, idx, w + L.partial, v_lm, expert, perm, offsets,
-                                       tile_cnt, tile_base, counts, tile_start, logits_early, st),
-                   "route"));
-  else if (c->use_routed)
-    TRY(hip_status(
-        launch_route(*c, q, q_lm, expert, perm, offsets, tile_cnt, tile_base, counts, tile_start, group, st),
-        "route"));
+  if (c->use_routed && !combined && !(fused && multi)) TRY(route());
   return MITA_OK;
 }
 

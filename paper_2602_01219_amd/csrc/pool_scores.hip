@@ -313,7 +313,7 @@ static hipError_t scores_t(const mita_cfg_t &c, const void *q_lm, const void *k,
   float2 *ml = (float2 *)partial;
   float *po = v_lm ? (float *)((char *)partial + align_up((size_t)BH(c) * nch * c.M * sizeof(float2))) : nullptr;
   const float sc = eff_scale(c);
-  const SelectArgs sel = sb ? SelectArgs{sb->plo, sb->ccnt, sb->cand} : SelectArgs{nullptr, nullptr, nullptr};
+  const SelectArgs sel = sb ? SelectArgs{sb->plo, sb->ccnt, sb->cand, {sb->live, sb->live_groups}} : SelectArgs{};
   const T *ql = (const T *)q_lm, *kk = (const T *)k, *vv = (const T *)v;
   // bf16, d = 128, with landmark values: every such pass (selection, stored
   // scores or values alone) runs score16_chunk, so their landmark values

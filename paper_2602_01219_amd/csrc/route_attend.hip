@@ -34,9 +34,86 @@ template <typename T, int D> struct RouteLds {
   static constexpr int BYTES = ROUTE_LB * LSTR * (int)sizeof(T);
 };
 
-// Workgroup (bx, by) of the routing grid (NWV waves, one 64-query tile
-// each); lms: RouteLds<T, D>::BYTES of LDS, cnt: NWV M words of LDS.
-template <typename T, int D, bool TILES = true, int NWV = 4>
+// A wave's 64-query tile: its query fragments (zero past N).
+template <typename T, int D>
+__device__ __forceinline__ void route_load(Frag<T> (&qf)[4][D / 32], const T *__restrict__ q, int64_t bh, int tile, int N) {
+  const int lane = threadIdx.x & 63, g = lane >> 4, p = lane & 15;
+#pragma unroll
+  for (int c = 0; c < 4; ++c) {
+    const int n = tile * ROUTE_TQ + c * 16 + p;
+#pragma unroll
+    for (int ks = 0; ks < D / 32; ++ks) {
+      if (n < N)
+        qf[c][ks].load(q + (bh * N + n) * D + ks * 32 + g * 8);
+      else
+        qf[c][ks].zero();
+    }
+  }
+}
+
+// Landmarks [l0, l0 + nl) into LDS, by a 256-thread workgroup.
+template <typename T, int D>
+__device__ __forceinline__ void route_stage(T *lms, const T *__restrict__ lmb, int l0, int nl) {
+  constexpr int VE = RouteLds<T, D>::VE, LSTR = RouteLds<T, D>::LSTR;
+  for (int ch = threadIdx.x; ch < ROUTE_LB * (D / VE); ch += BLOCK) {
+    const int r = ch / (D / VE), cc = ch % (D / VE);
+    uint4 x = make_uint4(0, 0, 0, 0);
+    if (r < nl) x = *reinterpret_cast<const uint4 *>(lmb + (int64_t)(l0 + r) * D + cc * VE);
+    *reinterpret_cast<uint4 *>(lms + r * LSTR + cc * VE) = x;
+  }
+}
+
+// The staged landmarks' logits against a tile's queries: running (max, argmax)
+// per column group.
+template <typename T, int D>
+__device__ __forceinline__ void route_argmax(float (&best)[4], int (&arg)[4], const T *lms, const Frag<T> (&qf)[4][D / 32],
+                                             int l0, int nl, int M, float scale) {
+  constexpr int LSTR = RouteLds<T, D>::LSTR;
+  const int lane = threadIdx.x & 63, g = lane >> 4, p = lane & 15;
+  for (int sb = 0; sb < nl; sb += 16) {
+    f32x4 acc[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) acc[c] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ks = 0; ks < D / 32; ++ks) {
+      Frag<T> a;
+      a.load(lms + (sb + p) * LSTR + ks * 32 + g * 8);
+#pragma unroll
+      for (int c = 0; c < 4; ++c) acc[c] = mma(a, qf[c][ks], acc[c]);
+    }
+    // running argmax, branch-free (selects); the first maximum is kept, and
+    // landmarks are visited in increasing order, so ties go to the lower one
+    const bool full = sb + 16 <= nl;
+#pragma unroll
+    for (int c = 0; c < 4; ++c)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int lmi = l0 + sb + 4 * g + r;
+        const float val = acc[c][r] * scale;
+        const bool up = (full || lmi < M) && val > best[c];
+        best[c] = up ? val : best[c];
+        arg[c] = up ? lmi : arg[c];
+      }
+  }
+}
+
+// The argmax over the four lane groups of a query column (lower landmark wins ties).
+__device__ __forceinline__ int route_merge(float best, int arg) {
+#pragma unroll
+  for (int o = 16; o <= 32; o <<= 1) {
+    const float ob = __shfl_xor(best, o);
+    const int oa = __shfl_xor(arg, o);
+    if (ob > best || (ob == best && oa < arg)) {
+      best = ob;
+      arg = oa;
+    }
+  }
+  return arg;
+}
+
+// Workgroup (bx, by) of the routing grid (4 waves, one 64-query tile
+// each); lms: RouteLds<T, D>::BYTES of LDS, cnt: 4 M words of LDS.
+template <typename T, int D, bool TILES = true>
 __device__ __forceinline__ void route_logits_body(T *lms, uint32_t *cnt, int bx, int by, const T *__restrict__ q,
                                                   const T *__restrict__ q_lm, int32_t *__restrict__ expert,
                                                   int32_t *__restrict__ tile_cnt, int32_t *__restrict__ counts, int N,
@@ -45,7 +122,7 @@ __device__ __forceinline__ void route_logits_body(T *lms, uint32_t *cnt, int bx,
   constexpr int LSTR = RouteLds<T, D>::LSTR;
   const int64_t bh = by;
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 4, p = lane & 15;
-  const int tile = bx * NWV + w;
+  const int tile = bx * 4 + w;
   uint32_t *wc = cnt + w * M;
   for (int i = lane; i < M; i += 64) wc[i] = 0u;
   Frag<T> qf[4][D / 32];
@@ -71,7 +148,7 @@ __device__ __forceinline__ void route_logits_body(T *lms, uint32_t *cnt, int bx,
   for (int l0 = 0; l0 < M; l0 += ROUTE_LB) {
     const int nl = min(ROUTE_LB, M - l0);
     __syncthreads();
-    for (int ch = threadIdx.x; ch < ROUTE_LB * (D / VE); ch += 64 * NWV) {
+    for (int ch = threadIdx.x; ch < ROUTE_LB * (D / VE); ch += BLOCK) {
       const int r = ch / (D / VE), cc = ch % (D / VE);
       uint4 x = make_uint4(0, 0, 0, 0);
       if (r < nl) x = *reinterpret_cast<const uint4 *>(lmb + (int64_t)(l0 + r) * D + cc * VE);
@@ -566,97 +643,178 @@ __global__ __launch_bounds__(256) void route_scatter_kernel(const int32_t *__res
 }
 
 // ---------------------------------------------------------------------------
-// The finish of the fused selection and the routing, which do not depend on
-// each other, share launches, so that the latency-bound selection work and
-// the routing work fill one another's idle time and the fallback steps (which
-// normally have nothing to do) cost no launch of their own:
-//   finalize_logits_kernel: selection finalize rows | routing logits;
-//   topk_scatter_kernel:    fallback rows (scored in full, then their top-k)
-//                           | routing placement and scatter.
-// Here the queries of an expert are grouped without a stable order (see
-// route_scatter_place_body); mita_route keeps the stable grouping.
-// The routing part's 2-D grid is flattened (x fastest). LDS is one buffer
-// that either part lays out for itself.
+// The sampled scores and pivots and the routing logits depend on the landmarks
+// only and share one launch, so that the latency-bound pivots and the logits
+// fill one another's idle time. The logits come this early because the sizes
+// of the experts then spare the score pass the candidate stores, and the finish
+// the selection, of experts without queries. Workgroups [0, nSp) take the nS
+// sample slots (spread over the XCDs by xcd_slot so that a head's blocks share
+// an L2; slots past nS exit), the rest the routing grid; LDS is one buffer that
+// either part lays out for itself.
 // ---------------------------------------------------------------------------
-// WAVE: finish rows by finalize_row_wave, four per workgroup.
-template <typename T, int D, int CAP, bool MERGE, bool WAVE> struct FinalizeLogitsLds {
-  static constexpr int F = WAVE ? 4 * (int)sizeof(FinalizeWaveLds) : (int)sizeof(FinalizeLds<T, D, CAP, MERGE>);
-  static constexpr int BYTES = F > RouteLds<T, D>::BYTES ? F : RouteLds<T, D>::BYTES;
-};
-
-// Finalize rows and routing workgroups interleave one to one while both last,
-// so the two kinds run side by side.
-template <typename T, int D, int CAP, bool MERGE, bool WAVE>
-__global__ __launch_bounds__(BLOCK) void finalize_logits_kernel(
-    const uint2 *__restrict__ cand, const uint32_t *__restrict__ ccnt, int32_t *__restrict__ idx,
-    uint32_t *__restrict__ fail_cnt, int32_t *__restrict__ fail_list, int k, int cap, int nch,
-    const float2 *__restrict__ part_ml, const float *__restrict__ part_o, T *__restrict__ v_lm, int nF,
-    const T *__restrict__ q, const T *__restrict__ q_lm, int32_t *__restrict__ expert, int32_t *__restrict__ tile_cnt,
-    int32_t *__restrict__ counts, int N, int M, float scale, int ntiles, int route_x, int nR, int64_t nrows) {
-  __shared__ __align__(16) char buf[FinalizeLogitsLds<T, D, CAP, MERGE, WAVE>::BYTES];
-  extern __shared__ uint32_t cnt[];  // routing: [4][M]
-  const int b = (int)blockIdx.x, lo = min(nF, nR);
-  bool fin;
-  int i;
-  if (b < 2 * lo) {
-    fin = (b & 1) == 0;
-    i = b >> 1;
-  } else {
-    fin = nF > nR;
-    i = b - lo;
-  }
-  if (fin) {
-    if constexpr (WAVE) {
-      const int w = (int)threadIdx.x >> 6;
-      const int64_t row = (int64_t)i * 4 + w;
-      if (row < nrows)  // the whole wave
-        finalize_row_wave<T, D, MERGE>(reinterpret_cast<FinalizeWaveLds *>(buf)[w], row, cand, ccnt, idx, fail_cnt,
-                                       fail_list, k, cap, nch, part_ml, part_o, v_lm, M, scale);
-    } else {
-      finalize_row<T, D, CAP, MERGE>(*reinterpret_cast<FinalizeLds<T, D, CAP, MERGE> *>(buf), i, cand, ccnt, idx,
-                                     fail_cnt, fail_list, k, cap, nch, part_ml, part_o, v_lm, M, scale);
-    }
-    return;
-  }
-  route_logits_body<T, D, false>(reinterpret_cast<T *>(buf), cnt, i % route_x, i / route_x, q, q_lm, expert, tile_cnt, counts,
-                          N, M, scale, ntiles);
-}
-
-// ---------------------------------------------------------------------------
-// bf16: the sampled scores and pivots and the routing logits (independent of
-// each other) share one launch of 16-wave workgroups: the few sample
-// workgroups are latency-bound and leave CUs idle, which the routing
-// workgroups (sixteen 64-query tiles each) fill. Workgroups [0, nSp) take
-// the nS sample slots (x fastest, spread over the XCDs by xcd_slot so that a
-// head's blocks share an L2; slots past nS exit), the rest the routing grid;
-// LDS is one buffer that either part lays out for itself.
-// ---------------------------------------------------------------------------
-template <typename T, int D> struct SampleLogitsLds {
-  static constexpr int A = 16 * SP_PITCH * (int)sizeof(uint32_t);
-  static constexpr int BYTES = A > RouteLds<T, D>::BYTES ? A : RouteLds<T, D>::BYTES;
-};
-
 template <typename T, int D>
-__global__ __launch_bounds__(1024) void sample_logits_kernel(const T *__restrict__ q_lm, const T *__restrict__ k,
-                                                             uint32_t *__restrict__ plo,
-                                                             uint32_t *__restrict__ fail_cnt, int ns, int r,
-                                                             int sample_x, int nS, int nSp, const T *__restrict__ q,
-                                                             int32_t *__restrict__ expert,
-                                                             int32_t *__restrict__ counts, int N, int M, float scale,
-                                                             int ntiles, int route_x) {
-  __shared__ __align__(16) char buf[SampleLogitsLds<T, D>::BYTES];
-  extern __shared__ uint32_t cnt[];  // routing: [16][M]
+__global__ __launch_bounds__(BLOCK) void pivots_logits_kernel(const T *__restrict__ q_lm, const T *__restrict__ k,
+                                                              uint32_t *__restrict__ plo,
+                                                              uint32_t *__restrict__ fail_cnt, int ns, int r,
+                                                              int sample_x, int nS, int nSp, const T *__restrict__ q,
+                                                              int32_t *__restrict__ expert,
+                                                              int32_t *__restrict__ counts, int N, int M, float scale,
+                                                              int ntiles, int route_x) {
+  constexpr int BYTES = SP_BYTES > RouteLds<T, D>::BYTES ? SP_BYTES : RouteLds<T, D>::BYTES;
+  __shared__ __align__(16) char buf[BYTES];
+  extern __shared__ uint32_t cnt[];  // routing: [4][M]
   const int b = (int)blockIdx.x;
   if (b < nSp) {  // nSp = nS rounded up to whole XCD ranges (xcd_slot)
     const int f = xcd_slot(b, nSp / NXCD);
     if (f >= nS) return;
-    sample_pivot_body<T, D, 16>(reinterpret_cast<uint32_t(*)[SP_PITCH]>(buf), f % sample_x, f / sample_x, q_lm, k,
-                                plo, fail_cnt, N, M, ns, r, scale);
+    sample_pivot_body<T, D>(reinterpret_cast<uint32_t(*)[SP_PITCH]>(buf), f % sample_x, f / sample_x, q_lm, k, plo,
+                            fail_cnt, N, M, ns, r, scale);
     return;
   }
   const int i = b - nSp;
-  route_logits_body<T, D, false, 16>(reinterpret_cast<T *>(buf), cnt, i % route_x, i / route_x, q, q_lm, expert,
-                                     nullptr, counts, N, M, scale, ntiles);
+  route_logits_body<T, D, false>(reinterpret_cast<T *>(buf), cnt, i % route_x, i / route_x, q, q_lm, expert, nullptr,
+                                 counts, N, M, scale, ntiles);
+}
+
+// ---------------------------------------------------------------------------
+// Direct selection (N <= SEL_NS tokens): everything between the landmarks and
+// the attention in one launch, by three kinds of workgroups that depend on the
+// landmarks only: the top-k sets (four rows each: sampled scores = all scores,
+// pivot, set), the landmark values (64 landmarks each: the score pass over the
+// head's one or two key chunks, then their merge), and the routing of one head
+// (logits, sizes, offsets and placement in LDS, the queries of an expert in
+// any order). These shapes are a chain of short launches otherwise: at 384
+// heads of 196 tokens, M = 16, k = 49, the five launches took about 35 us.
+// ---------------------------------------------------------------------------
+template <typename T, int D> struct DirectLds {
+  static constexpr bool S16 = sizeof(T) == 2 && D == 128;  // landmark values by score16_chunk
+  static constexpr int V = S16 ? 4 * DmaTile<D, TK32, 4>::BYTES
+                               : 2 * (TileDims<T, D>::K_ELEMS + TileDims<T, D>::V_ELEMS) * (int)sizeof(T);
+  static constexpr int A = SP_BYTES > RouteLds<T, D>::BYTES ? SP_BYTES : RouteLds<T, D>::BYTES;
+  template <bool VALUES> static constexpr int bytes() { return VALUES && V > A ? V : A; }
+};
+struct DirectRoute {
+  uint32_t cnt[SEL_NS];  // expert sizes, then each expert's next position (M <= N)
+  uint32_t wsum[4];
+  uint16_t ex[SEL_NS];   // the queries' experts
+};
+
+template <typename T, int D>
+__device__ __forceinline__ void route_head_body(T *lms, DirectRoute &sh, int64_t bh, const T *__restrict__ q,
+                                                const T *__restrict__ q_lm, int32_t *__restrict__ perm,
+                                                int32_t *__restrict__ offsets, int32_t *__restrict__ tile_start, int N,
+                                                int M, float scale) {
+  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, g = lane >> 4, p = lane & 15;
+  const int ntiles = (N + ROUTE_TQ - 1) / ROUTE_TQ;
+  for (int i = tid; i < M; i += BLOCK) sh.cnt[i] = 0u;
+  const T *lmb = q_lm + bh * (int64_t)M * D;
+  for (int t0 = 0; t0 < ntiles; t0 += 4) {
+    const int tile = t0 + w;
+    Frag<T> qf[4][D / 32];
+    route_load<T, D>(qf, q, bh, tile, N);
+    float best[4];
+    int arg[4];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      best[c] = -INFINITY;
+      arg[c] = 0;
+    }
+    for (int l0 = 0; l0 < M; l0 += ROUTE_LB) {
+      const int nl = min(ROUTE_LB, M - l0);
+      if (t0 == 0 || M > ROUTE_LB) {  // (one block of landmarks stays staged)
+        __syncthreads();
+        route_stage<T, D>(lms, lmb, l0, nl);
+        __syncthreads();
+      }
+      if (tile < ntiles) route_argmax<T, D>(best, arg, lms, qf, l0, nl, M, scale);
+    }
+#pragma unroll
+    for (int c = 0; c < 4; ++c) {
+      const int e = route_merge(best[c], arg[c]), n = tile * ROUTE_TQ + c * 16 + p;
+      if (g == 0 && n < N) {
+        sh.ex[n] = (uint16_t)e;
+        atomicAdd(&sh.cnt[e], 1u);
+      }
+    }
+  }
+  __syncthreads();
+  // sizes -> offsets and the attention work list, four experts per thread
+  uint32_t sz[4], a = 0, t = 0;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int x = 4 * tid + u;
+    sz[u] = x < M ? sh.cnt[x] : 0u;
+    a += sz[u];
+    t += (sz[u] + ATT_TQ - 1) / ATT_TQ;
+  }
+  uint32_t atot, ttot;
+  uint32_t off = block_exclusive_scan<256>(a, sh.wsum, &atot);
+  uint32_t ts = block_exclusive_scan<256>(t, sh.wsum, &ttot);
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int x = 4 * tid + u;
+    if (x < M) {
+      sh.cnt[x] = off;
+      offsets[bh * (M + 1) + x] = (int32_t)off;
+      tile_start[bh * (M + 1) + x] = (int32_t)ts;
+    }
+    off += sz[u];
+    ts += (sz[u] + ATT_TQ - 1) / ATT_TQ;
+  }
+  if (tid == 0) {
+    offsets[bh * (M + 1) + M] = (int32_t)atot;
+    tile_start[bh * (M + 1) + M] = (int32_t)ttot;
+  }
+  __syncthreads();
+  for (int n = tid; n < N; n += BLOCK) perm[bh * N + atomicAdd(&sh.cnt[sh.ex[n]], 1u)] = n;
+}
+
+// Workgroups [0, nSp): sample slots as above; [nSp, nSp + nV): landmark values;
+// the rest: one head's routing each.
+template <typename T, int D, bool VALUES>
+__global__ __launch_bounds__(BLOCK) void direct_kernel(const T *__restrict__ q, const T *__restrict__ q_lm,
+                                                       const T *__restrict__ k, const T *__restrict__ v,
+                                                       uint32_t *__restrict__ plo, uint32_t *__restrict__ fail_cnt,
+                                                       int32_t *__restrict__ idx, float2 *__restrict__ part_ml,
+                                                       float *__restrict__ part_o, T *__restrict__ v_lm,
+                                                       int32_t *__restrict__ perm, int32_t *__restrict__ offsets,
+                                                       int32_t *__restrict__ tile_start, int N, int M, int kk,
+                                                       float scale, int sample_x, int nS, int nSp, int nV, int nch) {
+  using DL = DirectLds<T, D>;
+  __shared__ __align__(16) char buf[DL::template bytes<VALUES>()];
+  __shared__ DirectRoute route;
+  const int b = (int)blockIdx.x;
+  if (b < nSp) {
+    const int f = xcd_slot(b, nSp / NXCD);
+    if (f >= nS) return;
+    sample_pivot_body<T, D>(reinterpret_cast<uint32_t(*)[SP_PITCH]>(buf), f % sample_x, f / sample_x, q_lm, k, plo,
+                            fail_cnt, N, M, N, kk, scale, idx, kk);
+    return;
+  }
+  if (VALUES && b < nSp + nV) {
+    const int lmblocks = (M + 63) / 64, lb = (b - nSp) % lmblocks;
+    const int64_t bh = (b - nSp) / lmblocks;
+    const SelectArgs none{};
+    for (int ch = 0; ch < nch; ++ch) {
+      if constexpr (DL::S16) {
+        score16_chunk<D, 1, 4, false, false>(buf, buf + DL::V / 2, q_lm, k, v, nullptr, part_ml, part_o, none, N, M,
+                                             scale, ch, nch, lb, bh);
+      } else {
+        T *Ks = reinterpret_cast<T *>(buf), *Vt = Ks + 2 * TileDims<T, D>::K_ELEMS;
+        score_chunk<T, D, false, true, false>(Ks, Vt, q_lm, k, v, nullptr, part_ml, part_o, none, N, M, scale, ch, nch,
+                                              lb, bh, -1);
+      }
+      __syncthreads();  // the tiles are free; the partials visible to the workgroup (one L1)
+    }
+    for (int i = threadIdx.x; i < 64 * D; i += BLOCK) {
+      const int lm = 64 * lb + i / D, dim = i % D;
+      if (lm < M)
+        v_lm[(bh * M + lm) * D + dim] = from_f32<T>(merge_landmark_value_1<D>(part_ml, part_o, bh, lm, M, nch, dim));
+    }
+    return;
+  }
+  route_head_body<T, D>(reinterpret_cast<T *>(buf), route, b - nSp - (VALUES ? nV : 0), q, q_lm, perm, offsets,
+                        tile_start, N, M, scale);
 }
 
 // Workgroups [0, nT) take the fallback rows: each scores its rows in full
@@ -685,7 +843,7 @@ __global__ __launch_bounds__(256) void topk_scatter_kernel(const T *__restrict__
   const int b = (int)blockIdx.x;
   if (b < nT) {
     const uint32_t nr = *nrows;
-    const SelectArgs none{nullptr, nullptr, nullptr};
+    const SelectArgs none{};
     for (uint32_t f = (uint32_t)b; f < nr; f += (uint32_t)nT) {
       const int row = rows[f];
       const int lm = row % M;
@@ -1396,36 +1554,38 @@ hipError_t launch_route(const mita_cfg_t &c, const void *q, const void *q_lm, in
                    : route_t<bf16_t, 128>(c, q, q_lm, expert, perm, offsets, tile_cnt, tile_base, counts, tile_start, st);
 }
 
-template <typename T, int D, int CAP, bool MERGE, bool WAVE>
-static hipError_t select_route_t(const mita_cfg_t &c, const void *q, const void *q_lm, const void *k,
-                                 const SelectBufs &sb, float *S, int32_t *idx, const void *partial, void *v_lm,
-                                 int32_t *expert, int32_t *perm, int32_t *offsets, int32_t *tile_cnt,
-                                 int32_t *tile_base, int32_t *counts, int32_t *tile_start, bool logits_done,
-                                 hipStream_t st) {
-  const int nt = route_tiles(c);
+template <typename T, int D>
+static hipError_t pivots_logits_t(const mita_cfg_t &c, const void *q, const void *q_lm, const void *k,
+                                  const SelectBufs &sb, int32_t *expert, int32_t *counts, hipStream_t st) {
   const int bh = (int)BH(c);
-  const int nch = score_chunks(c);
+  const int sample_x = (c.M + SP_ROWS - 1) / SP_ROWS, nS = sample_x * bh, nSp = NXCD * ((nS + NXCD - 1) / NXCD);
+  const int nt = route_tiles(c), route_x = (nt + 3) / 4;
+  hipLaunchKernelGGL((pivots_logits_kernel<T, D>), dim3((unsigned)(nSp + route_x * bh)), dim3(BLOCK),
+                     4 * (size_t)c.M * sizeof(uint32_t), st, (const T *)q_lm, (const T *)k, sb.plo, sb.fail_cnt, sb.ns,
+                     sb.rank, sample_x, nS, nSp, (const T *)q, expert, counts, c.N, c.M, eff_scale(c), nt, route_x);
+  return launched("pivots_logits_kernel", st);
+}
+
+hipError_t launch_pivots_logits(const mita_cfg_t &c, const void *q, const void *q_lm, const void *k,
+                                const SelectBufs &sb, int32_t *expert, int32_t *counts, hipStream_t st) {
+  if (sb.ns > SEL_NS || sb.idx) return hipErrorInvalidValue;
+  if (c.dtype == MITA_F32)
+    return c.d == 64 ? pivots_logits_t<float, 64>(c, q, q_lm, k, sb, expert, counts, st)
+                     : pivots_logits_t<float, 128>(c, q, q_lm, k, sb, expert, counts, st);
+  return c.d == 64 ? pivots_logits_t<bf16_t, 64>(c, q, q_lm, k, sb, expert, counts, st)
+                   : pivots_logits_t<bf16_t, 128>(c, q, q_lm, k, sb, expert, counts, st);
+}
+
+template <typename T, int D>
+static hipError_t place_t(const mita_cfg_t &c, const void *q_lm, const void *k, const SelectBufs &sb, float *S,
+                          int32_t *idx, const int32_t *expert, const int32_t *counts, int32_t *cursor, int32_t *perm,
+                          int32_t *offsets, int32_t *tile_start, hipStream_t st) {
+  const int nt = route_tiles(c), bh = (int)BH(c), nch = score_chunks(c);
   const int64_t rows = (int64_t)bh * c.M;
-  const float2 *ml = (const float2 *)partial;
-  const float *po = MERGE ? (const float *)((const char *)partial + align_up((size_t)rows * nch * sizeof(float2)))
-                          : nullptr;
-  // with the logits formed beside the sampled scores, the finish rows run
-  // alone; with the sets written by the pivot launch (direct selection) the
-  // routing logits do
-  const int route_x = (nt + 3) / 4;
-  const int nF = sb.idx ? 0 : (int)(WAVE ? (rows + 3) / 4 : rows), nR = logits_done ? 0 : route_x * bh;
-  if (nF + nR == 0) return hipErrorInvalidValue;
-  hipLaunchKernelGGL((finalize_logits_kernel<T, D, CAP, MERGE, WAVE>), dim3((unsigned)(nF + nR)), dim3(BLOCK),
-                     nR ? 4 * c.M * sizeof(uint32_t) : 0, st, sb.cand, sb.ccnt, idx, sb.fail_cnt, sb.fail_list, c.k, sb.cap,
-                     nch, ml, po, (T *)v_lm, nF, (const T *)q, (const T *)q_lm, expert, tile_cnt, counts, c.N, c.M,
-                     eff_scale(c), nt, route_x, nR, rows);
-  hipError_t err = launched("finalize_logits_kernel", st);
-  if (err != hipSuccess) return err;
-  // the fallback workgroups of the last launch (listed rows, scored in full and selected)
+  // the fallback workgroups (listed rows, scored in full and selected)
   // (few: the rows normally all pass and these workgroups exit at once; each
   // takes rows b, b + nT, ... when some do not)
   const int nT = (int)(rows < 64 ? rows : 64);
-  int32_t *cursor = tile_base;  // the placement cursors live in the (here unused) tile_base buffer
   const int scat_x = (nt + 4 * SCATTER_TPW - 1) / (4 * SCATTER_TPW);
   const int nS = scat_x * bh;
   int ebits = 0;
@@ -1442,74 +1602,48 @@ static hipError_t select_route_t(const mita_cfg_t &c, const void *q, const void 
   return launched("topk_scatter_kernel", st);
 }
 
-template <typename T, int D>
-static hipError_t select_route_n(const mita_cfg_t &c, const void *q, const void *q_lm, const void *k,
-                                 const SelectBufs &sb, float *S, int32_t *idx, const void *partial, void *v_lm,
-                                 int32_t *expert, int32_t *perm, int32_t *offsets, int32_t *tile_cnt,
-                                 int32_t *tile_base, int32_t *counts, int32_t *tile_start, bool logits_done,
-                                 hipStream_t st) {
-#define MITA_SR(CAP, MG, W)                                                                                      \
-  return select_route_t<T, D, CAP, MG, W>(c, q, q_lm, k, sb, S, idx, partial, v_lm, expert, perm, offsets, tile_cnt, \
-                                          tile_base, counts, tile_start, logits_done, st)
-  // lists of at most SEL_NS entries over at most 64 chunks: one wave per row
-  const bool wave = sb.cap <= SEL_NS && score_chunks(c) <= 64;
-  if (v_lm) {
-    if (wave) MITA_SR(SEL_NS, true, true);
-    if (sb.cap <= 1024) MITA_SR(1024, true, false);
-    if (sb.cap <= 2048) MITA_SR(2048, true, false);
-    if (sb.cap <= 4096) MITA_SR(4096, true, false);
-    MITA_SR(SEL_CAP, true, false);
-  }
-  if (wave) MITA_SR(SEL_NS, false, true);
-  if (sb.cap <= 1024) MITA_SR(1024, false, false);
-  if (sb.cap <= 2048) MITA_SR(2048, false, false);
-  if (sb.cap <= 4096) MITA_SR(4096, false, false);
-  MITA_SR(SEL_CAP, false, false);
-#undef MITA_SR
-}
-
-hipError_t launch_select_route(const mita_cfg_t &c, const void *q, const void *q_lm, const void *k,
-                               const SelectBufs &sb, float *S, int32_t *idx, const void *partial, void *v_lm,
-                               int32_t *expert, int32_t *perm, int32_t *offsets, int32_t *tile_cnt, int32_t *tile_base,
-                               int32_t *counts, int32_t *tile_start, bool logits_done, hipStream_t st) {
+hipError_t launch_select_place(const mita_cfg_t &c, const void *q_lm, const void *k, const SelectBufs &sb, float *S,
+                               int32_t *idx, const void *partial, void *v_lm, const int32_t *expert,
+                               const int32_t *counts, int32_t *cursor, int32_t *perm, int32_t *offsets,
+                               int32_t *tile_start, hipStream_t st) {
+  const hipError_t e = launch_select_finalize(c, sb, idx, partial, v_lm, st);
+  if (e != hipSuccess) return e;
   if (c.dtype == MITA_F32)
-    return c.d == 64 ? select_route_n<float, 64>(c, q, q_lm, k, sb, S, idx, partial, v_lm, expert, perm, offsets,
-                                                 tile_cnt, tile_base, counts, tile_start, logits_done, st)
-                     : select_route_n<float, 128>(c, q, q_lm, k, sb, S, idx, partial, v_lm, expert, perm, offsets,
-                                                  tile_cnt, tile_base, counts, tile_start, logits_done, st);
-  return c.d == 64 ? select_route_n<bf16_t, 64>(c, q, q_lm, k, sb, S, idx, partial, v_lm, expert, perm, offsets,
-                                                tile_cnt, tile_base, counts, tile_start, logits_done, st)
-                   : select_route_n<bf16_t, 128>(c, q, q_lm, k, sb, S, idx, partial, v_lm, expert, perm, offsets,
-                                                 tile_cnt, tile_base, counts, tile_start, logits_done, st);
+    return c.d == 64
+               ? place_t<float, 64>(c, q_lm, k, sb, S, idx, expert, counts, cursor, perm, offsets, tile_start, st)
+               : place_t<float, 128>(c, q_lm, k, sb, S, idx, expert, counts, cursor, perm, offsets, tile_start, st);
+  return c.d == 64 ? place_t<bf16_t, 64>(c, q_lm, k, sb, S, idx, expert, counts, cursor, perm, offsets, tile_start, st)
+                   : place_t<bf16_t, 128>(c, q_lm, k, sb, S, idx, expert, counts, cursor, perm, offsets, tile_start, st);
 }
 
-// The routing logits go beside the sampled scores when the selection's
-// finish rows hold long lists (cap above 2048 entries: 32 KB and more of LDS
-// per row), which would leave the routing workgroups that share their launch
-// few slots per CU; with shorter lists the finish launch serves them better
-// (at 16K tokens, M = 128, k = 512: 63.9 us against 75.4 for the pivots and
-// the finish together).
-bool pivots_with_logits(const mita_cfg_t &c, const SelectBufs &sb) {
-  return c.dtype == MITA_BF16 && sb.ns <= SEL_NS && sb.cap > 2048;
-}
-
-hipError_t launch_pivots_logits(const mita_cfg_t &c, const void *q, const void *q_lm, const void *k,
-                                const SelectBufs &sb, int32_t *expert, int32_t *counts, hipStream_t st) {
-  if (!pivots_with_logits(c, sb)) return hipErrorInvalidValue;
-  const int bh = (int)BH(c);
-  const int sample_x = (c.M + 15) / 16, nS = sample_x * bh, nSp = NXCD * ((nS + NXCD - 1) / NXCD);
-  const int nt = route_tiles(c), route_x = (nt + 15) / 16, nR = route_x * bh;
-  const dim3 grid((unsigned)(nSp + nR));
-  const size_t dyn = 16 * (size_t)c.M * sizeof(uint32_t);
-  if (c.d == 64)
-    hipLaunchKernelGGL((sample_logits_kernel<bf16_t, 64>), grid, dim3(1024), dyn, st, (const bf16_t *)q_lm,
-                       (const bf16_t *)k, sb.plo, sb.fail_cnt, sb.ns, sb.rank, sample_x, nS, nSp, (const bf16_t *)q, expert,
-                       counts, c.N, c.M, eff_scale(c), nt, route_x);
+template <typename T, int D>
+static hipError_t direct_t(const mita_cfg_t &c, const void *q, const void *q_lm, const void *k, const void *v,
+                           const SelectBufs &sb, void *partial, void *v_lm, int32_t *perm, int32_t *offsets,
+                           int32_t *tile_start, hipStream_t st) {
+  const int bh = (int)BH(c), nch = score_chunks(c);
+  const int sample_x = (c.M + SP_ROWS - 1) / SP_ROWS, nS = sample_x * bh, nSp = NXCD * ((nS + NXCD - 1) / NXCD);
+  const int nV = v_lm ? (c.M + 63) / 64 * bh : 0;
+  const dim3 grid((unsigned)(nSp + nV + bh));
+  float2 *ml = (float2 *)partial;
+  float *po = v_lm ? (float *)((char *)partial + align_up((size_t)bh * nch * c.M * sizeof(float2))) : nullptr;
+#define MITA_DIRECT(V)                                                                                                hipLaunchKernelGGL((direct_kernel<T, D, V>), grid, dim3(BLOCK), 0, st, (const T *)q, (const T *)q_lm, (const T *)k,                      (const T *)v, sb.plo, sb.fail_cnt, sb.idx, ml, po, (T *)v_lm, perm, offsets, tile_start, c.N,                         c.M, c.k, eff_scale(c), sample_x, nS, nSp, nV, nch)
+  if (v_lm)
+    MITA_DIRECT(true);
   else
-    hipLaunchKernelGGL((sample_logits_kernel<bf16_t, 128>), grid, dim3(1024), dyn, st, (const bf16_t *)q_lm,
-                       (const bf16_t *)k, sb.plo, sb.fail_cnt, sb.ns, sb.rank, sample_x, nS, nSp, (const bf16_t *)q, expert,
-                       counts, c.N, c.M, eff_scale(c), nt, route_x);
-  return launched("sample_logits_kernel", st);
+    MITA_DIRECT(false);
+#undef MITA_DIRECT
+  return launched("scores_kernel", st);  // (the score pass of these shapes: the timer keeps its name)
+}
+
+hipError_t launch_direct(const mita_cfg_t &c, const void *q, const void *q_lm, const void *k, const void *v,
+                         const SelectBufs &sb, void *partial, void *v_lm, int32_t *perm, int32_t *offsets,
+                         int32_t *tile_start, hipStream_t st) {
+  if (!sb.idx || sb.ns != c.N || sb.rank != c.k || c.N > SEL_NS) return hipErrorInvalidValue;
+  if (c.dtype == MITA_F32)
+    return c.d == 64 ? direct_t<float, 64>(c, q, q_lm, k, v, sb, partial, v_lm, perm, offsets, tile_start, st)
+                     : direct_t<float, 128>(c, q, q_lm, k, v, sb, partial, v_lm, perm, offsets, tile_start, st);
+  return c.d == 64 ? direct_t<bf16_t, 64>(c, q, q_lm, k, v, sb, partial, v_lm, perm, offsets, tile_start, st)
+                   : direct_t<bf16_t, 128>(c, q, q_lm, k, v, sb, partial, v_lm, perm, offsets, tile_start, st);
 }
 
 hipError_t launch_worklist(const mita_cfg_t &c, const int32_t *offsets, int32_t *tile_start, hipStream_t st) {

@@ -138,50 +138,51 @@ __device__ __forceinline__ uint32_t pivot_of(const uint32_t (&v)[PIVOT_PER], uin
 }
 
 // ---------------------------------------------------------------------------
-// Sampled scores and pivots in one launch. Workgroup = NW waves over 16
-// landmark rows of one head (one MFMA column block); wave w scores them
-// against the sampled keys [SEL_NS/NW w, SEL_NS/NW (w + 1)) in tiles of 64,
-// the A fragments loaded straight from the sampled key rows (tile arithmetic
-// as in the score pass, so the same values), keys = score_key(fl(dot) * scale)
-// into LDS; then wave w takes the pivots of rows 16/NW w .. 16/NW (w + 1) - 1,
-// its histogram and compaction slots in the first 384 words of its own row's
-// keys once they are in registers (the wave's LDS accesses are in order). Workgroup (0, 0) also
+// Sampled scores and pivots. Workgroup = 4 waves for 4 landmark rows of one
+// head: wave w scores the MFMA column block of 16 landmarks that holds them
+// against every fourth 64-key tile of the samples (the A fragments loaded
+// straight from the sampled key rows, the next tile's in flight; tile
+// arithmetic as in the score pass, so the same values) and keeps the four
+// rows' keys = score_key(fl(dot) * scale) in LDS; then wave w takes the pivot
+// of row w, its histogram and compaction slots in the first 384 words of its
+// row's keys once they are in registers (the wave's LDS accesses are in order).
+// Four workgroups score each column block: the products are cheap, and with
+// one row per wave and 16 KB of LDS the pivots run beside the routing (a
+// workgroup of 16 waves for all 16 rows held 66 KB). Workgroup (0, 0) also
 // zeroes the fallback counter.
 // ---------------------------------------------------------------------------
+constexpr int SP_ROWS = 4;            // landmark rows per workgroup
 constexpr int SP_PITCH = SEL_NS + 4;  // keys per LDS row: rows start 4 banks apart
+constexpr int SP_BYTES = SP_ROWS * SP_PITCH * 4;
 
-// Workgroup (bx, by) of the sample grid (16 landmarks of head by); keys: 16
-// LDS rows of SP_PITCH words.
+// Workgroup (bx, by) of the sample grid (landmarks 4 bx .. of head by); keys:
+// SP_ROWS LDS rows of SP_PITCH words.
 // With idx (only when the sample is the whole row, ns == N, and r == kk)
 // the rows' top-kk sets are written too, in ascending token order: every key
 // above the pivot and, in token order, as many keys equal to it as the set
 // still needs (the order of the top-k: larger score first, lower index first
 // among equal scores).
-template <typename T, int D, int NW>
+template <typename T, int D>
 __device__ __forceinline__ void sample_pivot_body(uint32_t (*keys)[SP_PITCH], int bx, int by,
                                                   const T *__restrict__ q_lm, const T *__restrict__ k,
                                                   uint32_t *__restrict__ plo, uint32_t *__restrict__ fail_cnt, int N,
                                                   int M, int ns, int r, float scale, int32_t *__restrict__ idx = nullptr,
                                                   int kk = 0) {
-  static_assert(16 % NW == 0 && SEL_NS % (NW * TK) == 0, "sample/pivot split");
-  constexpr int PERW = SEL_NS / NW;  // samples per wave
-  constexpr int RPW = 16 / NW;       // rows per wave
   const int64_t bh = by;
-  const int lm0 = bx * 16;
+  const int lm0 = bx * SP_ROWS, lmb = lm0 & ~15;  // the rows; their column block
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 4, p = lane & 15;
   if (bx == 0 && by == 0 && threadIdx.x == 0) *fail_cnt = 0;
   Frag<T> qf[D / 32];
 #pragma unroll
   for (int ks = 0; ks < D / 32; ++ks) {
-    if (lm0 + p < M)
-      qf[ks].load(q_lm + (bh * M + lm0 + p) * D + ks * 32 + g * 8);
+    if (lmb + p < M)
+      qf[ks].load(q_lm + (bh * M + lmb + p) * D + ks * 32 + g * 8);
     else
       qf[ks].zero();
   }
   const T *kb_ = k + bh * (int64_t)N * D;
-  for (int j0 = w * PERW; j0 < min(ns, (w + 1) * PERW); j0 += TK) {
-    // the tile's A fragments, all loads issued before the first is used
-    Frag<T> a[4][D / 32];
+  // a tile's A fragments, all loads issued before the first is used
+  auto load = [&](Frag<T> (&a)[4][D / 32], int j0) {
 #pragma unroll
     for (int kb = 0; kb < 4; ++kb) {
       const int j = j0 + kb * 16 + p;  // A row p of block kb: sample j
@@ -189,59 +190,78 @@ __device__ __forceinline__ void sample_pivot_body(uint32_t (*keys)[SP_PITCH], in
 #pragma unroll
       for (int ks = 0; ks < D / 32; ++ks) a[kb][ks].load(kb_ + pos * D + ks * 32 + g * 8);
     }
+  };
+  const int row = p - (lm0 - lmb);  // this column's row of the four, if it is one
+  auto use = [&](const Frag<T> (&a)[4][D / 32], int j0) {
 #pragma unroll
     for (int kb = 0; kb < 4; ++kb) {
       f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
       for (int ks = 0; ks < D / 32; ++ks) acc = mma(a[kb][ks], qf[ks], acc);
-      // lane (g, p) holds samples j0 + 16 kb + 4 g + (0..3) of row p
+      // lane (g, p) holds samples j0 + 16 kb + 4 g + (0..3) of column p
       const int jb = j0 + kb * 16 + 4 * g;
-      uint32_t key[4];
+      if (row >= 0 && row < SP_ROWS) {
+        uint32_t key[4];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) key[q] = jb + q < ns ? score_key(acc[q] * scale) : 0u;
-      *reinterpret_cast<uint4 *>(&keys[p][jb]) = make_uint4(key[0], key[1], key[2], key[3]);
+        for (int q = 0; q < 4; ++q) key[q] = jb + q < ns ? score_key(acc[q] * scale) : 0u;
+        *reinterpret_cast<uint4 *>(&keys[row][jb]) = make_uint4(key[0], key[1], key[2], key[3]);
+      }
+    }
+  };
+  constexpr bool AHEAD = sizeof(T) == 2 && D == 64;  // (registers for two tiles' fragments)
+  Frag<T> a[AHEAD ? 2 : 1][4][D / 32];
+  const int j1 = min(ns, SEL_NS);
+  if (AHEAD) {
+    if (w * TK < j1) load(a[0], w * TK);
+#pragma unroll
+    for (int i = 0; i < SEL_NS / (4 * TK); ++i) {
+      const int j0 = (4 * i + w) * TK;
+      if (j0 + 4 * TK < j1) load(a[(i + 1) & 1], j0 + 4 * TK);
+      if (j0 < j1) use(a[i & 1], j0);
+    }
+  } else {
+    for (int j0 = w * TK; j0 < j1; j0 += 4 * TK) {
+      load(a[0], j0);
+      use(a[0], j0);
     }
   }
   // slots past ns stay 0 (below every key) for the selection
-  for (int j = ns + (int)threadIdx.x; j < SEL_NS; j += 64 * NW)
+  for (int j = ns + (int)threadIdx.x; j < SEL_NS; j += 256)
 #pragma unroll
-    for (int row = 0; row < 16; ++row) keys[row][j] = 0u;
+    for (int q = 0; q < SP_ROWS; ++q) keys[q][j] = 0u;
   __syncthreads();
-  for (int q = 0; q < RPW; ++q) {
-    const int rl = RPW * w + q;
-    if (lm0 + rl >= M) break;  // uniform for the wave; no workgroup barriers below
-    uint32_t v[PIVOT_PER];
+  if (lm0 + w >= M) return;  // uniform for the wave; no workgroup barriers below
+  uint32_t v[PIVOT_PER];
 #pragma unroll
-    for (int i = 0; i < PIVOT_PER / 4; ++i) {
-      const uint4 x = *reinterpret_cast<const uint4 *>(&keys[rl][256 * i + 4 * lane]);
-      v[4 * i] = x.x;
-      v[4 * i + 1] = x.y;
-      v[4 * i + 2] = x.z;
-      v[4 * i + 3] = x.w;
-    }
-    const uint32_t lo = pivot_of(v, &keys[rl][0], r);
-    if (lane == 0) plo[bh * M + lm0 + rl] = lo;
-    if (idx) {
-      // the row's keys back in LDS (pivot_of used its first words)
+  for (int i = 0; i < PIVOT_PER / 4; ++i) {
+    const uint4 x = *reinterpret_cast<const uint4 *>(&keys[w][256 * i + 4 * lane]);
+    v[4 * i] = x.x;
+    v[4 * i + 1] = x.y;
+    v[4 * i + 2] = x.z;
+    v[4 * i + 3] = x.w;
+  }
+  const uint32_t lo = pivot_of(v, &keys[w][0], r);
+  if (lane == 0) plo[bh * M + lm0 + w] = lo;
+  if (idx) {
+    // the row's keys back in LDS (pivot_of used its first words)
 #pragma unroll
-      for (int i = 0; i < PIVOT_PER / 4; ++i)
-        *reinterpret_cast<uint4 *>(&keys[rl][256 * i + 4 * lane]) = make_uint4(v[4 * i], v[4 * i + 1], v[4 * i + 2], v[4 * i + 3]);
-      uint32_t gt = 0;
+    for (int i = 0; i < PIVOT_PER / 4; ++i)
+      *reinterpret_cast<uint4 *>(&keys[w][256 * i + 4 * lane]) = make_uint4(v[4 * i], v[4 * i + 1], v[4 * i + 2], v[4 * i + 3]);
+    uint32_t gt = 0;
 #pragma unroll
-      for (int i = 0; i < PIVOT_PER; ++i) gt += v[i] > lo ? 1u : 0u;
-      const uint32_t need_eq = (uint32_t)kk - wave_sum_u32(gt);  // >= 1: lo is the kk-th largest
-      int32_t *out = idx + (bh * M + lm0 + rl) * (int64_t)kk;
-      uint32_t taken = 0, eq_seen = 0;
-      for (int j0 = 0; j0 < ns; j0 += 64) {
-        const int j = j0 + lane;
-        const uint32_t key = j < ns ? keys[rl][j] : 0u;  // 0 lies below every key
-        const uint64_t be = __ballot(key == lo);
-        const bool take = key > lo || (key == lo && eq_seen + lanes_below(be) < need_eq);
-        const uint64_t bt = __ballot(take);
-        if (take) out[taken + lanes_below(bt)] = j;
-        taken += (uint32_t)__popcll(bt);
-        eq_seen += (uint32_t)__popcll(be);
-      }
+    for (int i = 0; i < PIVOT_PER; ++i) gt += v[i] > lo ? 1u : 0u;
+    const uint32_t need_eq = (uint32_t)kk - wave_sum_u32(gt);  // >= 1: lo is the kk-th largest
+    int32_t *out = idx + (bh * M + lm0 + w) * (int64_t)kk;
+    uint32_t taken = 0, eq_seen = 0;
+    for (int j0 = 0; j0 < ns; j0 += 64) {
+      const int j = j0 + lane;
+      const uint32_t key = j < ns ? keys[w][j] : 0u;  // 0 lies below every key
+      const uint64_t be = __ballot(key == lo);
+      const bool take = key > lo || (key == lo && eq_seen + lanes_below(be) < need_eq);
+      const uint64_t bt = __ballot(take);
+      if (take) out[taken + lanes_below(bt)] = j;
+      taken += (uint32_t)__popcll(bt);
+      eq_seen += (uint32_t)__popcll(be);
     }
   }
 }

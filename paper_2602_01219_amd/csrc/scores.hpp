@@ -47,6 +47,21 @@ __device__ __forceinline__ bool dot_bound(float piv, float scale, float &t) {
   return false;
 }
 
+// Experts with routed queries: counts [BH, G] per routing group, G = M, or
+// 2 M (s > 1: expert lm's rank-1 pairs in group lm, the others in M + lm).
+// Without counts (the routing comes later) every expert counts as needed. An
+// expert without queries (about 40% of them on clustered inputs) needs no
+// top-k set: nothing reads it.
+struct LiveRows {
+  const int32_t *counts;
+  int G;
+  __device__ __forceinline__ bool operator()(int64_t bh, int lm, int M) const {
+    if (!counts) return true;
+    const int32_t *c = counts + bh * G + lm;
+    return c[0] > 0 || (G > M && c[M] > 0);
+  }
+};
+
 // ---------------------------------------------------------------------------
 // Scores and landmark values. Workgroup = 4 waves x 16 landmarks over one
 // chunk of SCORE_NC keys, key tiles of 64 staged in LDS (K row-major, V
@@ -72,6 +87,7 @@ struct SelectArgs {
   const uint32_t *plo;  // [rows] pivot keys
   uint32_t *ccnt;       // [rows, chunks] candidates listed
   uint2 *cand;          // [rows, chunks, SCORE_NC] (unscaled dot bits, token index)
+  LiveRows live;        // rows whose candidates are needed: the others' are only counted
 };
 
 template <typename T, int D, bool WRITE_S, bool DO_V, bool SELECT>
@@ -113,6 +129,7 @@ __device__ __forceinline__ void score_chunk(T *__restrict__ Ks, T *__restrict__ 
     scaled = nan_in || !(scale > 0.f && scale < INFINITY) || !dot_bound(piv, scale, dotpiv);
   }
   const bool write_row = WRITE_S && lm < M && (only_lm < 0 || lm == only_lm);
+  const uint32_t keep = SELECT && lm < M && sel.live(bh, lm, M) ? 15u : 0u;  // store the candidates?
   uint32_t listed = 0;  // SELECT: candidates of this landmark listed so far in the chunk
   // SELECT: the candidate regions of this wave's landmarks start here (the
   // wave index is uniform; readfirstlane lets the compiler keep it scalar)
@@ -207,6 +224,7 @@ __device__ __forceinline__ void score_chunk(T *__restrict__ Ks, T *__restrict__ 
       const uint32_t lane_off = ((uint32_t)p * (uint32_t)nchunks * SCORE_NC + listed) * 8u;
 #pragma unroll
       for (int kb = 0; kb < 4; ++kb) {
+        m[kb] &= keep;
         if (!__ballot(m[kb] != 0u)) continue;  // no candidate of this block in the wave
         uint32_t at = lane_off + ((pos >> (8 * kb)) & 255u) * 8u;
         const uint32_t ib = (uint32_t)(k0 + kb * 16 + 4 * g);
@@ -244,7 +262,7 @@ __device__ __forceinline__ void scores_rows_body(T *Ks, int b, int nb, const T *
                                                  const uint32_t *__restrict__ nrows, const int32_t *__restrict__ rows,
                                                  int N, int M, float scale, int nchunks) {
   const int64_t items = (int64_t)*nrows * nchunks;
-  const SelectArgs none{nullptr, nullptr, nullptr};
+  const SelectArgs none{};
   for (int64_t it = b; it < items; it += nb) {
     const int row = rows[it / nchunks];
     const int chunk = (int)(it % nchunks);
@@ -322,10 +340,11 @@ __device__ __forceinline__ void score16_chunk(char *tiles0, char *tiles1, const 
 
   Frag<bf16_t> qf[NG][D / 32];
   float piv[NG], dotpiv[NG];
-  bool nan_in[NG], scaled = false;
+  bool nan_in[NG], keep[NG], scaled = false;
 #pragma unroll
   for (int c = 0; c < NG; ++c) {
     const int lm = lmw + 16 * c + p;
+    keep[c] = SELECT && lm < M && sel.live(bh, lm, M);  // store the candidates?
     const int64_t row = bh * M + lm;
 #pragma unroll
     for (int ks = 0; ks < D / 32; ++ks) {
@@ -410,7 +429,7 @@ __device__ __forceinline__ void score16_chunk(char *tiles0, char *tiles1, const 
             uint32_t at = base + ((ppos[c] >> (8 * kb)) & 255u) * 8u;
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-              if (listed_key(c, pacc[c][kb][r], kb * 16 + 4 * g + r, pnv, masked_c)) {
+              if (keep[c] && listed_key(c, pacc[c][kb][r], kb * 16 + 4 * g + r, pnv, masked_c)) {
                 *reinterpret_cast<uint2 *>(cw + at) = make_uint2(__float_as_uint(pacc[c][kb][r]), iv[4 * kb + r]);
                 at += 8u;
               }

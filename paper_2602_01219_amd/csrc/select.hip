@@ -32,19 +32,19 @@
 
 namespace mita {
 
-// One workgroup per (16 landmarks, head) slot, slots spread over the XCDs in
+// One workgroup per (4 landmarks, head) slot, slots spread over the XCDs in
 // contiguous ranges (xcd_slot): a head's landmark blocks share an XCD, so
 // its sampled key rows are fetched into one L2 instead of one per block.
-template <typename T, int D, int NW>
-__global__ __launch_bounds__(64 * NW) void sample_pivot_kernel(const T *__restrict__ q_lm, const T *__restrict__ k,
-                                                               uint32_t *__restrict__ plo,
-                                                               uint32_t *__restrict__ fail_cnt, int N, int M, int ns,
-                                                               int r, float scale, int nbx, int nslots,
-                                                               int32_t *__restrict__ idx, int kk) {
-  __shared__ __align__(16) uint32_t keys[16][SP_PITCH];
+template <typename T, int D>
+__global__ __launch_bounds__(256) void sample_pivot_kernel(const T *__restrict__ q_lm, const T *__restrict__ k,
+                                                           uint32_t *__restrict__ plo,
+                                                           uint32_t *__restrict__ fail_cnt, int N, int M, int ns,
+                                                           int r, float scale, int nbx, int nslots,
+                                                           int32_t *__restrict__ idx, int kk) {
+  __shared__ __align__(16) uint32_t keys[SP_ROWS][SP_PITCH];
   const int f = xcd_slot((int)blockIdx.x, (int)gridDim.x / NXCD);
   if (f >= nslots) return;  // the whole workgroup
-  sample_pivot_body<T, D, NW>(keys, f % nbx, f / nbx, q_lm, k, plo, fail_cnt, N, M, ns, r, scale, idx, kk);
+  sample_pivot_body<T, D>(keys, f % nbx, f / nbx, q_lm, k, plo, fail_cnt, N, M, ns, r, scale, idx, kk);
 }
 
 template <typename T, int D, int CAP, bool MERGE>
@@ -54,10 +54,10 @@ __global__ __launch_bounds__(256) void finalize_kernel(const uint2 *__restrict__
                                                        int32_t *__restrict__ fail_list, int k, int cap, int nch,
                                                        const float2 *__restrict__ part_ml,
                                                        const float *__restrict__ part_o, T *__restrict__ v_lm, int M,
-                                                       float scale) {
+                                                       float scale, LiveRows live) {
   __shared__ FinalizeLds<T, D, CAP, MERGE> sh;
   finalize_row<T, D, CAP, MERGE>(sh, blockIdx.x, cand, ccnt, idx, fail_cnt, fail_list, k, cap, nch, part_ml, part_o,
-                                 v_lm, M, scale);
+                                 v_lm, M, scale, live);
 }
 
 // The same with one wave per row (lists of at most SEL_NS, at most 64 chunks).
@@ -68,13 +68,13 @@ __global__ __launch_bounds__(256) void finalize_wave_kernel(const uint2 *__restr
                                                             int32_t *__restrict__ fail_list, int k, int cap, int nch,
                                                             const float2 *__restrict__ part_ml,
                                                             const float *__restrict__ part_o, T *__restrict__ v_lm,
-                                                            int M, float scale, int64_t nrows) {
+                                                            int M, float scale, int64_t nrows, LiveRows live) {
   __shared__ FinalizeWaveLds sh[4];
   const int w = (int)threadIdx.x >> 6;
   const int64_t row = (int64_t)blockIdx.x * 4 + w;
   if (row >= nrows) return;  // the whole wave
   finalize_row_wave<T, D, MERGE>(sh[w], row, cand, ccnt, idx, fail_cnt, fail_list, k, cap, nch, part_ml, part_o,
-                                 v_lm, M, scale);
+                                 v_lm, M, scale, live);
 }
 
 // ---------------------------------------------------------------------------
@@ -83,13 +83,10 @@ __global__ __launch_bounds__(256) void finalize_wave_kernel(const uint2 *__restr
 template <typename T, int D>
 static hipError_t sample_pivot_t(const mita_cfg_t &c, const void *q_lm, const void *k, const SelectBufs &sb,
                                  hipStream_t st) {
-  // bf16: one sample tile and one row per wave (16 waves); fp32 (more
-  // registers per fragment): four waves, four tiles and four rows each
-  constexpr int NW = sizeof(T) == 2 ? 16 : 4;
-  const int nbx = (c.M + 15) / 16, nslots = nbx * (int)BH(c);
+  const int nbx = (c.M + SP_ROWS - 1) / SP_ROWS, nslots = nbx * (int)BH(c);
   const dim3 grid((unsigned)(NXCD * ((nslots + NXCD - 1) / NXCD)));
-  hipLaunchKernelGGL((sample_pivot_kernel<T, D, NW>), grid, dim3(64 * NW), 0, st, (const T *)q_lm, (const T *)k,
-                     sb.plo, sb.fail_cnt, c.N, c.M, sb.ns, sb.rank, eff_scale(c), nbx, nslots, sb.idx, c.k);
+  hipLaunchKernelGGL((sample_pivot_kernel<T, D>), grid, dim3(256), 0, st, (const T *)q_lm, (const T *)k, sb.plo,
+                     sb.fail_cnt, c.N, c.M, sb.ns, sb.rank, eff_scale(c), nbx, nslots, sb.idx, c.k);
   return launched("sample_pivot_kernel", st);
 }
 
@@ -102,8 +99,8 @@ hipError_t launch_select_pivots(const mita_cfg_t &c, const void *q_lm, const voi
   return c.d == 64 ? sample_pivot_t<bf16_t, 64>(c, q_lm, k, sb, st) : sample_pivot_t<bf16_t, 128>(c, q_lm, k, sb, st);
 }
 
-// The finalize kernel alone (one workgroup per landmark row).
-static hipError_t launch_select_finalize(const mita_cfg_t &c, const SelectBufs &sb, int32_t *idx, const void *partial,
+// The finalize kernel alone (a workgroup or a wave per landmark row).
+hipError_t launch_select_finalize(const mita_cfg_t &c, const SelectBufs &sb, int32_t *idx, const void *partial,
                                   void *v_lm, hipStream_t st) {
   const unsigned rows = (unsigned)(BH(c) * c.M);
   const int nch = score_chunks(c);
@@ -112,11 +109,12 @@ static hipError_t launch_select_finalize(const mita_cfg_t &c, const SelectBufs &
                          : nullptr;
 #define MITA_FINALIZE(TT, DD, CAP, MG)                                                                          \
   hipLaunchKernelGGL((finalize_kernel<TT, DD, CAP, MG>), dim3(rows), dim3(256), 0, st, sb.cand, sb.ccnt, idx,   \
-                     sb.fail_cnt, sb.fail_list, c.k, sb.cap, nch, ml, po, (TT *)v_lm, c.M, eff_scale(c))
+                     sb.fail_cnt, sb.fail_list, c.k, sb.cap, nch, ml, po, (TT *)v_lm, c.M, eff_scale(c), live)
 #define MITA_FINALIZE_WAVE(TT, DD, MG)                                                                          \
   hipLaunchKernelGGL((finalize_wave_kernel<TT, DD, MG>), dim3((rows + 3) / 4), dim3(256), 0, st, sb.cand, sb.ccnt, \
                      idx, sb.fail_cnt, sb.fail_list, c.k, sb.cap, nch, ml, po, (TT *)v_lm, c.M, eff_scale(c),      \
-                     (int64_t)rows)
+                     (int64_t)rows, live)
+  const LiveRows live{sb.live, sb.live_groups};
   // lists of at most SEL_NS entries over at most 64 chunks: one wave per row
   const bool wave = sb.cap <= SEL_NS && nch <= 64;
 #define MITA_FINALIZE_CAP(TT, DD, MG)     \
