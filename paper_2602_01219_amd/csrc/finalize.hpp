@@ -265,31 +265,41 @@ __device__ __forceinline__ void finalize_row_wave(FinalizeWaveLds &sh, int64_t r
         }
       }
     }
-    uint32_t v[PIVOT_PER];
-    int32_t ix[PIVOT_PER];
+    // (lists of at most 256 or 512 entries take fewer registers and steps)
+    auto select = [&](auto per_c) {
+      constexpr int P = decltype(per_c)::value;
+      uint32_t v[P];
+      int32_t ix[P];
 #pragma unroll
-    for (int m = 0; m < PIVOT_PER; ++m) {
-      const uint32_t j = (uint32_t)(lane + 64 * m);
-      const uint2 x = j < total ? sh.lst[j] : make_uint2(0u, 0u);
-      v[m] = x.x;
-      ix[m] = (int32_t)x.y;
-    }
-    const uint32_t K = pivot_of(v, sh.scratch, k);
-    uint32_t gt = 0;
+      for (int m = 0; m < P; ++m) {
+        const uint32_t j = (uint32_t)(lane + 64 * m);
+        const uint2 x = j < total ? sh.lst[j] : make_uint2(0u, 0u);
+        v[m] = x.x;
+        ix[m] = (int32_t)x.y;
+      }
+      const uint32_t K = pivot_of(v, sh.scratch, k);
+      uint32_t gt = 0;
 #pragma unroll
-    for (int m = 0; m < PIVOT_PER; ++m) gt += v[m] > K ? 1u : 0u;
-    const uint32_t need_eq = (uint32_t)k - wave_sum_u32(gt);  // >= 1: K is the k-th largest
-    int32_t *out = idx + row * (int64_t)k;
-    uint32_t taken = 0, eq_seen = 0;
+      for (int m = 0; m < P; ++m) gt += v[m] > K ? 1u : 0u;
+      const uint32_t need_eq = (uint32_t)k - wave_sum_u32(gt);  // >= 1: K is the k-th largest
+      int32_t *out = idx + row * (int64_t)k;
+      uint32_t taken = 0, eq_seen = 0;
 #pragma unroll
-    for (int m = 0; m < PIVOT_PER; ++m) {
-      const uint64_t be = __ballot(v[m] == K);
-      const bool take = v[m] > K || (v[m] == K && eq_seen + lanes_below(be) < need_eq);
-      const uint64_t bt = __ballot(take);
-      if (take) out[taken + lanes_below(bt)] = ix[m];
-      taken += (uint32_t)__popcll(bt);
-      eq_seen += (uint32_t)__popcll(be);
-    }
+      for (int m = 0; m < P; ++m) {
+        const uint64_t be = __ballot(v[m] == K);
+        const bool take = v[m] > K || (v[m] == K && eq_seen + lanes_below(be) < need_eq);
+        const uint64_t bt = __ballot(take);
+        if (take) out[taken + lanes_below(bt)] = ix[m];
+        taken += (uint32_t)__popcll(bt);
+        eq_seen += (uint32_t)__popcll(be);
+      }
+    };
+    if (total <= 256u)
+      select(std::integral_constant<int, 4>{});
+    else if (total <= 512u)
+      select(std::integral_constant<int, 8>{});
+    else
+      select(std::integral_constant<int, SEL_NS / 64>{});
   }
   if (MERGE)
 #pragma unroll

@@ -650,25 +650,31 @@ __global__ __launch_bounds__(256) void route_scatter_kernel(const int32_t *__res
 // the selection, of experts without queries. Workgroups [0, nSp) take the nS
 // sample slots (spread over the XCDs by xcd_slot so that a head's blocks share
 // an L2; slots past nS exit), the rest the routing grid; LDS is one buffer that
-// either part lays out for itself.
+// either part lays out for itself. Three waves per SIMD (four spill: 84 against
+// 78 us at 256 heads of 2048 tokens, M = 128).
 // ---------------------------------------------------------------------------
 template <typename T, int D>
-__global__ __launch_bounds__(BLOCK) void pivots_logits_kernel(const T *__restrict__ q_lm, const T *__restrict__ k,
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 2 ? 3 : 2))) void pivots_logits_kernel(const T *__restrict__ q_lm, const T *__restrict__ k,
                                                               uint32_t *__restrict__ plo,
-                                                              uint32_t *__restrict__ fail_cnt, int ns, int r,
+                                                              uint32_t *__restrict__ fail_cnt, int r, bool rows4,
                                                               int sample_x, int nS, int nSp, const T *__restrict__ q,
                                                               int32_t *__restrict__ expert,
                                                               int32_t *__restrict__ counts, int N, int M, float scale,
                                                               int ntiles, int route_x) {
-  constexpr int BYTES = SP_BYTES > RouteLds<T, D>::BYTES ? SP_BYTES : RouteLds<T, D>::BYTES;
+  constexpr int BYTES = (int)sizeof(PivotLds) > RouteLds<T, D>::BYTES ? (int)sizeof(PivotLds) : RouteLds<T, D>::BYTES;
+  static_assert(BYTES >= SP_BYTES, "either pivot body fits");
   __shared__ __align__(16) char buf[BYTES];
   extern __shared__ uint32_t cnt[];  // routing: [4][M]
   const int b = (int)blockIdx.x;
   if (b < nSp) {  // nSp = nS rounded up to whole XCD ranges (xcd_slot)
     const int f = xcd_slot(b, nSp / NXCD);
     if (f >= nS) return;
-    sample_pivot_body<T, D>(reinterpret_cast<uint32_t(*)[SP_PITCH]>(buf), f % sample_x, f / sample_x, q_lm, k, plo,
-                            fail_cnt, N, M, ns, r, scale);
+    if (rows4)
+      sample_pivot_body<T, D, false>(reinterpret_cast<uint32_t(*)[SP_PITCH]>(buf), f % sample_x, f / sample_x, q_lm, k,
+                                     plo, fail_cnt, N, M, SEL_NS, r, scale, nullptr, 0);
+    else
+      pivots16_body<T, D>(*reinterpret_cast<PivotLds *>(buf), f % sample_x, f / sample_x, q_lm, k, plo, fail_cnt, N, M,
+                          r, scale);
     return;
   }
   const int i = b - nSp;
@@ -787,8 +793,8 @@ __global__ __launch_bounds__(BLOCK) void direct_kernel(const T *__restrict__ q, 
   if (b < nSp) {
     const int f = xcd_slot(b, nSp / NXCD);
     if (f >= nS) return;
-    sample_pivot_body<T, D>(reinterpret_cast<uint32_t(*)[SP_PITCH]>(buf), f % sample_x, f / sample_x, q_lm, k, plo,
-                            fail_cnt, N, M, N, kk, scale, idx, kk);
+    sample_pivot_body<T, D, true>(reinterpret_cast<uint32_t(*)[SP_PITCH]>(buf), f % sample_x, f / sample_x, q_lm, k,
+                                  plo, fail_cnt, N, M, N, kk, scale, idx, kk);
     return;
   }
   if (VALUES && b < nSp + nV) {
@@ -1558,17 +1564,19 @@ template <typename T, int D>
 static hipError_t pivots_logits_t(const mita_cfg_t &c, const void *q, const void *q_lm, const void *k,
                                   const SelectBufs &sb, int32_t *expert, int32_t *counts, hipStream_t st) {
   const int bh = (int)BH(c);
-  const int sample_x = (c.M + SP_ROWS - 1) / SP_ROWS, nS = sample_x * bh, nSp = NXCD * ((nS + NXCD - 1) / NXCD);
+  const bool rows4 = (int64_t)(c.M + 15) / 16 * bh < PIVOT16_MIN;
+  const int sample_x = rows4 ? (c.M + SP_ROWS - 1) / SP_ROWS : (c.M + 15) / 16;
+  const int nS = sample_x * bh, nSp = NXCD * ((nS + NXCD - 1) / NXCD);
   const int nt = route_tiles(c), route_x = (nt + 3) / 4;
   hipLaunchKernelGGL((pivots_logits_kernel<T, D>), dim3((unsigned)(nSp + route_x * bh)), dim3(BLOCK),
-                     4 * (size_t)c.M * sizeof(uint32_t), st, (const T *)q_lm, (const T *)k, sb.plo, sb.fail_cnt, sb.ns,
-                     sb.rank, sample_x, nS, nSp, (const T *)q, expert, counts, c.N, c.M, eff_scale(c), nt, route_x);
+                     4 * (size_t)c.M * sizeof(uint32_t), st, (const T *)q_lm, (const T *)k, sb.plo, sb.fail_cnt, sb.rank,
+                     rows4, sample_x, nS, nSp, (const T *)q, expert, counts, c.N, c.M, eff_scale(c), nt, route_x);
   return launched("pivots_logits_kernel", st);
 }
 
 hipError_t launch_pivots_logits(const mita_cfg_t &c, const void *q, const void *q_lm, const void *k,
                                 const SelectBufs &sb, int32_t *expert, int32_t *counts, hipStream_t st) {
-  if (sb.ns > SEL_NS || sb.idx) return hipErrorInvalidValue;
+  if (sb.ns != SEL_NS || sb.idx) return hipErrorInvalidValue;
   if (c.dtype == MITA_F32)
     return c.d == 64 ? pivots_logits_t<float, 64>(c, q, q_lm, k, sb, expert, counts, st)
                      : pivots_logits_t<float, 128>(c, q, q_lm, k, sb, expert, counts, st);

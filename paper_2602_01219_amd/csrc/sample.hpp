@@ -4,6 +4,8 @@
 // samples; used by the pivot launch and by the launch that runs it together
 // with the routing logits.
 #pragma once
+#include <type_traits>
+
 #include "cdna4.hpp"
 #include "flash.hpp"
 #include "check.hpp"
@@ -51,9 +53,8 @@ __device__ __forceinline__ int wave_find_bin(const uint32_t *hist, uint32_t need
 }
 
 // ---------------------------------------------------------------------------
-// Pivot of one landmark row from its ns (<= SEL_NS) sampled keys, held by one
-// wave: lane l holds keys 4 l + 256 i + (0..3) in v[4 i .. 4 i + 3], 0 marking
-// a slot past ns (no score has key 0). The pivot is the exact r-th largest
+// Pivot of one landmark row from its at most 64 P keys, held by one wave, P per
+// lane (in any order; 0 marks an empty slot: no score has key 0). The pivot is the exact r-th largest
 // sampled key, found in two steps:
 //  1. a 256-bin LDS histogram over the VALUE range [fmin, fmax] of the row's
 //     samples (bin = floor((x - fmin) * 255.5 / (fmax - fmin)), a
@@ -70,8 +71,6 @@ __device__ __forceinline__ int wave_find_bin(const uint32_t *hist, uint32_t need
 // bin (clustered scores) take the bisection over all samples instead.
 // Uses words 0..383 of the LDS row at `lds`.
 // ---------------------------------------------------------------------------
-constexpr int PIVOT_PER = SEL_NS / 64;
-
 // need-th largest of the keys x, one per lane (0 = none); 1 <= need <= count
 // of nonzero keys. Bit b of the result is set iff at least `need` keys reach
 // the result's higher bits with b set.
@@ -98,11 +97,12 @@ __device__ __forceinline__ uint32_t wave_kth_key(const uint32_t (&x)[P], uint32_
   return t;
 }
 
-__device__ __forceinline__ uint32_t pivot_of(const uint32_t (&v)[PIVOT_PER], uint32_t *lds, int r) {
+template <int P>
+__device__ __forceinline__ uint32_t pivot_of(const uint32_t (&v)[P], uint32_t *lds, int r) {
   const int lane = threadIdx.x & 63;
   uint32_t mn = 0xffffffffu, mx = 0u;
 #pragma unroll
-  for (int i = 0; i < PIVOT_PER; ++i) {
+  for (int i = 0; i < P; ++i) {
     if (v[i]) mn = min(mn, v[i]);
     mx = max(mx, v[i]);
   }
@@ -113,11 +113,11 @@ __device__ __forceinline__ uint32_t pivot_of(const uint32_t (&v)[PIVOT_PER], uin
   if (!(span < INFINITY) || !(inv < INFINITY)) return wave_kth_key(v, (uint32_t)r);
   // (x - fmin) <= span after rounding, so (x - fmin) * inv < 256: bins 0..255;
   // empty slots go to words 256 + lane (distinct, never read as counts)
-  uint32_t bin[PIVOT_PER];
+  uint32_t bin[P];
 #pragma unroll
   for (int q = 0; q < 4; ++q) lds[lane + 64 * q] = 0u;
 #pragma unroll
-  for (int i = 0; i < PIVOT_PER; ++i) {
+  for (int i = 0; i < P; ++i) {
     const uint32_t b = min((uint32_t)((key_to_float(v[i]) - fmin) * inv), 255u);
     bin[i] = v[i] ? b : 256u + (uint32_t)lane;
     atomicAdd(lds + bin[i], 1u);
@@ -129,7 +129,7 @@ __device__ __forceinline__ uint32_t pivot_of(const uint32_t (&v)[PIVOT_PER], uin
   uint32_t *slot = lds + 320;
   uint32_t base = 0;
 #pragma unroll
-  for (int i = 0; i < PIVOT_PER; ++i) {
+  for (int i = 0; i < P; ++i) {
     const uint64_t m = __ballot(bin[i] == b);
     if (bin[i] == b) slot[base + lanes_below(m)] = v[i];
     base += (uint32_t)__popcll(m);
@@ -157,17 +157,16 @@ constexpr int SP_BYTES = SP_ROWS * SP_PITCH * 4;
 
 // Workgroup (bx, by) of the sample grid (landmarks 4 bx .. of head by); keys:
 // SP_ROWS LDS rows of SP_PITCH words.
-// With idx (only when the sample is the whole row, ns == N, and r == kk)
-// the rows' top-kk sets are written too, in ascending token order: every key
-// above the pivot and, in token order, as many keys equal to it as the set
-// still needs (the order of the top-k: larger score first, lower index first
-// among equal scores).
-template <typename T, int D>
+// SETS (the sample is the whole row, ns == N, and r == kk): the rows' top-kk
+// sets are written too, in ascending token order: every key above the pivot
+// and, in token order, as many keys equal to it as the set still needs (the
+// order of the top-k: larger score first, lower index first among equal
+// scores).
+template <typename T, int D, bool SETS>
 __device__ __forceinline__ void sample_pivot_body(uint32_t (*keys)[SP_PITCH], int bx, int by,
                                                   const T *__restrict__ q_lm, const T *__restrict__ k,
                                                   uint32_t *__restrict__ plo, uint32_t *__restrict__ fail_cnt, int N,
-                                                  int M, int ns, int r, float scale, int32_t *__restrict__ idx = nullptr,
-                                                  int kk = 0) {
+                                                  int M, int ns, int r, float scale, int32_t *__restrict__ idx, int kk) {
   const int64_t bh = by;
   const int lm0 = bx * SP_ROWS, lmb = lm0 & ~15;  // the rows; their column block
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 4, p = lane & 15;
@@ -231,25 +230,29 @@ __device__ __forceinline__ void sample_pivot_body(uint32_t (*keys)[SP_PITCH], in
     for (int q = 0; q < SP_ROWS; ++q) keys[q][j] = 0u;
   __syncthreads();
   if (lm0 + w >= M) return;  // uniform for the wave; no workgroup barriers below
-  uint32_t v[PIVOT_PER];
+  // lane l holds keys 4 l + 256 i + (0..3); rows of at most 256 or 512 samples
+  // take fewer registers and steps
+  auto row_pivot = [&](auto per_c) {
+    constexpr int P = decltype(per_c)::value;
+    uint32_t v[P];
 #pragma unroll
-  for (int i = 0; i < PIVOT_PER / 4; ++i) {
-    const uint4 x = *reinterpret_cast<const uint4 *>(&keys[w][256 * i + 4 * lane]);
-    v[4 * i] = x.x;
-    v[4 * i + 1] = x.y;
-    v[4 * i + 2] = x.z;
-    v[4 * i + 3] = x.w;
-  }
-  const uint32_t lo = pivot_of(v, &keys[w][0], r);
-  if (lane == 0) plo[bh * M + lm0 + w] = lo;
-  if (idx) {
+    for (int i = 0; i < P / 4; ++i) {
+      const uint4 x = *reinterpret_cast<const uint4 *>(&keys[w][256 * i + 4 * lane]);
+      v[4 * i] = x.x;
+      v[4 * i + 1] = x.y;
+      v[4 * i + 2] = x.z;
+      v[4 * i + 3] = x.w;
+    }
+    const uint32_t lo = pivot_of(v, &keys[w][0], r);
+    if (lane == 0) plo[bh * M + lm0 + w] = lo;
+    if (!SETS) return;
     // the row's keys back in LDS (pivot_of used its first words)
 #pragma unroll
-    for (int i = 0; i < PIVOT_PER / 4; ++i)
+    for (int i = 0; i < P / 4; ++i)
       *reinterpret_cast<uint4 *>(&keys[w][256 * i + 4 * lane]) = make_uint4(v[4 * i], v[4 * i + 1], v[4 * i + 2], v[4 * i + 3]);
     uint32_t gt = 0;
 #pragma unroll
-    for (int i = 0; i < PIVOT_PER; ++i) gt += v[i] > lo ? 1u : 0u;
+    for (int i = 0; i < P; ++i) gt += v[i] > lo ? 1u : 0u;
     const uint32_t need_eq = (uint32_t)kk - wave_sum_u32(gt);  // >= 1: lo is the kk-th largest
     int32_t *out = idx + (bh * M + lm0 + w) * (int64_t)kk;
     uint32_t taken = 0, eq_seen = 0;
@@ -263,7 +266,203 @@ __device__ __forceinline__ void sample_pivot_body(uint32_t (*keys)[SP_PITCH], in
       taken += (uint32_t)__popcll(bt);
       eq_seen += (uint32_t)__popcll(be);
     }
+  };
+  if (ns <= 256)
+    row_pivot(std::integral_constant<int, 4>{});
+  else if (ns <= 512)
+    row_pivot(std::integral_constant<int, 8>{});
+  else
+    row_pivot(std::integral_constant<int, 16>{});
+}
+
+// ---------------------------------------------------------------------------
+// The pivots alone, from SEL_NS samples of N > SEL_NS keys. Workgroup = 4 waves
+// for one MFMA column block of 16 landmark rows; wave w scores every fourth
+// 64-key tile, and the samples stay in registers as floats in key order (NaN
+// as -inf, -0 as +0): lane (g, p) of a wave holds 64 of row p. The exact r-th
+// largest of each row, by the steps of pivot_of over all 16 rows at once:
+// range, 256-bin histogram over it, the bin of rank r, that bin's few samples
+// ranked. Rows whose range is not finite or whose bin holds more than 64
+// samples bisect the 32 key bits over all samples instead.
+// The sampled keys are read once per 16 rows and the samples cross LDS only as
+// histogram counts: 21 KB per workgroup, so that the routing logits fit beside
+// it (16 rows of keys took 66 KB and 16 waves; with four rows per workgroup, at
+// 256 heads of 2048 tokens, M = 128, the launch with the logits took 159 us, 81
+// this way). Few rows (PIVOT16_MIN blocks) take four per workgroup all the same:
+// there the chain of one block counts, not the products.
+// ---------------------------------------------------------------------------
+constexpr int PIVOT16_MIN = 64;  // fewer 16-row blocks than this: a quarter of the CUs at most would work
+struct PivotLds {
+  uint32_t hist[16][260];  // counts per bin; rows start 4 banks apart
+  uint32_t slot[16][64];   // the keys of a row's bin
+  uint32_t red[4][2][16];  // the waves' key ranges per row
+  uint32_t n[16];          // keys in slot
+  uint32_t bin[16], above[16];
+  uint32_t bad;            // some row bisects
+};
+
+__device__ __forceinline__ float canonical_score(float x) { return x != x ? -INFINITY : x + 0.f; }
+
+template <typename T, int D>
+__device__ __forceinline__ void pivots16_body(PivotLds &sh, int bx, int by, const T *__restrict__ q_lm,
+                                              const T *__restrict__ k, uint32_t *__restrict__ plo,
+                                              uint32_t *__restrict__ fail_cnt, int N, int M, int r, float scale) {
+  constexpr int NT = SEL_NS / (4 * TK);  // tiles per wave
+  static_assert(NT * 4 * TK == SEL_NS, "whole tiles");
+  const int64_t bh = by;
+  const int lm0 = bx * 16;
+  const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, g = lane >> 4, p = lane & 15;
+  if (bx == 0 && by == 0 && tid == 0) *fail_cnt = 0;
+  for (int i = tid; i < 16 * 260; i += 256) (&sh.hist[0][0])[i] = 0u;
+  if (tid < 16) sh.n[tid] = 0u;
+  if (tid == 0) sh.bad = 0u;
+  Frag<T> qf[D / 32];
+#pragma unroll
+  for (int ks = 0; ks < D / 32; ++ks) {
+    if (lm0 + p < M)
+      qf[ks].load(q_lm + (bh * M + lm0 + p) * D + ks * 32 + g * 8);
+    else
+      qf[ks].zero();
   }
+  const T *kb_ = k + bh * (int64_t)N * D;
+  float x[NT][4][4];
+#pragma unroll
+  for (int t = 0; t < NT; ++t) {
+    Frag<T> a[4][D / 32];  // all loads of a tile issued before the first is used
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb) {
+      const int64_t pos = sample_pos((4 * t + w) * TK + kb * 16 + p, N, SEL_NS);
+#pragma unroll
+      for (int ks = 0; ks < D / 32; ++ks) a[kb][ks].load(kb_ + pos * D + ks * 32 + g * 8);
+    }
+#pragma unroll
+    for (int kb = 0; kb < 4; ++kb) {
+      f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int ks = 0; ks < D / 32; ++ks) acc = mma(a[kb][ks], qf[ks], acc);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) x[t][kb][q] = canonical_score(acc[q] * scale);
+    }
+  }
+  // every sample once: f(x)
+  auto each = [&](auto f) {
+#pragma unroll
+    for (int t = 0; t < NT; ++t)
+#pragma unroll
+      for (int kb = 0; kb < 4; ++kb)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) f(x[t][kb][q]);
+  };
+  // the rows' ranges: lanes, lane groups, waves
+  float lo = INFINITY, hi = -INFINITY;
+  each([&](float v) {
+    lo = fminf(lo, v);
+    hi = fmaxf(hi, v);
+  });
+#pragma unroll
+  for (int o = 16; o <= 32; o <<= 1) {
+    lo = fminf(lo, __shfl_xor(lo, o));
+    hi = fmaxf(hi, __shfl_xor(hi, o));
+  }
+  if (g == 0) {
+    sh.red[w][0][p] = __float_as_uint(lo);
+    sh.red[w][1][p] = __float_as_uint(hi);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    lo = fminf(lo, __uint_as_float(sh.red[i][0][p]));
+    hi = fmaxf(hi, __uint_as_float(sh.red[i][1][p]));
+  }
+  const float span = hi - lo, inv = 255.5f / span;
+  // one value only (span 0) needs no bins; a range or scale that is not finite bisects
+  const bool same = hi == lo, ok = !same && span < INFINITY && inv < INFINITY;
+  auto bin_of = [&](float v) { return min((uint32_t)((v - lo) * inv), 255u); };
+  if (ok) each([&](float v) { atomicAdd(&sh.hist[p][bin_of(v)], 1u); });
+  if (w == 0 && g == 0 && !same && !ok) sh.bad = 1u;
+  __syncthreads();
+  {
+    // wave w's lane group g: the bin of row 4 w + g that holds rank r, lane p
+    // summing bins 255 - 16 p down to 240 - 16 p
+    const int row = 4 * w + g;
+    uint32_t c[16], sum = 0;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) {
+      c[i] = sh.hist[row][255 - 16 * p - i];
+      sum += c[i];
+    }
+    uint32_t incl = sum;
+#pragma unroll
+    for (int o = 1; o < 16; o <<= 1) {
+      const uint32_t y = (uint32_t)__shfl_up((int)incl, o, 16);
+      if (p >= o) incl += y;
+    }
+    uint32_t ab = incl - sum;
+    if (ab < (uint32_t)r && (uint32_t)r <= incl) {  // one lane of the row (none if it has no bins)
+      int b = 0;
+      uint32_t cb = 0;
+      bool found = false;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) {
+        const bool here = !found && ab + c[i] >= (uint32_t)r;
+        b = here ? 255 - 16 * p - i : b;
+        cb = here ? c[i] : cb;
+        found = found || here;
+        ab += found ? 0u : c[i];
+      }
+      sh.bin[row] = (uint32_t)b;
+      sh.above[row] = ab;
+      if (cb > 64u) sh.bad = 1u;
+    }
+  }
+  __syncthreads();
+  if (sh.bad == 0u) {  // uniform
+    const uint32_t mybin = sh.bin[p];
+    if (ok)
+      each([&](float v) {
+        if (bin_of(v) == mybin) sh.slot[p][atomicAdd(&sh.n[p], 1u) & 63u] = ordered_key(v);
+      });
+    __syncthreads();
+    // wave w ranks the slots of rows 4 w .. 4 w + 3
+    for (int i = 0; i < 4; ++i) {
+      const int row = 4 * w + i;
+      if (lm0 + row >= M) break;  // uniform for the wave
+      const uint32_t n = sh.n[row];
+      // (a row of one value: no slots)
+      uint32_t key = ordered_key(__shfl(lo, row));
+      if (n > 0u) {
+        const uint32_t mine = (uint32_t)lane < n ? sh.slot[row][lane] : 0u;
+        uint32_t rank = 0;
+        for (uint32_t j = 0; j < n; ++j) {
+          const uint32_t other = sh.slot[row][j];
+          rank += other > mine || (other == mine && j < (uint32_t)lane) ? 1u : 0u;
+        }
+        const uint64_t m = __ballot((uint32_t)lane < n && rank == (uint32_t)r - 1u - sh.above[row]);
+        key = (uint32_t)__shfl((int)mine, __ffsll((unsigned long long)m) - 1);
+      }
+      if (lane == 0) plo[bh * M + lm0 + row] = key;
+    }
+    return;
+  }
+  // bisection over all samples, every row: bit b of the result is set iff at
+  // least r samples reach the result's higher bits with b set (counts of step
+  // `bit` in hist row bit / 2, words 128 (bit & 1) + row of a fresh buffer)
+  __syncthreads();
+  for (int i = tid; i < 16 * 260; i += 256) (&sh.hist[0][0])[i] = 0u;
+  __syncthreads();
+  uint32_t t = 0;
+  for (int bit = 31; bit >= 0; --bit) {
+    const uint32_t c = t | (1u << bit);
+    uint32_t n = 0;
+    each([&](float v) { n += ordered_key(v) >= c ? 1u : 0u; });
+    n += (uint32_t)__shfl_xor((int)n, 16);
+    n += (uint32_t)__shfl_xor((int)n, 32);
+    uint32_t *cell = &sh.hist[bit >> 1][128 * (bit & 1) + p];
+    if (g == 0) atomicAdd(cell, n);
+    __syncthreads();
+    if (*cell >= (uint32_t)r) t = c;
+  }
+  if (w == 0 && g == 0 && lm0 + p < M) plo[bh * M + lm0 + p] = t;
 }
 
 }  // namespace mita

@@ -30,21 +30,27 @@
 #include "sample.hpp"
 #include "worklist.hpp"
 
+#include <type_traits>
+
 namespace mita {
 
-// One workgroup per (4 landmarks, head) slot, slots spread over the XCDs in
-// contiguous ranges (xcd_slot): a head's landmark blocks share an XCD, so
-// its sampled key rows are fetched into one L2 instead of one per block.
-template <typename T, int D>
+// One workgroup per (16 landmarks, head) slot, or (4 landmarks, head) with
+// the sets (SETS: the sample is the whole row); slots spread over the XCDs in
+// contiguous ranges (xcd_slot): a head's landmark blocks share an XCD, so its
+// sampled key rows are fetched into one L2 instead of one per block.
+template <typename T, int D, bool SETS>
 __global__ __launch_bounds__(256) void sample_pivot_kernel(const T *__restrict__ q_lm, const T *__restrict__ k,
                                                            uint32_t *__restrict__ plo,
-                                                           uint32_t *__restrict__ fail_cnt, int N, int M, int ns,
-                                                           int r, float scale, int nbx, int nslots,
-                                                           int32_t *__restrict__ idx, int kk) {
-  __shared__ __align__(16) uint32_t keys[SP_ROWS][SP_PITCH];
+                                                           uint32_t *__restrict__ fail_cnt, int N, int M, int r,
+                                                           float scale, int nbx, int nslots,
+                                                           int32_t *__restrict__ idx) {
+  __shared__ __align__(16) std::conditional_t<SETS, uint32_t[SP_ROWS][SP_PITCH], PivotLds> sh;
   const int f = xcd_slot((int)blockIdx.x, (int)gridDim.x / NXCD);
   if (f >= nslots) return;  // the whole workgroup
-  sample_pivot_body<T, D>(keys, f % nbx, f / nbx, q_lm, k, plo, fail_cnt, N, M, ns, r, scale, idx, kk);
+  if constexpr (SETS)
+    sample_pivot_body<T, D, true>(sh, f % nbx, f / nbx, q_lm, k, plo, fail_cnt, N, M, N, r, scale, idx, r);
+  else
+    pivots16_body<T, D>(sh, f % nbx, f / nbx, q_lm, k, plo, fail_cnt, N, M, r, scale);
 }
 
 template <typename T, int D, int CAP, bool MERGE>
@@ -83,17 +89,24 @@ __global__ __launch_bounds__(256) void finalize_wave_kernel(const uint2 *__restr
 template <typename T, int D>
 static hipError_t sample_pivot_t(const mita_cfg_t &c, const void *q_lm, const void *k, const SelectBufs &sb,
                                  hipStream_t st) {
-  const int nbx = (c.M + SP_ROWS - 1) / SP_ROWS, nslots = nbx * (int)BH(c);
+  const bool sets = sb.idx != nullptr;
+  const int nbx = sets ? (c.M + SP_ROWS - 1) / SP_ROWS : (c.M + 15) / 16, nslots = nbx * (int)BH(c);
   const dim3 grid((unsigned)(NXCD * ((nslots + NXCD - 1) / NXCD)));
-  hipLaunchKernelGGL((sample_pivot_kernel<T, D>), grid, dim3(256), 0, st, (const T *)q_lm, (const T *)k, sb.plo,
-                     sb.fail_cnt, c.N, c.M, sb.ns, sb.rank, eff_scale(c), nbx, nslots, sb.idx, c.k);
+#define MITA_PIVOTS(SETS)                                                                                          \
+  hipLaunchKernelGGL((sample_pivot_kernel<T, D, SETS>), grid, dim3(256), 0, st, (const T *)q_lm, (const T *)k, sb.plo, \
+                     sb.fail_cnt, c.N, c.M, sb.rank, eff_scale(c), nbx, nslots, sb.idx)
+  if (sets)
+    MITA_PIVOTS(true);
+  else
+    MITA_PIVOTS(false);
+#undef MITA_PIVOTS
   return launched("sample_pivot_kernel", st);
 }
 
 hipError_t launch_select_pivots(const mita_cfg_t &c, const void *q_lm, const void *k, const SelectBufs &sb,
                                 hipStream_t st) {
-  if (sb.ns > SEL_NS) return hipErrorInvalidValue;  // the workgroup holds SEL_NS keys per row
-  if (sb.idx && (sb.ns != c.N || sb.rank != c.k)) return hipErrorInvalidValue;  // direct sets need the whole row
+  // sets from the whole row, or pivots of SEL_NS samples
+  if (sb.idx ? sb.ns != c.N || sb.ns > SEL_NS || sb.rank != c.k : sb.ns != SEL_NS) return hipErrorInvalidValue;
   if (c.dtype == MITA_F32)
     return c.d == 64 ? sample_pivot_t<float, 64>(c, q_lm, k, sb, st) : sample_pivot_t<float, 128>(c, q_lm, k, sb, st);
   return c.d == 64 ? sample_pivot_t<bf16_t, 64>(c, q_lm, k, sb, st) : sample_pivot_t<bf16_t, 128>(c, q_lm, k, sb, st);
