@@ -467,10 +467,14 @@ __global__ __launch_bounds__(256) void bwd_kernel(BwdArgs a) {
 constexpr int BWD16_TK = 32;
 constexpr int BWD16_LMV_CHUNK = 2048;  // most keys per workgroup of the landmark queries' gradient
 template <int D> constexpr int BWD16_GROUPS = D == 64 ? 2 : 1;
+// query groups per wave of the dQ pass: at d = 128 two waves per SIMD instead of
+// four, but half the LDS reads per MFMA (16 heads of 4096 tokens, M = 64,
+// k = 256: 80 -> 60 us; the landmark mode has too few workgroups to gain)
+constexpr int BWD16_DQ_GROUPS = 2;
 template <int D> constexpr size_t bwd16_tiles_lds() { return 4 * (size_t)DmaTile<D, BWD16_TK>::BYTES; }
 
 template <int D, bool SHARED, bool ROUTED, int NG, bool LMV = false>
-__global__ __launch_bounds__(256 / NG) __attribute__((amdgpu_waves_per_eu(4))) void bwd_att16_kernel(BwdArgs a) {
+__global__ __launch_bounds__(256 / NG) __attribute__((amdgpu_waves_per_eu(D == 128 && NG == 2 ? 2 : 4))) void bwd_att16_kernel(BwdArgs a) {
   constexpr int NW = 4 / NG;  // waves per workgroup
   constexpr int NT = 64 * NW;
   constexpr int TK = BWD16_TK;
@@ -1466,7 +1470,7 @@ static hipError_t bwd_t(const mita_cfg_t &c, const BwdBufs &b, hipStream_t st) {
   if constexpr (sizeof(T) == 2) {
     // bf16 with the key row list in LDS: the DMA-tiled kernel
     if (list_in_lds(nlist, bwd16_tiles_lds<D>())) {
-      constexpr int NG = BWD16_GROUPS<D>;
+      constexpr int NG = BWD16_DQ_GROUPS;
       const dim3 blk(256 / NG);
       const size_t dyn = (size_t)nlist * sizeof(uint32_t);
       if (c.use_shared && c.use_routed)

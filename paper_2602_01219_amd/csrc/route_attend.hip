@@ -921,8 +921,6 @@ template <typename T, int D> constexpr size_t attend_tiles_lds() {
   return 2 * (size_t)(TileDims<T, D>::K_ELEMS + TileDims<T, D>::V_ELEMS) * sizeof(T);
 }
 template <int D> constexpr size_t attend16_tiles_lds() { return 4 * (size_t)DmaTile<D, 32>::BYTES; }
-// query groups per wave of attend16_kernel
-template <int D> constexpr int ATT16_GROUPS = D == 64 ? 2 : 1;
 
 
 template <typename T, int D, bool SHARED, bool ROUTED, bool FUSED, bool IDX_LDS, bool MULTI>
@@ -1187,10 +1185,15 @@ __global__ __launch_bounds__(BLOCK) void attend_kernel(const T *__restrict__ q, 
 // the LDS reads per MFMA are half those of NG = 1, and the two groups' MFMA
 // chains are independent.
 // ---------------------------------------------------------------------------
-// d = 64, one group per wave: registers for seven waves per SIMD (seven
-// workgroups of 16 + 2.5 KB LDS fit a CU at M + k = 640); two groups per
-// wave: four waves per SIMD (eight two-wave workgroups per CU)
-#define ATTEND16_OCCUPANCY __attribute__((amdgpu_waves_per_eu(NG == 2 ? 4 : (D == 64 ? 7 : 4))))
+// Two groups per wave, two waves: every fragment read from LDS serves two MFMAs.
+// d = 64: four waves per SIMD (eight workgroups per CU). d = 128: two (216
+// registers, four workgroups per CU): at 65536 tokens, 16 heads, M = 256,
+// k = 1024 952 to 1011 us against 1108 to 1160 with one group per wave and
+// four waves per SIMD, whose LDS reads per MFMA are twice as many. Four waves
+// on one tile (128 queries, half the fetches) leave more waves without
+// queries: 1170 us there, and 95 -> 104 us at 16384 tokens, d = 64.
+constexpr int ATT16_GROUPS = 2;
+#define ATTEND16_OCCUPANCY __attribute__((amdgpu_waves_per_eu(D == 64 ? 4 : 2)))
 
 template <int D, bool SHARED, bool ROUTED, bool FUSED, bool MULTI, int NG>
 __global__ __launch_bounds__(256 / NG) ATTEND16_OCCUPANCY void attend16_kernel(
@@ -1678,8 +1681,7 @@ static hipError_t attend_t3(const mita_cfg_t &c, const void *q, const void *q_lm
     // bf16: lists of up to IDX_LDS_MAX - 1 rows (and the kernel's rerun flag)
     // beside the 16 / 32 KB DMA tiles
     if (list_in_lds(nlist + 1, attend16_tiles_lds<D>())) {
-      // d = 64: two query groups per wave, two waves; d = 128: one group, four
-      constexpr int NG = ATT16_GROUPS<D>;
+      constexpr int NG = ATT16_GROUPS;
       hipLaunchKernelGGL((attend16_kernel<D, SH, RT, FU, MU, NG>), grid, dim3(256 / NG),
                          (size_t)(nlist + 1) * sizeof(int32_t),
                          st, (const bf16_t *)q, (const bf16_t *)q_lm, (const bf16_t *)v_lm, (const bf16_t *)rk,
