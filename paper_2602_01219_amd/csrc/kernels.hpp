@@ -15,8 +15,8 @@ namespace mita {
 hipError_t launched(const char *kernel, hipStream_t st);
 
 // Landmark pooling (Sec. 3.2; Algorithm 1 AdaptiveAvgPool): q [BH,N,d] -> q_lm [BH,M,d].
-// If zero_counts (zero_cursor) is not NULL its BH*M entries are set to 0
-// (routing totals; the forward's placement cursors).
+// If zero_counts (zero_cursor) is not NULL its BH*route_groups entries are set
+// to 0 (routing totals; the forward's placement cursors).
 hipError_t launch_pool(const mita_cfg_t &c, const void *q, void *q_lm, int32_t *zero_counts, int32_t *zero_cursor,
                        hipStream_t st);
 
@@ -99,12 +99,18 @@ hipError_t launch_pivots_logits(const mita_cfg_t &c, const void *q, const void *
 
 // The finish of the fused selection (launch_select_finish: top-k into idx,
 // fallback rows, landmark-value merge into v_lm when given), its fallback rows
-// sharing a launch with the placement of the queries by expert (perm, offsets,
-// tile_start; cursor [BH,M] zero on entry), after launch_pivots_logits.
+// sharing a launch with the placement of the routing items by group (perm,
+// offsets, tile_start; cursor [BH,groups] zero on entry). group: the items'
+// groups, from launch_pivots_logits (the experts) or launch_route_tops.
 hipError_t launch_select_place(const mita_cfg_t &c, const void *q_lm, const void *k, const SelectBufs &sel, float *S,
-                               int32_t *idx, const void *partial, void *v_lm, const int32_t *expert,
+                               int32_t *idx, const void *partial, void *v_lm, const int32_t *group,
                                const int32_t *counts, int32_t *cursor, int32_t *perm, int32_t *offsets,
                                int32_t *tile_start, hipStream_t st);
+
+// s > 1: the ranked experts [BH,N,s] and the pairs' groups [BH,N*s], and the
+// group sizes counts [BH,2M] (zero on entry).
+hipError_t launch_route_tops(const mita_cfg_t &c, const void *q, const void *q_lm, int32_t *expert, int32_t *group,
+                             int32_t *counts, hipStream_t st);
 
 // Direct selection (N <= SEL_NS): the top-k sets, the landmark values (v_lm,
 // when given; partials in `partial`) and the routing (perm, offsets,

@@ -129,42 +129,40 @@ int enqueue_experts(const mita_cfg_t *c, const void *q, const void *k, const voi
   }
   const bool direct = fused && sel.idx;
 
-  // s > 1 routes through its own launches (stable grouping of the pairs);
-  // otherwise, with the fused selection and in-place gather, routing and
-  // selection share launches, the grouping is not stable and its placement
-  // cursors (in the tile_base buffer) start at zero
+  // with the fused selection and in-place gather, routing and selection share
+  // launches, the grouping is not stable and its placement cursors (in the
+  // tile_base buffer) start at zero
   const bool multi = multi_route(*c);
-  const bool combined = fused && !staged && !multi;
+  const bool combined = fused && !staged;
+  const bool one = combined && direct && !multi;  // everything before the attention in one launch
   int32_t *group = multi ? (int32_t *)(w + L.group) : nullptr;
-  const int64_t rows = BH(*c) * c->M;
-  int32_t *zero_counts = c->use_routed && !multi && !(combined && direct) ? counts : nullptr;
-  int32_t *zero_cursor = combined && !direct ? tile_base : nullptr;
+  const int64_t groups = BH(*c) * route_groups(*c);
+  int32_t *zero_counts = c->use_routed && !one && (combined || !multi) ? counts : nullptr;
+  int32_t *zero_cursor = combined && !one ? tile_base : nullptr;
   rec.stage = 0;
   if (q_lm_in) {
-    TRY(hip_status(launch_zero2(zero_counts, zero_counts ? rows : 0, zero_cursor, zero_cursor ? rows : 0, st),
+    TRY(hip_status(launch_zero2(zero_counts, zero_counts ? groups : 0, zero_cursor, zero_cursor ? groups : 0, st),
                    "landmarks"));
   } else {
     TRY(hip_status(launch_pool(*c, q, q_lm_ws, zero_counts, zero_cursor, st), "landmarks"));
   }
-  if (combined && direct) {
+  if (one) {
     rec.stage = 4;
     return hip_status(launch_direct(*c, q, q_lm, k, v, sel, w + L.partial, v_lm, perm, offsets, tile_start, st),
                       "select and route");
   }
-  auto route = [&]() -> int {
-    rec.stage = 4;
-    return hip_status(
-        launch_route(*c, q, q_lm, expert, perm, offsets, tile_cnt, tile_base, counts, tile_start, group, st), "route");
-  };
-  // where the experts' sizes are known before the scores, the sets of experts
-  // without queries are not formed (the staged gather reads every set)
-  if (fused && multi) TRY(route());
-  if (combined || (fused && multi && !staged)) {
+  if (combined) {
+    // the experts' sizes are known before the scores: the sets of experts
+    // without queries are not formed (the staged gather reads every set)
     sel.live = counts;
     sel.live_groups = route_groups(*c);
   }
+  if (combined && multi) {
+    rec.stage = 4;
+    TRY(hip_status(launch_route_tops(*c, q, q_lm, expert, group, counts, st), "route"));
+  }
   rec.stage = 1;
-  if (combined)
+  if (combined && !multi)
     TRY(hip_status(launch_pivots_logits(*c, q, q_lm, k, sel, expert, counts, st), "select pivots"));
   else if (fused)
     TRY(hip_status(launch_select_pivots(*c, q_lm, k, sel, st), "select pivots"));
@@ -174,8 +172,8 @@ int enqueue_experts(const mita_cfg_t *c, const void *q, const void *k, const voi
                  "scores"));
   rec.stage = 2;
   if (combined)
-    TRY(hip_status(launch_select_place(*c, q_lm, k, sel, S, idx, w + L.partial, v_lm, expert, counts, tile_base, perm,
-                                       offsets, tile_start, st),
+    TRY(hip_status(launch_select_place(*c, q_lm, k, sel, S, idx, w + L.partial, v_lm, multi ? group : expert, counts,
+                                       tile_base, perm, offsets, tile_start, st),
                    "topk"));
   else if (fused)
     TRY(hip_status(launch_select_finish(*c, q_lm, k, sel, S, idx, w + L.partial, v_lm, st), "topk"));
@@ -183,7 +181,11 @@ int enqueue_experts(const mita_cfg_t *c, const void *q, const void *k, const voi
     TRY(hip_status(launch_topk(*c, S, idx, st), "topk"));
   rec.stage = 3;
   if (staged) TRY(hip_status(launch_gather(*c, k, v, idx, w + L.kx, w + L.vx, st), "gather"));
-  if (c->use_routed && !combined && !(fused && multi)) TRY(route());
+  rec.stage = 4;
+  if (c->use_routed && !combined)
+    TRY(hip_status(
+        launch_route(*c, q, q_lm, expert, perm, offsets, tile_cnt, tile_base, counts, tile_start, group, st),
+        "route"));
   return MITA_OK;
 }
 

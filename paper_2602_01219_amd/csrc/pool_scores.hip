@@ -18,7 +18,7 @@ namespace mita {
 template <typename T, int D>
 __global__ __launch_bounds__(256) void pool_kernel(const T *__restrict__ q, T *__restrict__ q_lm,
                                                    int32_t *__restrict__ zero_counts, int32_t *__restrict__ zero_cursor,
-                                                   int N, int gh, int gw, int lh, int lw) {
+                                                   int zn, int N, int gh, int gw, int lh, int lw) {
   constexpr int VE = 16 / (int)sizeof(T);
   constexpr int CPT = D / VE;   // chunks per token row
   constexpr int P = 256 / CPT;  // token slots
@@ -30,8 +30,8 @@ __global__ __launch_bounds__(256) void pool_kernel(const T *__restrict__ q, T *_
   const int r0 = (int)(((int64_t)a * gh) / lh), r1 = (int)(((int64_t)(a + 1) * gh + lh - 1) / lh);
   const int c0 = (int)(((int64_t)b * gw) / lw), c1 = (int)(((int64_t)(b + 1) * gw + lw - 1) / lw);
   const int cols = c1 - c0, count = (r1 - r0) * cols;
-  if (zero_counts && threadIdx.x == 0) zero_counts[bh * M + i] = 0;
-  if (zero_cursor && threadIdx.x == 0) zero_cursor[bh * M + i] = 0;
+  if (zero_counts && (int)threadIdx.x < zn) zero_counts[(bh * M + i) * zn + threadIdx.x] = 0;
+  if (zero_cursor && (int)threadIdx.x < zn) zero_cursor[(bh * M + i) * zn + threadIdx.x] = 0;
   const int ch = threadIdx.x % CPT, slot = threadIdx.x / CPT;
   float acc[VE];
 #pragma unroll
@@ -88,8 +88,8 @@ constexpr int SMALL_WINDOW = 32;
 template <typename T, int D>
 __global__ __launch_bounds__(256) void pool_small_kernel(const T *__restrict__ q, T *__restrict__ q_lm,
                                                          int32_t *__restrict__ zero_counts,
-                                                         int32_t *__restrict__ zero_cursor, int N, int gh, int gw,
-                                                         int lh, int lw, int64_t rows) {
+                                                         int32_t *__restrict__ zero_cursor, int zn, int N, int gh,
+                                                         int gw, int lh, int lw, int64_t rows) {
   constexpr int VE = 16 / (int)sizeof(T);
   constexpr int CPT = D / VE;  // chunks per token row
   constexpr int PS = 64 / CPT;  // token slots per wave
@@ -104,8 +104,8 @@ __global__ __launch_bounds__(256) void pool_small_kernel(const T *__restrict__ q
   const int r0 = (int)(((int64_t)a * gh) / lh), r1 = (int)(((int64_t)(a + 1) * gh + lh - 1) / lh);
   const int c0 = (int)(((int64_t)b * gw) / lw), c1 = (int)(((int64_t)(b + 1) * gw + lw - 1) / lw);
   const int cols = c1 - c0, count = (r1 - r0) * cols;
-  if (zero_counts && lane == 0) zero_counts[row] = 0;
-  if (zero_cursor && lane == 0) zero_cursor[row] = 0;
+  if (zero_counts && lane < zn) zero_counts[row * zn + lane] = 0;
+  if (zero_cursor && lane < zn) zero_cursor[row * zn + lane] = 0;
   const int ch = lane % CPT, slot = lane / CPT;
   float acc[VE];
 #pragma unroll
@@ -223,12 +223,12 @@ static hipError_t pool_t(const mita_cfg_t &c, const void *q, void *q_lm, int32_t
   if ((int64_t)wr * wc <= SMALL_WINDOW) {
     const int64_t rows = BH(c) * c.M;
     hipLaunchKernelGGL((pool_small_kernel<T, D>), dim3((unsigned)((rows + 3) / 4)), dim3(256), 0, st, (const T *)q,
-                       (T *)q_lm, zc, zcur, c.N, c.grid_h, c.grid_w, c.lm_h, c.lm_w, rows);
+                       (T *)q_lm, zc, zcur, route_groups(c) / c.M, c.N, c.grid_h, c.grid_w, c.lm_h, c.lm_w, rows);
     return launched("pool_small_kernel", st);
   }
   dim3 grid(c.M, (unsigned)BH(c));
-  hipLaunchKernelGGL((pool_kernel<T, D>), grid, dim3(256), 0, st, (const T *)q, (T *)q_lm, zc, zcur, c.N, c.grid_h,
-                     c.grid_w, c.lm_h, c.lm_w);
+  hipLaunchKernelGGL((pool_kernel<T, D>), grid, dim3(256), 0, st, (const T *)q, (T *)q_lm, zc, zcur,
+                     route_groups(c) / c.M, c.N, c.grid_h, c.grid_w, c.lm_h, c.lm_w);
   return launched("pool_kernel", st);
 }
 

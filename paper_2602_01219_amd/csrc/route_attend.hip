@@ -229,7 +229,8 @@ __global__ __launch_bounds__(BLOCK) void route_logits_kernel(const T *__restrict
 // four lane groups of a query column then merge their lists: S rounds, each
 // taking the best head among the four lists (the owner's list advances;
 // landmarks are distinct, so the owner is unique). Writes expert[n * S + j]
-// and the pair's group: expert for j = 0, M + expert otherwise.
+// and the pair's group: expert for j = 0, M + expert otherwise; with counts
+// (zeroed beforehand) also adds up the group sizes (cnt: 2 M words of LDS).
 // ---------------------------------------------------------------------------
 template <int S> struct TopS {
   float v[S];
@@ -268,11 +269,15 @@ template <int S> struct TopS {
 template <typename T, int D, int S>
 __global__ __launch_bounds__(BLOCK) void route_tops_kernel(const T *__restrict__ q, const T *__restrict__ q_lm,
                                                            int32_t *__restrict__ expert, int32_t *__restrict__ group,
-                                                           int N, int M, float scale, int ntq) {
+                                                           int32_t *__restrict__ counts, int N, int M, float scale,
+                                                           int ntq) {
   constexpr int VE = RouteLds<T, D>::VE;
   constexpr int LSTR = RouteLds<T, D>::LSTR;
   __shared__ __align__(16) T lms[RouteLds<T, D>::BYTES / sizeof(T)];
+  extern __shared__ uint32_t cnt[];
   const int64_t bh = blockIdx.y;
+  if (counts)
+    for (int i = threadIdx.x; i < 2 * M; i += BLOCK) cnt[i] = 0u;  // (M >= 1: a barrier follows before any use)
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 4, p = lane & 15;
   const int tile = blockIdx.x * 4 + w;
   Frag<T> qf[4][D / 32];
@@ -324,7 +329,6 @@ __global__ __launch_bounds__(BLOCK) void route_tops_kernel(const T *__restrict__
         }
     }
   }
-  if (tile >= ntq) return;  // no workgroup barriers below
 #pragma unroll
   for (int c = 0; c < 4; ++c) {
     const int n = tile * ROUTE_TQ + c * 16 + p;
@@ -346,12 +350,20 @@ __global__ __launch_bounds__(BLOCK) void route_tops_kernel(const T *__restrict__
         }
       }
       h += i == bi ? 1 : 0;
-      if (g == 0 && n < N) {
+      if (g == 0 && tile < ntq && n < N) {
         const int64_t at = (bh * N + n) * S + j;
+        const int gr = j == 0 ? bi : M + bi;
         expert[at] = bi;
-        group[at] = j == 0 ? bi : M + bi;
+        group[at] = gr;
+        if (counts) atomicAdd(&cnt[gr], 1u);
       }
     }
+  }
+  if (!counts) return;  // uniform
+  __syncthreads();
+  for (int i = threadIdx.x; i < 2 * M; i += BLOCK) {
+    const uint32_t x = cnt[i];
+    if (x) atomicAdd(&counts[bh * 2 * M + i], (int32_t)x);  // integer sums: order-independent
   }
 }
 
@@ -558,7 +570,9 @@ constexpr int SCATTER_TPW = 4;  // 64-query tiles per wave of the forward's scat
 // the tile's queries, one block of positions with one atomic add on that
 // expert's cursor (zeroed by the pooling) and places the queries there in
 // lane order. A workgroup covers 4 * SCATTER_TPW tiles.
-// pre: M + 1 words of LDS, wsum: 4 words.
+// pre: M + 1 words of LDS, wsum: 4 words. Up to 256 EPT groups (s > 1: N items
+// are the (query, rank) pairs, M their groups).
+template <int EPT>
 __device__ __forceinline__ void route_scatter_place_body(uint32_t *pre, uint32_t *wsum, int bx, int by,
                                                          const int32_t *__restrict__ expert,
                                                          const int32_t *__restrict__ counts,
@@ -566,7 +580,6 @@ __device__ __forceinline__ void route_scatter_place_body(uint32_t *pre, uint32_t
                                                          int32_t *__restrict__ offsets,
                                                          int32_t *__restrict__ tile_start, int N, int M, int ntiles,
                                                          int ebits) {
-  constexpr int EPT = (1024 + 255) / 256;  // experts per thread (M <= 1024)
   const int64_t bh = by;
   const int tid = threadIdx.x, lane = tid & 63;
   // the wave's queries (SCATTER_TPW tiles of 64) and their experts first:
@@ -833,7 +846,7 @@ template <typename T, int D, int CAP, bool VEC> struct TopkScatterLds {
   static constexpr int BYTES = A > B ? A : B;
 };
 
-template <typename T, int D, int CAP, bool VEC>
+template <typename T, int D, int CAP, bool VEC, bool MULTI>
 __global__ __launch_bounds__(256) void topk_scatter_kernel(const T *__restrict__ q_lm, const T *__restrict__ k,
                                                            float *__restrict__ S, float scale, int nchunks,
                                                            int32_t *__restrict__ idx, int kk,
@@ -843,8 +856,8 @@ __global__ __launch_bounds__(256) void topk_scatter_kernel(const T *__restrict__
                                                            const int32_t *__restrict__ counts,
                                                            int32_t *__restrict__ cursor, int32_t *__restrict__ perm,
                                                            int32_t *__restrict__ offsets,
-                                                           int32_t *__restrict__ tile_start, int N, int M, int ntiles,
-                                                           int ebits, int scat_x) {
+                                                           int32_t *__restrict__ tile_start, int N, int M, int NP,
+                                                           int G, int ntiles, int ebits, int scat_x) {
   __shared__ __align__(16) char buf[TopkScatterLds<T, D, CAP, VEC>::BYTES];
   const int b = (int)blockIdx.x;
   if (b < nT) {
@@ -867,8 +880,9 @@ __global__ __launch_bounds__(256) void topk_scatter_kernel(const T *__restrict__
   const int rb = b - nT;
   uint32_t *pre = reinterpret_cast<uint32_t *>(buf);
   __shared__ uint32_t wsum[4];
-  route_scatter_place_body(pre, wsum, rb % scat_x, rb / scat_x, expert, counts, cursor, perm, offsets, tile_start,
-                           N, M, ntiles, ebits);
+  static_assert(TopkScatterLds<T, D, CAP, VEC>::BYTES >= (2048 + 1) * 4, "the groups' offsets");
+  route_scatter_place_body<(MULTI ? 2048 : 1024) / 256>(pre, wsum, rb % scat_x, rb / scat_x, expert, counts, cursor,
+                                                        perm, offsets, tile_start, NP, G, ntiles, ebits);
 }
 
 // Attention work list: tile_start[e] = sum over e' < e of ceil(size(e') / 64),
@@ -1507,20 +1521,49 @@ static hipError_t route_t(const mita_cfg_t &c, const void *q, const void *q_lm, 
   return launched("route_scatter_kernel", st);
 }
 
-// s > 1: top-s logits, per-tile pair counts, then the stable scan and
-// scatter of route_t over the N s pairs and 2 M groups.
+// s > 1: the top-s logits (with the group sizes when counts is given).
+template <typename T, int D, int S>
+static hipError_t route_tops_t(const mita_cfg_t &c, const void *q, const void *q_lm, int32_t *expert, int32_t *group,
+                               int32_t *counts, hipStream_t st) {
+  const int ntq = (c.N + ROUTE_TQ - 1) / ROUTE_TQ;
+  hipLaunchKernelGGL((route_tops_kernel<T, D, S>), dim3((ntq + 3) / 4, (unsigned)BH(c)), dim3(BLOCK),
+                     counts ? 2 * (size_t)c.M * sizeof(uint32_t) : 0, st, (const T *)q, (const T *)q_lm, expert, group,
+                     counts, c.N, c.M, eff_scale(c), ntq);
+  return launched("route_tops_kernel", st);
+}
+
+template <typename T, int D>
+static hipError_t route_tops_s(const mita_cfg_t &c, const void *q, const void *q_lm, int32_t *expert, int32_t *group,
+                               int32_t *counts, hipStream_t st) {
+  static_assert(MITA_MAX_S == 4, "one instance per s");
+  switch (c.s) {
+    case 2: return route_tops_t<T, D, 2>(c, q, q_lm, expert, group, counts, st);
+    case 3: return route_tops_t<T, D, 3>(c, q, q_lm, expert, group, counts, st);
+    default: return route_tops_t<T, D, 4>(c, q, q_lm, expert, group, counts, st);
+  }
+}
+
+hipError_t launch_route_tops(const mita_cfg_t &c, const void *q, const void *q_lm, int32_t *expert, int32_t *group,
+                             int32_t *counts, hipStream_t st) {
+  if (!multi_route(c) || !counts) return hipErrorInvalidValue;
+  if (c.dtype == MITA_F32)
+    return c.d == 64 ? route_tops_s<float, 64>(c, q, q_lm, expert, group, counts, st)
+                     : route_tops_s<float, 128>(c, q, q_lm, expert, group, counts, st);
+  return c.d == 64 ? route_tops_s<bf16_t, 64>(c, q, q_lm, expert, group, counts, st)
+                   : route_tops_s<bf16_t, 128>(c, q, q_lm, expert, group, counts, st);
+}
+
+// The stage call's routing for s > 1: top-s logits, per-tile pair counts, then
+// the stable scan and scatter of route_t over the N s pairs and 2 M groups.
 template <typename T, int D, int S>
 static hipError_t route_multi_t(const mita_cfg_t &c, const void *q, const void *q_lm, int32_t *expert, int32_t *group,
                                 int32_t *perm, int32_t *offsets, int32_t *tile_cnt, int32_t *tile_base,
                                 int32_t *counts, int32_t *tile_start, hipStream_t st) {
   const int G = route_groups(c), NP = route_items(c), nt = route_tiles(c);
-  const int ntq = (c.N + ROUTE_TQ - 1) / ROUTE_TQ;
   const unsigned bh = (unsigned)BH(c);
   hipError_t err = launch_zero(counts, (int64_t)bh * G, st);
   if (err != hipSuccess) return err;
-  hipLaunchKernelGGL((route_tops_kernel<T, D, S>), dim3((ntq + 3) / 4, bh), dim3(BLOCK), 0, st, (const T *)q,
-                     (const T *)q_lm, expert, group, c.N, c.M, eff_scale(c), ntq);
-  if ((err = launched("route_tops_kernel", st)) != hipSuccess) return err;
+  if ((err = route_tops_t<T, D, S>(c, q, q_lm, expert, group, nullptr, st)) != hipSuccess) return err;
   hipLaunchKernelGGL(pair_count_kernel, dim3((nt + 3) / 4, bh), dim3(256), 4 * (size_t)G * sizeof(uint32_t), st, group,
                      tile_cnt, counts, NP, G, nt);
   if ((err = launched("pair_count_kernel", st)) != hipSuccess) return err;
@@ -1589,7 +1632,7 @@ hipError_t launch_pivots_logits(const mita_cfg_t &c, const void *q, const void *
 
 template <typename T, int D>
 static hipError_t place_t(const mita_cfg_t &c, const void *q_lm, const void *k, const SelectBufs &sb, float *S,
-                          int32_t *idx, const int32_t *expert, const int32_t *counts, int32_t *cursor, int32_t *perm,
+                          int32_t *idx, const int32_t *group, const int32_t *counts, int32_t *cursor, int32_t *perm,
                           int32_t *offsets, int32_t *tile_start, hipStream_t st) {
   const int nt = route_tiles(c), bh = (int)BH(c), nch = score_chunks(c);
   const int64_t rows = (int64_t)bh * c.M;
@@ -1599,32 +1642,41 @@ static hipError_t place_t(const mita_cfg_t &c, const void *q_lm, const void *k, 
   const int nT = (int)(rows < 64 ? rows : 64);
   const int scat_x = (nt + 4 * SCATTER_TPW - 1) / (4 * SCATTER_TPW);
   const int nS = scat_x * bh;
+  const int G = route_groups(c);
   int ebits = 0;
-  while ((1 << ebits) < c.M) ++ebits;
+  while ((1 << ebits) < G) ++ebits;
   constexpr int TCAP = 512;
-  if (c.N % 4 == 0)
-    hipLaunchKernelGGL((topk_scatter_kernel<T, D, TCAP, true>), dim3((unsigned)(nT + nS)), dim3(256), 0, st,
-                       (const T *)q_lm, (const T *)k, S, eff_scale(c), nch, idx, c.k, sb.fail_cnt, sb.fail_list, nT,
-                       expert, counts, cursor, perm, offsets, tile_start, c.N, c.M, nt, ebits, scat_x);
-  else
-    hipLaunchKernelGGL((topk_scatter_kernel<T, D, TCAP, false>), dim3((unsigned)(nT + nS)), dim3(256), 0, st,
-                       (const T *)q_lm, (const T *)k, S, eff_scale(c), nch, idx, c.k, sb.fail_cnt, sb.fail_list, nT,
-                       expert, counts, cursor, perm, offsets, tile_start, c.N, c.M, nt, ebits, scat_x);
+#define MITA_PLACE(VEC, MU)                                                                                          \
+  hipLaunchKernelGGL((topk_scatter_kernel<T, D, TCAP, VEC, MU>), dim3((unsigned)(nT + nS)), dim3(256), 0, st,        \
+                     (const T *)q_lm, (const T *)k, S, eff_scale(c), nch, idx, c.k, sb.fail_cnt, sb.fail_list, nT,  \
+                     group, counts, cursor, perm, offsets, tile_start, c.N, c.M, route_items(c), G, nt, ebits, scat_x)
+  if (multi_route(c)) {
+    if (c.N % 4 == 0)
+      MITA_PLACE(true, true);
+    else
+      MITA_PLACE(false, true);
+  } else if (c.N % 4 == 0) {
+    MITA_PLACE(true, false);
+  } else {
+    MITA_PLACE(false, false);
+  }
+#undef MITA_PLACE
   return launched("topk_scatter_kernel", st);
 }
 
 hipError_t launch_select_place(const mita_cfg_t &c, const void *q_lm, const void *k, const SelectBufs &sb, float *S,
-                               int32_t *idx, const void *partial, void *v_lm, const int32_t *expert,
+                               int32_t *idx, const void *partial, void *v_lm, const int32_t *group,
                                const int32_t *counts, int32_t *cursor, int32_t *perm, int32_t *offsets,
                                int32_t *tile_start, hipStream_t st) {
-  const hipError_t e = launch_select_finalize(c, sb, idx, partial, v_lm, st);
+  // (direct selection: the pivot launch wrote the sets, nothing is listed)
+  const hipError_t e = sb.idx ? hipSuccess : launch_select_finalize(c, sb, idx, partial, v_lm, st);
   if (e != hipSuccess) return e;
   if (c.dtype == MITA_F32)
     return c.d == 64
-               ? place_t<float, 64>(c, q_lm, k, sb, S, idx, expert, counts, cursor, perm, offsets, tile_start, st)
-               : place_t<float, 128>(c, q_lm, k, sb, S, idx, expert, counts, cursor, perm, offsets, tile_start, st);
-  return c.d == 64 ? place_t<bf16_t, 64>(c, q_lm, k, sb, S, idx, expert, counts, cursor, perm, offsets, tile_start, st)
-                   : place_t<bf16_t, 128>(c, q_lm, k, sb, S, idx, expert, counts, cursor, perm, offsets, tile_start, st);
+               ? place_t<float, 64>(c, q_lm, k, sb, S, idx, group, counts, cursor, perm, offsets, tile_start, st)
+               : place_t<float, 128>(c, q_lm, k, sb, S, idx, group, counts, cursor, perm, offsets, tile_start, st);
+  return c.d == 64 ? place_t<bf16_t, 64>(c, q_lm, k, sb, S, idx, group, counts, cursor, perm, offsets, tile_start, st)
+                   : place_t<bf16_t, 128>(c, q_lm, k, sb, S, idx, group, counts, cursor, perm, offsets, tile_start, st);
 }
 
 template <typename T, int D>
@@ -1637,7 +1689,10 @@ static hipError_t direct_t(const mita_cfg_t &c, const void *q, const void *q_lm,
   const dim3 grid((unsigned)(nSp + nV + bh));
   float2 *ml = (float2 *)partial;
   float *po = v_lm ? (float *)((char *)partial + align_up((size_t)bh * nch * c.M * sizeof(float2))) : nullptr;
-#define MITA_DIRECT(V)                                                                                                hipLaunchKernelGGL((direct_kernel<T, D, V>), grid, dim3(BLOCK), 0, st, (const T *)q, (const T *)q_lm, (const T *)k,                      (const T *)v, sb.plo, sb.fail_cnt, sb.idx, ml, po, (T *)v_lm, perm, offsets, tile_start, c.N,                         c.M, c.k, eff_scale(c), sample_x, nS, nSp, nV, nch)
+#define MITA_DIRECT(V)                                                                                               \
+  hipLaunchKernelGGL((direct_kernel<T, D, V>), grid, dim3(BLOCK), 0, st, (const T *)q, (const T *)q_lm, (const T *)k, \
+                     (const T *)v, sb.plo, sb.fail_cnt, sb.idx, ml, po, (T *)v_lm, perm, offsets, tile_start, c.N,    \
+                     c.M, c.k, eff_scale(c), sample_x, nS, nSp, nV, nch)
   if (v_lm)
     MITA_DIRECT(true);
   else
