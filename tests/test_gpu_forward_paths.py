@@ -1,0 +1,55 @@
+"""The forward's launches against its path over stored scores, at the sizes
+where a launch or a tile changes.
+
+The default forward selects from candidate lists or from scores held in
+registers, routes first and forms no sets for experts without queries; with
+full_scores every score is stored and every set selected from them. Scores, sets,
+routing and the order of every merge are the same on both, so outputs are equal
+bit for bit (tolerance 0); the stored path is checked against the oracle in
+test_gpu_parity.py.
+"""
+from __future__ import annotations
+
+import dataclasses
+
+import pytest
+import torch
+
+from paper_2602_01219_amd import mita, synth
+from tests.gpu_helpers import inputs_to_dev, log
+
+pytestmark = pytest.mark.gpu
+
+# N: one token; a part of a 64-token tile; each side of the direct launch's
+# register sizes (256, 512) and of its end (1024); lists finished by a wave
+# and (cap above 1024) by a workgroup. M: one landmark, each side of a
+# 16-landmark block and of 64, experts without queries (clusters < M).
+# (B, H) puts the pivots on each side of 64 sixteen-landmark blocks.
+# N, landmark rows and columns, k, d, s, dtype, B, H, clusters
+CASES = [
+    (1, 1, 1, 1, 64, 1, "f32", 1, 1, 1), (63, 1, 3, 5, 64, 1, "bf16", 1, 3, 3), (196, 4, 4, 196, 64, 1, "bf16", 2, 2, 9),
+    (255, 1, 16, 49, 128, 1, "bf16", 1, 2, 5), (256, 4, 4, 256, 64, 1, "f32", 1, 2, 4), (257, 1, 17, 100, 64, 1, "bf16", 2, 3, 6),
+    (512, 8, 8, 128, 64, 1, "bf16", 1, 3, 7), (513, 5, 13, 511, 128, 1, "f32", 1, 2, 5), (1023, 1, 33, 31, 64, 1, "f32", 1, 2, 8),
+    (1024, 8, 16, 128, 64, 1, "bf16", 4, 6, 16), (1025, 5, 5, 33, 64, 1, "bf16", 1, 3, 6), (1025, 5, 13, 64, 128, 1, "f32", 2, 9, 20),
+    (1600, 7, 7, 49, 64, 1, "bf16", 2, 16, 13), (4097, 8, 8, 500, 64, 1, "f32", 1, 2, 9), (4097, 8, 8, 257, 128, 1, "bf16", 2, 16, 9),
+    (1024, 8, 8, 64, 64, 2, "bf16", 2, 3, 9), (1025, 1, 17, 65, 128, 3, "f32", 1, 2, 5), (2500, 8, 8, 100, 64, 2, "bf16", 3, 6, 12),
+    (257, 4, 4, 16, 64, 4, "f32", 1, 2, 3), (16384, 4, 4, 512, 64, 1, "bf16", 1, 2, 6), (9000, 4, 5, 800, 128, 1, "bf16", 1, 2, 6),
+]
+
+
+@pytest.mark.parametrize("case", CASES, ids=["n%d_m%d_k%d_d%d_s%d_%s" % (c[0], c[1] * c[2], *c[3:7]) for c in CASES])
+def test_forward_equals_stored_scores(case):
+    N, lh, lw, k, d, s, dtype, B, H, clusters = case
+    g = next(g for g in range(int(N ** 0.5), 0, -1) if N % g == 0)
+    if lh > g:  # no such grid: 1-D landmarks
+        g, lh, lw = 1, 1, lh * lw
+    wl = synth.Workload(name="fwd_paths", B=B, H=H, grid_h=g, grid_w=N // g, d=d, lm_h=lh, lm_w=lw, k=k, dtype=dtype,
+                        clusters=clusters, std=0.5, cluster_map="iid", seed=N + k)
+    cfg = dataclasses.replace(mita.Config.from_workload(wl), s=s)
+    q, K, v = inputs_to_dev(synth.generate(wl))
+    K[:, :, N // 2:] = K[:, :, :N - N // 2].clone()  # every score twice: the cut falls between equal ones
+    ref = mita.forward(dataclasses.replace(cfg, full_scores=True), q, K, v)
+    for staged in (False, True):
+        o = mita.forward(dataclasses.replace(cfg, staged_gather=staged), q, K, v)
+        log(f"  staged {staged}: {int((o != ref).sum())} elements differ")
+        assert torch.isfinite(o).all() and torch.equal(o, ref)
