@@ -84,18 +84,17 @@ def kernel_work(name: str, wl, plan: dict, staged: bool, s: int = 1, launched=()
         "pool_kernel": (tens + lmt, 0),
         "sample_pivot_kernel": (BH * ns * d * e + lmt + 4 * rows + (4 * rows * k if ns == N else 0),
                                 2 * M * ns * d * BH),
-        "scores_kernel": (tens * (1 + sh) + lmt + 4 * BH * M * N * stored_s, 2 * M * N * d * BH * (1 + sh)),
+        # sampled scores with pivots, and the routing logits
+        "pivots_logits_kernel": (BH * ns * d * e + lmt + 4 * rows + tens + lmt + 4 * BH * N,
+                                 2 * M * ns * d * BH + 2 * N * M * d * BH),
+        # (direct selection, N <= 1024 and s = 1: this launch forms the sets,
+        # the landmark values and the routing)
+        "scores_kernel": (tens * (2 + sh) + lmt * (1 + sh) + 4 * rows * k + 4 * BH * N,
+                          2 * M * N * d * BH * (2 + sh))
+                         if ns == N and s == 1 and "route_logits_kernel" not in launched else
+                         (tens * (1 + sh) + lmt + 4 * BH * M * N * stored_s, 2 * M * N * d * BH * (1 + sh)),
         "merge_kernel": (BH * nch * M * (d + 2) * 4 + lmt, 0),
         "finalize_kernel": (4 * rows * k + lmt * sh, 0),
-        # the routing logits run in the finish launch unless the pivot launch
-        # took them (sample_logits_kernel)
-        # (with the sample the whole row, N <= 1024, the sample launch writes the
-        # sets and the finish launch forms the routing logits only)
-        "finalize_logits_kernel": (4 * rows * k + lmt * sh, 0) if "sample_logits_kernel" in launched else
-                                  ((tens + lmt + 4 * BH * N, 2 * N * M * d * BH) if ns == N else
-                                   (4 * rows * k + lmt * sh + tens + lmt + 4 * BH * N, 2 * N * M * d * BH)),
-        "sample_logits_kernel": (BH * ns * d * e + lmt + 4 * rows + tens + lmt + 4 * BH * N,
-                                 2 * M * ns * d * BH + 2 * N * M * d * BH),
         "topk_scatter_kernel": (8 * BH * N + 8 * BH * (M + 1), 0),
         "scores_rows_kernel": (0, 0),
         "topk_kernel": (4 * BH * M * N + 4 * rows * k, 0),
@@ -138,12 +137,13 @@ def kernel_work(name: str, wl, plan: dict, staged: bool, s: int = 1, launched=()
         w["bwd_kv_landmark_kernel"] = (2 * tens + 2 * lmt + 8 * rows
                                        + (8 * BH * M * k * d + 4 * BH * M * k + 4 * BH * N) * rt + 2 * tens,
                                        8 * M * N * d * BH * sh)
-        w["lmv_prep_kernel"] = (4 * BH * M * d + 2 * lmt + 4 * rows, 0)
     # (bf16 with the landmark values: dk, dv come from the landmark-value
     # key pass, the finish forms dq only)
     w["bwd_finish_kernel"] = ((4 * BH * N * d + 4 * BH * M * d + tens, 0) if "bwd_kv_landmark_kernel" in launched
                               else (12 * BH * N * d + 4 * BH * M * d * sh + 3 * tens, 0))
-    w["lse_rows_kernel"] = (8 * BH * nch * M + 4 * rows, 0)
+    # the landmark rows' gradients so far, the bf16 copy, log-sum-exps (its
+    # partial sums, this design's, are not counted)
+    w["bwd_prep_kernel"] = (8 * BH * M * d + 2 * lmt + 8 * BH * nch * M + 8 * rows, 0)
     w["scores16_kernel"] = w["scores_kernel"]
     w["pool_small_kernel"] = w["pool_kernel"]
     w["finalize_wave_kernel"] = w["finalize_kernel"]

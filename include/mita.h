@@ -310,8 +310,8 @@ int mita_attend(const mita_cfg_t *cfg, const void *q, const void *q_lm, const vo
  *        the io type (must not overlap the inputs or each other).
  *   ws : >= mita_workspace_size(cfg, MITA_WS_BACKWARD) bytes.
  * Requires s = 1 when use_routed is set (MITA_ERR_UNSUPPORTED otherwise). The
- * key-side gradients are summed with fp32 atomic adds, whose order varies:
- * dk, dv and dq are reproducible only to rounding, not bit for bit.
+ * order of some key-side sums varies (a token's experts; fp32 atomic adds in
+ * fp32): dk, dv and dq are reproducible only to rounding, not bit for bit.
  */
 int mita_backward(const mita_cfg_t *cfg, const void *q, const void *k, const void *v, const void *o,
                   const void *dO, void *dq, void *dk, void *dv, void *ws, size_t ws_bytes, mita_stream_t stream);
@@ -324,8 +324,8 @@ int mita_backward(const mita_cfg_t *cfg, const void *q, const void *k, const voi
  * so the interval of a launch is that kernel's time on the stream. Every
  * launch belongs to one of MITA_NUM_STAGES stages (0 landmarks, 1 scores,
  * 2 top-k, 3 gather, 4 routing, 5 attention); a kernel that does the work of
- * two stages (the forward's selection finish runs inside the routing
- * launches) counts under the later one, and a stage that launches nothing
+ * two stages (the forward's routing logits run inside the selection's
+ * launches) counts under one of them, and a stage that launches nothing
  * takes no time.
  */
 #define MITA_NUM_STAGES 6

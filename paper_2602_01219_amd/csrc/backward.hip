@@ -4,7 +4,9 @@
 // landmark-value (itself an attention of the landmark queries over all keys)
 // and the pooling of the landmark queries.
 //
-// Both attentions take the same kernel, bwd_kernel, in one of two modes:
+// bf16 takes the DMA-tiled kernels: bwd_att16_kernel (dQ, and the landmark
+// queries' gradient) below and the key passes of backward_keys.hpp. fp32, and
+// the dQ of bf16 row lists too long for LDS, take bwd_kernel in one of two modes:
 //   ATT: a workgroup takes one tile of the forward's work list (64 queries
 //        of one expert); its keys are the shared landmarks (keys q_lm,
 //        values v_lm) and the expert's k routed rows. A first pass over the
@@ -26,17 +28,19 @@
 // elements: Q and dO row-major (and, for bf16 at d = 64, transposed; else
 // their columns are read element by element), the key tile row-major and
 // transposed, P and dZ as [key][query] and dZ as [query][key].
-// The keys' gradients of the MiTA attention come from bwd_kv_kernel, where a
-// workgroup owns 64 keys and streams the queries that attend them, so that
-// dK and dV stay in registers: a routed key block of one expert sees that
-// expert's queries (the per-expert sums are staged and then summed per token
-// through an inverse index of the top-k sets); a block of shared keys sees a
-// chunk of all queries (few atomic adds per chunk). fp32 atomic adds retire at
-// a few hundred G/s on the whole chip, so a design that adds every 64-query
-// tile's key gradients atomically is bound by them.
-// The landmark queries' gradient and the landmark-value backward use atomic
-// adds whose order varies from run to run, so dq, dk, dv are reproducible
-// only to rounding (a few ulp), not bit for bit.
+// The keys' gradients of the MiTA attention come from key-owned kernels
+// (bwd_kv_kernel in fp32), where a workgroup owns a block of keys and streams
+// the queries that attend them, so that dK and dV stay in registers: a routed
+// key block of one expert sees that expert's queries (the per-expert sums are
+// staged and then summed per token through an inverse index of the top-k sets);
+// a block of shared keys sees a chunk of all queries and writes its partial
+// sums, which bwd_prep_kernel adds up. fp32 atomic adds retire at a few hundred
+// G/s on the whole chip, and many chunks adding to the same rows at less, so a
+// design that adds every tile's key gradients atomically is bound by them.
+// The order of a token's slots in the inverse index, and with it the order of
+// its staged rows, varies from run to run (as do the atomic adds of the fp32
+// landmark-value backward), so dq, dk, dv are reproducible only to rounding (a
+// few ulp), not bit for bit.
 #include "backward_keys.hpp"
 #include "cdna4.hpp"
 #include "check.hpp"

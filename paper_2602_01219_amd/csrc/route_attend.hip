@@ -667,13 +667,11 @@ __global__ __launch_bounds__(256) void route_scatter_kernel(const int32_t *__res
 // 78 us at 256 heads of 2048 tokens, M = 128).
 // ---------------------------------------------------------------------------
 template <typename T, int D>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 2 ? 3 : 2))) void pivots_logits_kernel(const T *__restrict__ q_lm, const T *__restrict__ k,
-                                                              uint32_t *__restrict__ plo,
-                                                              uint32_t *__restrict__ fail_cnt, int r, bool rows4,
-                                                              int sample_x, int nS, int nSp, const T *__restrict__ q,
-                                                              int32_t *__restrict__ expert,
-                                                              int32_t *__restrict__ counts, int N, int M, float scale,
-                                                              int ntiles, int route_x) {
+__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 2 ? 3 : 2)))
+void pivots_logits_kernel(const T *__restrict__ q_lm, const T *__restrict__ k, uint32_t *__restrict__ plo,
+                          uint32_t *__restrict__ fail_cnt, int r, bool rows4, int sample_x, int nS, int nSp,
+                          const T *__restrict__ q, int32_t *__restrict__ expert, int32_t *__restrict__ counts, int N,
+                          int M, float scale, int ntiles, int route_x) {
   constexpr int BYTES = (int)sizeof(PivotLds) > RouteLds<T, D>::BYTES ? (int)sizeof(PivotLds) : RouteLds<T, D>::BYTES;
   static_assert(BYTES >= SP_BYTES, "either pivot body fits");
   __shared__ __align__(16) char buf[BYTES];

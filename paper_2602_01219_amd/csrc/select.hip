@@ -1,24 +1,26 @@
 // select.hip - the top-k selection of the forward (Eq. top-k), fused with the
 // landmark-key score pass so that the M x N score matrix is never stored.
 //
-//   1-2. sample_pivot_kernel: the scores of every landmark against ns evenly
-//      spaced keys, as order-preserving keys (the same tile arithmetic as the
-//      score pass, so the same values), kept in LDS; per landmark row, the
-//      pivot = the r-th largest sampled key. r is chosen on the host so that
-//      at least k and far fewer than `cap` tokens of the row score >= pivot,
-//      except with negligible probability (r = k exactly when the sample is
-//      the whole row).
+//   1-2. the sampled scores and pivots (sample.hpp; in the forward's one-expert
+//      path beside the routing logits, pivots_logits_kernel): the scores of
+//      every landmark against ns evenly spaced keys, as order-preserving keys
+//      (the same tile arithmetic as the score pass, so the same values); per
+//      landmark row, the pivot = the r-th largest sampled key. r is chosen on
+//      the host so that at least k and far fewer than `cap` tokens of the row
+//      score >= pivot, except with negligible probability (r = k exactly when
+//      the sample is the whole row).
 //   3. the score pass lists every token scoring >= pivot (bits of its
 //      unscaled dot, token index), in token order, in one region per (row,
 //      key chunk); the finish scales the dots as every score is scaled.
 //   4. finalize_kernel: with k <= count <= cap the list holds the row's whole
 //      top-k, since every token left out scores below the pivot, which the
-//      k-th listed score reaches. The row's regions are packed into LDS, an
-//      exact radix select over the composite (score key, -index) finds the
-//      k-th token of the order (larger score first, lower index first among
-//      equal scores), and an ordered scan writes the selected indices, which
-//      the list already holds in ascending order. A row whose count is out of
-//      range goes to a fallback list.
+//      k-th listed score reaches. The row's regions are packed into LDS, the
+//      k-th largest key is found exactly, and an ordered scan writes the
+//      tokens above it and the first ones equal to it, as many as the set still
+//      needs; the list is already in ascending token order. A row whose count
+//      is out of range goes to a fallback list. Where the routing came first,
+//      rows of experts without queries are only counted, not stored or
+//      selected: nothing reads their sets.
 //   5. fallback rows: the score pass recomputes the full score row and the
 //      exact top-k kernel selects from it.
 // The sets equal those of the exact top-k over the stored score rows.
