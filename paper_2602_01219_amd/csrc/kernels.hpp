@@ -52,6 +52,16 @@ struct SelectBufs {
 hipError_t launch_scores(const mita_cfg_t &c, const void *q_lm, const void *k, const void *v, float *scores,
                          void *v_lm, void *partial, const SelectBufs *sel, hipStream_t st);
 
+// Direct selection (N <= SEL_NS), few enough scores that latency counts: four rows per workgroup and, at s = 1,
+// one launch for scores, sets and routing; else sixteen rows, which read the keys a quarter as often, and a
+// launch for each part. The line is BH M N^2 (d / 64)^2 (the rows' products, times the length of one row's
+// chain): 24 heads of 1024 tokens, M = 64, d = 64 (1.6e9) 42.5 us against 53.9, 96 heads of 784, M = 49 (2.9e9)
+// 72.9 against 73.1, 96 of 1024, M = 49 (4.9e9) 80.3 against 78.2, 512 of 1024, M = 128 (7e10) 657 against 533;
+// d = 128: 24 heads of 512, M = 64 (1.6e9) 48.6 against 58.6, 24 of 784, M = 49 (2.9e9) 67.1 against 64.5.
+inline bool few_rows(const mita_cfg_t &c) {
+  return (double)c.B * c.H * c.M * c.N * c.N * (c.d / 64) * (c.d / 64) <= 2.5e9;
+}
+
 // Fused selection, before the score pass: sampled scores, per-row pivots;
 // zeroes the candidate and fallback counters.
 hipError_t launch_select_pivots(const mita_cfg_t &c, const void *q_lm, const void *k, const SelectBufs &sel,
@@ -93,7 +103,7 @@ hipError_t launch_route(const mita_cfg_t &c, const void *q, const void *q_lm, in
 
 // The sampled scores and pivots (launch_select_pivots) and the routing
 // logits (expert [BH,N] and counts [BH,M], which must be zero on entry) in one
-// launch.
+// launch; with sel.idx (the sample is the whole row) the logits alone.
 hipError_t launch_pivots_logits(const mita_cfg_t &c, const void *q, const void *q_lm, const void *k,
                                 const SelectBufs &sel, int32_t *expert, int32_t *counts, hipStream_t st);
 

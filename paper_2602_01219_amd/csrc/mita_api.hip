@@ -134,7 +134,7 @@ int enqueue_experts(const mita_cfg_t *c, const void *q, const void *k, const voi
   // tile_base buffer) start at zero
   const bool multi = multi_route(*c);
   const bool combined = fused && !staged;
-  const bool one = combined && direct && !multi;  // everything before the attention in one launch
+  const bool one = combined && direct && !multi && few_rows(*c);  // everything before the attention in one launch
   int32_t *group = multi ? (int32_t *)(w + L.group) : nullptr;
   const int64_t groups = BH(*c) * route_groups(*c);
   int32_t *zero_counts = c->use_routed && !one && (combined || !multi) ? counts : nullptr;
@@ -164,7 +164,7 @@ int enqueue_experts(const mita_cfg_t *c, const void *q, const void *k, const voi
   rec.stage = 1;
   if (combined && !multi)
     TRY(hip_status(launch_pivots_logits(*c, q, q_lm, k, sel, expert, counts, st), "select pivots"));
-  else if (fused)
+  if (fused && (multi || staged || direct))
     TRY(hip_status(launch_select_pivots(*c, q_lm, k, sel, st), "select pivots"));
   // (direct selection: the score pass forms the landmark values only)
   TRY(hip_status(launch_scores(*c, q_lm, k, v, fused ? nullptr : S, v_lm, w + L.partial,

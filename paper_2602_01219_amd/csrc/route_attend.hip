@@ -238,7 +238,8 @@ __device__ __forceinline__ void route_logits_body(T *lms, uint32_t *cnt, int bx,
   }
 }
 
-template <typename T, int D>
+// TILES: the tiles' counts are kept for the stable placement.
+template <typename T, int D, bool TILES>
 __global__ __launch_bounds__(BLOCK) void route_logits_kernel(const T *__restrict__ q, const T *__restrict__ q_lm,
                                                              int32_t *__restrict__ expert,
                                                              int32_t *__restrict__ tile_cnt,
@@ -246,8 +247,8 @@ __global__ __launch_bounds__(BLOCK) void route_logits_kernel(const T *__restrict
                                                              float scale, int ntiles) {
   __shared__ __align__(16) T lms[RouteLds<T, D>::BYTES / sizeof(T)];
   extern __shared__ uint32_t cnt[];  // [4][M]
-  route_logits_body<T, D>(lms, cnt, (int)blockIdx.x, (int)blockIdx.y, q, q_lm, expert, tile_cnt, counts, N, M, scale,
-                          ntiles);
+  route_logits_body<T, D, TILES>(lms, cnt, (int)blockIdx.x, (int)blockIdx.y, q, q_lm, expert, tile_cnt, counts, N, M,
+                                 scale, ntiles);
 }
 
 // ---------------------------------------------------------------------------
@@ -1534,7 +1535,7 @@ static hipError_t route_t(const mita_cfg_t &c, const void *q, const void *q_lm, 
                           int32_t *tile_start, hipStream_t st) {
   const int nt = route_tiles(c);
   const unsigned bh = (unsigned)BH(c);
-  hipLaunchKernelGGL((route_logits_kernel<T, D>), dim3((nt + 3) / 4, bh), dim3(BLOCK), 4 * c.M * sizeof(uint32_t),
+  hipLaunchKernelGGL((route_logits_kernel<T, D, true>), dim3((nt + 3) / 4, bh), dim3(BLOCK), 4 * c.M * sizeof(uint32_t),
                      st, (const T *)q, (const T *)q_lm, expert, tile_cnt, counts, c.N, c.M, eff_scale(c), nt);
   hipError_t err = launched("route_logits_kernel", st);
   if (err != hipSuccess) return err;
@@ -1641,6 +1642,12 @@ static hipError_t pivots_logits_t(const mita_cfg_t &c, const void *q, const void
   const int sample_x = rows4 ? (c.M + SP_ROWS - 1) / SP_ROWS : (c.M + 15) / 16;
   const int nS = sample_x * bh, nSp = NXCD * ((nS + NXCD - 1) / NXCD);
   const int nt = route_tiles(c), route_x = (nt + 3) / 4;
+  if (sb.idx) {  // direct selection: the sets have a launch of their own
+    hipLaunchKernelGGL((route_logits_kernel<T, D, false>), dim3((unsigned)route_x, (unsigned)bh), dim3(BLOCK),
+                       4 * (size_t)c.M * sizeof(uint32_t), st, (const T *)q, (const T *)q_lm, expert,
+                       (int32_t *)nullptr, counts, c.N, c.M, eff_scale(c), nt);
+    return launched("route_logits_kernel", st);
+  }
   hipLaunchKernelGGL((pivots_logits_kernel<T, D>), dim3((unsigned)(nSp + route_x * bh)), dim3(BLOCK),
                      4 * (size_t)c.M * sizeof(uint32_t), st, (const T *)q_lm, (const T *)k, sb.plo, sb.fail_cnt, sb.rank,
                      rows4, sample_x, nS, nSp, (const T *)q, expert, counts, c.N, c.M, eff_scale(c), nt, route_x);
@@ -1649,7 +1656,7 @@ static hipError_t pivots_logits_t(const mita_cfg_t &c, const void *q, const void
 
 hipError_t launch_pivots_logits(const mita_cfg_t &c, const void *q, const void *q_lm, const void *k,
                                 const SelectBufs &sb, int32_t *expert, int32_t *counts, hipStream_t st) {
-  if (sb.ns != SEL_NS || sb.idx) return hipErrorInvalidValue;
+  if (sb.idx ? sb.ns != c.N : sb.ns != SEL_NS) return hipErrorInvalidValue;
   if (c.dtype == MITA_F32)
     return c.d == 64 ? pivots_logits_t<float, 64>(c, q, q_lm, k, sb, expert, counts, st)
                      : pivots_logits_t<float, 128>(c, q, q_lm, k, sb, expert, counts, st);

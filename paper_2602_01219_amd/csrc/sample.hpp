@@ -9,6 +9,7 @@
 #include "cdna4.hpp"
 #include "flash.hpp"
 #include "check.hpp"
+#include "scores.hpp"
 
 namespace mita {
 
@@ -155,20 +156,21 @@ constexpr int SP_ROWS = 4;            // landmark rows per workgroup
 constexpr int SP_PITCH = SEL_NS + 4;  // keys per LDS row: rows start 4 banks apart
 constexpr int SP_BYTES = SP_ROWS * SP_PITCH * 4;
 
-// Workgroup (bx, by) of the sample grid (landmarks 4 bx .. of head by); keys:
-// SP_ROWS LDS rows of SP_PITCH words.
+// Workgroup (bx, by) of the sample grid (landmarks ROWS bx .. of head by; ROWS waves,
+// a row each); keys: ROWS LDS rows of SP_PITCH words.
 // SETS (the sample is the whole row, ns == N, and r == kk): the rows' top-kk
 // sets are written too, in ascending token order: every key above the pivot
 // and, in token order, as many keys equal to it as the set still needs (the
 // order of the top-k: larger score first, lower index first among equal
-// scores).
-template <typename T, int D, bool SETS>
+// scores); rows that are not live are left out.
+template <typename T, int D, bool SETS, int ROWS = SP_ROWS>
 __device__ __forceinline__ void sample_pivot_body(uint32_t (*keys)[SP_PITCH], int bx, int by,
                                                   const T *__restrict__ q_lm, const T *__restrict__ k,
                                                   uint32_t *__restrict__ plo, uint32_t *__restrict__ fail_cnt, int N,
-                                                  int M, int ns, int r, float scale, int32_t *__restrict__ idx, int kk) {
+                                                  int M, int ns, int r, float scale, int32_t *__restrict__ idx, int kk,
+                                                  LiveRows live = LiveRows{}) {
   const int64_t bh = by;
-  const int lm0 = bx * SP_ROWS, lmb = lm0 & ~15;  // the rows; their column block
+  const int lm0 = bx * ROWS, lmb = lm0 & ~15;  // the rows; their column block
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 4, p = lane & 15;
   if (bx == 0 && by == 0 && threadIdx.x == 0) *fail_cnt = 0;
   Frag<T> qf[D / 32];
@@ -199,7 +201,7 @@ __device__ __forceinline__ void sample_pivot_body(uint32_t (*keys)[SP_PITCH], in
       for (int ks = 0; ks < D / 32; ++ks) acc = mma(a[kb][ks], qf[ks], acc);
       // lane (g, p) holds samples j0 + 16 kb + 4 g + (0..3) of column p
       const int jb = j0 + kb * 16 + 4 * g;
-      if (row >= 0 && row < SP_ROWS) {
+      if (row >= 0 && row < ROWS) {
         uint32_t key[4];
 #pragma unroll
         for (int q = 0; q < 4; ++q) key[q] = jb + q < ns ? score_key(acc[q] * scale) : 0u;
@@ -207,29 +209,30 @@ __device__ __forceinline__ void sample_pivot_body(uint32_t (*keys)[SP_PITCH], in
       }
     }
   };
-  constexpr bool AHEAD = sizeof(T) == 2 && D == 64;  // (registers for two tiles' fragments)
+  constexpr bool AHEAD = sizeof(T) == 2 && D == 64 && ROWS == 4;  // (registers for two tiles' fragments)
   Frag<T> a[AHEAD ? 2 : 1][4][D / 32];
   const int j1 = min(ns, SEL_NS);
   if (AHEAD) {
     if (w * TK < j1) load(a[0], w * TK);
 #pragma unroll
-    for (int i = 0; i < SEL_NS / (4 * TK); ++i) {
-      const int j0 = (4 * i + w) * TK;
-      if (j0 + 4 * TK < j1) load(a[(i + 1) & 1], j0 + 4 * TK);
+    for (int i = 0; i < SEL_NS / (ROWS * TK); ++i) {
+      const int j0 = (ROWS * i + w) * TK;
+      if (j0 + ROWS * TK < j1) load(a[(i + 1) & 1], j0 + ROWS * TK);
       if (j0 < j1) use(a[i & 1], j0);
     }
   } else {
-    for (int j0 = w * TK; j0 < j1; j0 += 4 * TK) {
+    for (int j0 = w * TK; j0 < j1; j0 += ROWS * TK) {
       load(a[0], j0);
       use(a[0], j0);
     }
   }
   // slots past ns stay 0 (below every key) for the selection
-  for (int j = ns + (int)threadIdx.x; j < SEL_NS; j += 256)
+  for (int j = ns + (int)threadIdx.x; j < SEL_NS; j += 64 * ROWS)
 #pragma unroll
-    for (int q = 0; q < SP_ROWS; ++q) keys[q][j] = 0u;
+    for (int q = 0; q < ROWS; ++q) keys[q][j] = 0u;
   __syncthreads();
-  if (lm0 + w >= M) return;  // uniform for the wave; no workgroup barriers below
+  // uniform for the wave; no workgroup barriers below
+  if (lm0 + w >= M || (SETS && !live(bh, lm0 + w, M))) return;
   // lane l holds keys 4 l + 256 i + (0..3); rows of at most 256 or 512 samples
   // take fewer registers and steps
   auto row_pivot = [&](auto per_c) {

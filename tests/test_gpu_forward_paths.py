@@ -23,7 +23,8 @@ pytestmark = pytest.mark.gpu
 # N: one token; a part of a 64-token tile; each side of the direct launch's
 # register sizes (256, 512) and of its end (1024); lists finished by a wave
 # and (cap above 1024) by a workgroup. M: one landmark, each side of a
-# 16-landmark block and of 64, experts without queries (clusters < M).
+# 16-landmark block and of 64, experts without queries (clusters < M). The last
+# ones have too many scores for the direct launch.
 # (B, H) puts the pivots on each side of 64 sixteen-landmark blocks.
 # N, landmark rows and columns, k, d, s, dtype, B, H, clusters
 CASES = [
@@ -34,6 +35,8 @@ CASES = [
     (1600, 7, 7, 49, 64, 1, "bf16", 2, 16, 13), (4097, 8, 8, 500, 64, 1, "f32", 1, 2, 9), (4097, 8, 8, 257, 128, 1, "bf16", 2, 16, 9),
     (1024, 8, 8, 64, 64, 2, "bf16", 2, 3, 9), (1025, 1, 17, 65, 128, 3, "f32", 1, 2, 5), (2500, 8, 8, 100, 64, 2, "bf16", 3, 6, 12),
     (257, 4, 4, 16, 64, 4, "f32", 1, 2, 3), (16384, 4, 4, 512, 64, 1, "bf16", 1, 2, 6), (9000, 4, 5, 800, 128, 1, "bf16", 1, 2, 6),
+    (1000, 5, 10, 77, 64, 1, "f32", 4, 16, 9), (900, 1, 26, 900, 128, 1, "f32", 2, 16, 5), (1023, 3, 11, 64, 128, 2, "bf16", 2, 12, 5),
+    (1000, 7, 7, 49, 64, 1, "bf16", 8, 12, 11),
 ]
 
 
