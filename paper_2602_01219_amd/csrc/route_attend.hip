@@ -1234,8 +1234,18 @@ __global__ __launch_bounds__(BLOCK) void attend_kernel(const T *__restrict__ q, 
 // four waves per SIMD, whose LDS reads per MFMA are twice as many. Four waves
 // on one tile (128 queries, half the fetches) leave more waves without
 // queries: 1170 us there, and 95 -> 104 us at 16384 tokens, d = 64.
-constexpr int ATT16_GROUPS = 2;
-#define ATTEND16_OCCUPANCY __attribute__((amdgpu_waves_per_eu(D == 64 ? 4 : 2)))
+// d = 128 takes one group per wave and four waves where an expert has fewer than
+// 64 queries on average (most groups are empty, and two waves issue a tile's
+// loads more slowly than four: 49.4 against 53.9 us at 512 heads of 196 tokens,
+// M = 16; 70.4 against 73.4 at 16 heads of 4096, M = 256; with 128 queries 86.8
+// against 77.9 at 16 heads of 8192, M = 64), or where the row list leaves three
+// workgroups per CU (k = 2100: 101 against 112 us).
+static bool att16_two(const mita_cfg_t &c, int nlist) {
+  if (c.d == 64) return true;
+  const bool busy = !c.use_routed || route_items(c) >= (int64_t)ATT_TQ * route_groups(c);
+  return busy && 4 * (attend16_tiles_lds<128>() + 4 * (size_t)nlist) <= LDS_BYTES;
+}
+#define ATTEND16_OCCUPANCY __attribute__((amdgpu_waves_per_eu(D == 64 ? 4 : NG == 2 ? 2 : 4)))
 
 template <int D, bool SHARED, bool ROUTED, bool FUSED, bool MULTI, int NG>
 __global__ __launch_bounds__(256 / NG) ATTEND16_OCCUPANCY void attend16_kernel(
@@ -1770,12 +1780,17 @@ static hipError_t attend_t3(const mita_cfg_t &c, const void *q, const void *q_lm
     // bf16: lists of up to IDX_LDS_MAX - 1 rows (and the kernel's rerun flag)
     // beside the 16 / 32 KB DMA tiles
     if (list_in_lds(nlist + 1, attend16_tiles_lds<D>())) {
-      constexpr int NG = ATT16_GROUPS;
-      hipLaunchKernelGGL((attend16_kernel<D, SH, RT, FU, MU, NG>), grid, dim3(256 / NG),
-                         (size_t)(nlist + 1) * sizeof(int32_t),
-                         st, (const bf16_t *)q, (const bf16_t *)q_lm, (const bf16_t *)v_lm, (const bf16_t *)rk,
-                         (const bf16_t *)rv, idx, perm, offsets, tile_start, (bf16_t *)o, c.N, c.M, c.k, eff_scale(c), s,
-                         pair_o, pair_lse);
+      auto run = [&](auto ng) {
+        constexpr int NG = decltype(ng)::value;
+        hipLaunchKernelGGL((attend16_kernel<D, SH, RT, FU, MU, NG>), grid, dim3(256 / NG),
+                           (size_t)(nlist + 1) * sizeof(int32_t), st, (const bf16_t *)q, (const bf16_t *)q_lm,
+                           (const bf16_t *)v_lm, (const bf16_t *)rk, (const bf16_t *)rv, idx, perm, offsets, tile_start,
+                           (bf16_t *)o, c.N, c.M, c.k, eff_scale(c), s, pair_o, pair_lse);
+      };
+      if (att16_two(c, nlist + 1))
+        run(std::integral_constant<int, 2>{});
+      else if constexpr (D == 128)
+        run(std::integral_constant<int, 1>{});
       err = launched("attend16_kernel", st);
       done = true;
     }
