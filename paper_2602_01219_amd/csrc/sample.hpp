@@ -149,8 +149,9 @@ __device__ __forceinline__ uint32_t pivot_of(const uint32_t (&v)[P], uint32_t *l
 // row's keys once they are in registers (the wave's LDS accesses are in order).
 // Four workgroups score each column block: the products are cheap, and with
 // one row per wave and 16 KB of LDS the pivots run beside the routing (a
-// workgroup of 16 waves for all 16 rows held 66 KB). Workgroup (0, 0) also
-// zeroes the fallback counter.
+// workgroup of 16 waves for all 16 rows held 66 KB). Where rows are many and
+// nothing runs beside them (few_rows), ROWS = 16 waves and rows do read the keys
+// once per block. Workgroup (0, 0) also zeroes the fallback counter.
 // ---------------------------------------------------------------------------
 constexpr int SP_ROWS = 4;            // landmark rows per workgroup
 constexpr int SP_PITCH = SEL_NS + 4;  // keys per LDS row: rows start 4 banks apart
