@@ -1,4 +1,5 @@
 // route_attend.hip - routing of queries to landmarks and the MiTA attention.
+#include <algorithm>
 #include <climits>
 #include <type_traits>
 
@@ -864,53 +865,51 @@ __global__ __launch_bounds__(BLOCK) void direct_kernel(const T *__restrict__ q, 
                         tile_start, N, M, scale);
 }
 
-// Workgroups [0, nT) take the fallback rows: each scores its rows in full
-// with the score pass's own arithmetic (one key chunk at a time), then
-// selects their top-k from those rows (the barrier between orders the stores
-// before the reads: the waves of a workgroup share one L1); the rest scatter.
-template <typename T, int D, int CAP, bool VEC> struct TopkScatterLds {
+// Workgroups [0, nS) scatter; then all take the fallback rows, each scoring its
+// rows in full and selecting their top-k from those rows (the barrier between
+// orders the stores before the reads: the waves of a workgroup share one L1).
+// Normally no row is listed. Padded or repeated tokens list every row of a head:
+// 1536 rows of 16384 keys (12 heads) take 420 us here and 128 rows (one head)
+// 97; on 64 workgroups 2050 and 175, with the score pass's tiles in place of
+// score_row 4630 and 370. At least FALLBACK_WG workgroups (two per CU) therefore;
+// the scatter's own usually are, so that calls without such rows pay nothing (512
+// more that only exit cost them 1 us).
+constexpr int FALLBACK_WG = 512;
+template <int CAP> struct TopkScatterLds {
   static constexpr int A = (int)sizeof(TopkSmem<CAP>);
-  static constexpr int B = 2 * TileDims<T, D>::K_ELEMS * (int)sizeof(T);  // two K tiles
+  static constexpr int B = (2048 + 1) * 4;  // the groups' offsets
   static constexpr int BYTES = A > B ? A : B;
 };
 
 template <typename T, int D, int CAP, bool VEC, bool MULTI>
 __global__ __launch_bounds__(256) void topk_scatter_kernel(const T *__restrict__ q_lm, const T *__restrict__ k,
-                                                           float *__restrict__ S, float scale, int nchunks,
+                                                           float *__restrict__ S, float scale,
                                                            int32_t *__restrict__ idx, int kk,
                                                            const uint32_t *__restrict__ nrows,
-                                                           const int32_t *__restrict__ rows, int nT,
+                                                           const int32_t *__restrict__ rows, int nS,
                                                            const int32_t *__restrict__ expert,
                                                            const int32_t *__restrict__ counts,
                                                            int32_t *__restrict__ cursor, int32_t *__restrict__ perm,
                                                            int32_t *__restrict__ offsets,
                                                            int32_t *__restrict__ tile_start, int N, int M, int NP,
                                                            int G, int ntiles, int ebits, int scat_x) {
-  __shared__ __align__(16) char buf[TopkScatterLds<T, D, CAP, VEC>::BYTES];
+  __shared__ __align__(16) char buf[TopkScatterLds<CAP>::BYTES];
   const int b = (int)blockIdx.x;
-  if (b < nT) {
-    const uint32_t nr = *nrows;
-    const SelectArgs none{};
-    for (uint32_t f = (uint32_t)b; f < nr; f += (uint32_t)nT) {
-      const int row = rows[f];
-      const int lm = row % M;
-      for (int chunk = 0; chunk < nchunks; ++chunk) {
-        __syncthreads();  // the previous use of the LDS is done
-        score_chunk<T, D, true, false, false>(reinterpret_cast<T *>(buf), nullptr, q_lm, k, nullptr, S, nullptr,
-                                              nullptr, none, N, M, scale, chunk, nchunks, lm / 64, row / M, lm);
-      }
-      __syncthreads();  // the row's scores are stored and visible to the workgroup
-      topk_row<CAP, VEC, 0>(*reinterpret_cast<TopkSmem<CAP> *>(buf), nullptr, S + (int64_t)row * N,
-                            idx + (int64_t)row * kk, N, kk);
-    }
-    return;
+  const uint32_t nr = *nrows;
+  if (b < nS) {
+    uint32_t *pre = reinterpret_cast<uint32_t *>(buf);
+    __shared__ uint32_t wsum[4];
+    route_scatter_place_body<(MULTI ? 2048 : 1024) / 256>(pre, wsum, b % scat_x, b / scat_x, expert, counts, cursor,
+                                                          perm, offsets, tile_start, NP, G, ntiles, ebits);
   }
-  const int rb = b - nT;
-  uint32_t *pre = reinterpret_cast<uint32_t *>(buf);
-  __shared__ uint32_t wsum[4];
-  static_assert(TopkScatterLds<T, D, CAP, VEC>::BYTES >= (2048 + 1) * 4, "the groups' offsets");
-  route_scatter_place_body<(MULTI ? 2048 : 1024) / 256>(pre, wsum, rb % scat_x, rb / scat_x, expert, counts, cursor,
-                                                        perm, offsets, tile_start, NP, G, ntiles, ebits);
+  for (uint32_t f = (uint32_t)b; f < nr; f += gridDim.x) {
+    const int row = rows[f];
+    score_row<T, D>(q_lm, k, S, row / M, row % M, N, M, scale);
+    // the row's scores are stored and visible to the workgroup, the LDS is free
+    __syncthreads();
+    topk_row<CAP, VEC, 0>(*reinterpret_cast<TopkSmem<CAP> *>(buf), nullptr, S + (int64_t)row * N,
+                          idx + (int64_t)row * kk, N, kk);
+  }
 }
 
 // Attention work list: tile_start[e] = sum over e' < e of ceil(size(e') / 64),
@@ -1678,21 +1677,17 @@ template <typename T, int D>
 static hipError_t place_t(const mita_cfg_t &c, const void *q_lm, const void *k, const SelectBufs &sb, float *S,
                           int32_t *idx, const int32_t *group, const int32_t *counts, int32_t *cursor, int32_t *perm,
                           int32_t *offsets, int32_t *tile_start, hipStream_t st) {
-  const int nt = route_tiles(c), bh = (int)BH(c), nch = score_chunks(c);
+  const int nt = route_tiles(c), bh = (int)BH(c);
   const int64_t rows = (int64_t)bh * c.M;
-  // the fallback workgroups (listed rows, scored in full and selected)
-  // (few: the rows normally all pass and these workgroups exit at once; each
-  // takes rows b, b + nT, ... when some do not)
-  const int nT = (int)(rows < 64 ? rows : 64);
   const int scat_x = (nt + 4 * SCATTER_TPW - 1) / (4 * SCATTER_TPW);
-  const int nS = scat_x * bh;
+  const int nS = scat_x * bh, grid = std::max(nS, (int)std::min<int64_t>(rows, FALLBACK_WG));
   const int G = route_groups(c);
   int ebits = 0;
   while ((1 << ebits) < G) ++ebits;
   constexpr int TCAP = 512;
 #define MITA_PLACE(VEC, MU)                                                                                          \
-  hipLaunchKernelGGL((topk_scatter_kernel<T, D, TCAP, VEC, MU>), dim3((unsigned)(nT + nS)), dim3(256), 0, st,        \
-                     (const T *)q_lm, (const T *)k, S, eff_scale(c), nch, idx, c.k, sb.fail_cnt, sb.fail_list, nT,  \
+  hipLaunchKernelGGL((topk_scatter_kernel<T, D, TCAP, VEC, MU>), dim3((unsigned)grid), dim3(256), 0, st,             \
+                     (const T *)q_lm, (const T *)k, S, eff_scale(c), idx, c.k, sb.fail_cnt, sb.fail_list, nS,       \
                      group, counts, cursor, perm, offsets, tile_start, c.N, c.M, route_items(c), G, nt, ebits, scat_x)
   if (multi_route(c)) {
     if (c.N % 4 == 0)

@@ -252,6 +252,63 @@ __device__ __forceinline__ void score_chunk(T *__restrict__ Ks, T *__restrict__ 
   }
 }
 
+// The scores of one landmark row against all keys, by a 256-thread workgroup:
+// wave w takes every fourth 16 KB keys, the A fragments loaded straight from the
+// key rows with the next ones in flight, the row one of the 16 columns of its
+// MFMA block (the products of the score pass, so the same values). No LDS and no
+// barriers: a row of 16384 keys of 64 dims takes about a third of the time of
+// the score pass's tiles, whose 63 other landmarks nothing needs here.
+template <typename T, int D>
+__device__ __forceinline__ void score_row(const T *__restrict__ q_lm, const T *__restrict__ k, float *__restrict__ S,
+                                          int64_t bh, int lm, int N, int M, float scale) {
+  constexpr int KB = 512 / (int)(sizeof(T) * D);  // 16-key blocks per step: two steps take 64 registers
+  constexpr int STEP = 4 * 16 * KB;                 // keys per step of the workgroup
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 4, p = lane & 15;
+  const int col = lm & 15, lmb = lm - col;
+  Frag<T> qf[D / 32];
+#pragma unroll
+  for (int ks = 0; ks < D / 32; ++ks) {
+    if (lmb + p < M)
+      qf[ks].load(q_lm + (bh * M + lmb + p) * D + ks * 32 + g * 8);
+    else
+      qf[ks].zero();
+  }
+  const T *kb_ = k + bh * (int64_t)N * D;
+  float *s = S + (bh * M + lm) * (int64_t)N;
+  Frag<T> a[2][KB][D / 32];
+  auto load = [&](Frag<T>(&f)[KB][D / 32], int j0) {
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb) {
+      const int64_t n = min(j0 + 16 * kb + p, N - 1);  // (past the end: not stored)
+#pragma unroll
+      for (int ks = 0; ks < D / 32; ++ks) f[kb][ks].load(kb_ + n * D + ks * 32 + g * 8);
+    }
+  };
+  auto use = [&](const Frag<T>(&f)[KB][D / 32], int j0) {
+#pragma unroll
+    for (int kb = 0; kb < KB; ++kb) {
+      f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+      for (int ks = 0; ks < D / 32; ++ks) acc = mma(f[kb][ks], qf[ks], acc);
+      const int n = j0 + 16 * kb + 4 * g;
+      if (p == col) {
+#pragma unroll
+        for (int r = 0; r < 4; ++r)
+          if (n + r < N) s[n + r] = acc[r] * scale;
+      }
+    }
+  };
+  int j = w * 16 * KB;
+  if (j < N) load(a[0], j);
+  for (; j < N; j += 2 * STEP) {
+    if (j + STEP < N) load(a[1], j + STEP);
+    use(a[0], j);
+    if (j + STEP >= N) break;
+    if (j + 2 * STEP < N) load(a[0], j + 2 * STEP);
+    use(a[1], j + STEP);
+  }
+}
+
 // Score rows of listed landmark rows (fallback of the fused selection): work
 // item = (listed row, key chunk), taken by workgroup b of nb; each item
 // recomputes the row's 64-landmark block exactly as the score pass does and
