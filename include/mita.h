@@ -161,7 +161,10 @@ int mita_forward_noalloc(const mita_cfg_t *cfg, const void *q, const void *k, co
 /*
  * Diagnostic: the number of landmark rows whose top-k selection in the last
  * mita_forward on workspace ws fell back to recomputing the full score row
- * (0 when that forward stored the whole score matrix). Waits for `stream`.
+ * (0 when that forward stored the whole score matrix). Rows of experts without
+ * queries are counted too, but their sets, which nothing reads, are not formed
+ * (except with MITA_FLAG_STAGED_GATHER, which reads every set). Waits for
+ * `stream`.
  *   count : host pointer, output.
  */
 int mita_forward_fallbacks(const mita_cfg_t *cfg, const void *ws, size_t ws_bytes, int64_t *count,

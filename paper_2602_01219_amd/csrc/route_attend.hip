@@ -867,7 +867,8 @@ __global__ __launch_bounds__(BLOCK) void direct_kernel(const T *__restrict__ q, 
 
 // Workgroups [0, nS) scatter; then all take the fallback rows, each scoring its
 // rows in full and selecting their top-k from those rows (the barrier between
-// orders the stores before the reads: the waves of a workgroup share one L1).
+// orders the stores before the reads: the waves of a workgroup share one L1);
+// rows of experts without queries, whose sets nothing reads, are left out.
 // Normally no row is listed. Padded or repeated tokens list every row of a head:
 // 1536 rows of 16384 keys (12 heads) take 420 us here and 128 rows (one head)
 // 97; on 64 workgroups 2050 and 175, with the score pass's tiles in place of
@@ -904,6 +905,7 @@ __global__ __launch_bounds__(256) void topk_scatter_kernel(const T *__restrict__
   }
   for (uint32_t f = (uint32_t)b; f < nr; f += gridDim.x) {
     const int row = rows[f];
+    if (!LiveRows{counts, G}(row / M, row % M, M)) continue;  // uniform
     score_row<T, D>(q_lm, k, S, row / M, row % M, N, M, scale);
     // the row's scores are stored and visible to the workgroup, the LDS is free
     __syncthreads();

@@ -92,6 +92,28 @@ def test_backward(shape, kind):
         assert torch.isfinite(a.float()).all() and err <= (2.0 ** -8 if cfg.dtype == "bf16" else 1e-6), name
 
 
+@pytest.mark.parametrize("s", [1, 2])
+def test_rows_of_experts_without_queries_are_not_rescored(s):
+    """Every row falls back (zero keys in all heads) and is listed, but only
+    those of experts with queries are scored: the score rows of the others keep
+    the bits the workspace held on entry."""
+    cfg, (q, k, v) = _case((2048, 8, 16, 64, 64, "bf16", 2, 7), s)
+    K = torch.zeros_like(k)
+    ws = torch.full((mita.workspace_size(cfg),), 0xFF, dtype=torch.uint8, device="cuda")
+    o = mita.forward(cfg, q, K, v, ws=ws)
+    assert mita.forward_fallbacks(cfg, ws) == cfg.H * cfg.M
+    assert torch.equal(o, mita.forward(dataclasses.replace(cfg, full_scores=True), q, K, v))
+    # the workspace begins with q_lm, v_lm (bf16 [H, M, d], 256-byte aligned) and S (fp32 [H, M, N])
+    lm = cfg.H * cfg.M * cfg.d * 2
+    assert lm % 256 == 0
+    S = ws[2 * lm:2 * lm + cfg.H * cfg.M * cfg.N * 4].view(torch.int32).view(cfg.H, cfg.M, cfg.N)
+    expert = mita.route(cfg, q, mita.landmarks(cfg, q))[0].view(cfg.H, -1).long()
+    live = torch.zeros((cfg.H, cfg.M), dtype=torch.bool, device="cuda").scatter_(1, expert, True)
+    log(f"  {int(live.sum())} of {cfg.H * cfg.M} experts have queries")
+    assert 0 < int(live.sum()) < cfg.H * cfg.M
+    assert torch.equal((S != -1).all(-1), live) and torch.equal((S != -1).any(-1), live)
+
+
 def _us(f, n=5):
     f()
     best = float("inf")
