@@ -103,9 +103,13 @@ hipError_t launch_route(const mita_cfg_t &c, const void *q, const void *q_lm, in
 
 // The sampled scores and pivots (launch_select_pivots) and the routing
 // logits (expert [BH,N] and counts [BH,M], which must be zero on entry) in one
-// launch; with sel.idx (the sample is the whole row) the logits alone.
+// launch.
 hipError_t launch_pivots_logits(const mita_cfg_t &c, const void *q, const void *q_lm, const void *k,
                                 const SelectBufs &sel, int32_t *expert, int32_t *counts, hipStream_t st);
+
+// The routing logits alone.
+hipError_t launch_route_logits(const mita_cfg_t &c, const void *q, const void *q_lm, int32_t *expert, int32_t *counts,
+                               hipStream_t st);
 
 // The finish of the fused selection (launch_select_finish: top-k into idx,
 // fallback rows, landmark-value merge into v_lm when given), its fallback rows

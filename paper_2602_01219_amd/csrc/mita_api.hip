@@ -135,6 +135,13 @@ int enqueue_experts(const mita_cfg_t *c, const void *q, const void *k, const voi
   const bool multi = multi_route(*c);
   const bool combined = fused && !staged;
   const bool one = combined && direct && !multi && few_rows(*c);  // everything before the attention in one launch
+  // routing before the scores: the experts' sizes then spare the sets of experts
+  // without queries their candidate stores and their finish (the staged gather
+  // reads every set). Not in direct selection, where a set costs little (512
+  // heads of 1024 tokens, M = 49: the sets take 97 us either way) and the
+  // attention, right behind the routing, finds the queries in the last-level
+  // cache (100 against 96 us there).
+  const bool first = combined && !direct;
   int32_t *group = multi ? (int32_t *)(w + L.group) : nullptr;
   const int64_t groups = BH(*c) * route_groups(*c);
   int32_t *zero_counts = c->use_routed && !one && (combined || !multi) ? counts : nullptr;
@@ -151,18 +158,17 @@ int enqueue_experts(const mita_cfg_t *c, const void *q, const void *k, const voi
     return hip_status(launch_direct(*c, q, q_lm, k, v, sel, w + L.partial, v_lm, perm, offsets, tile_start, st),
                       "select and route");
   }
-  if (combined) {
-    // the experts' sizes are known before the scores: the sets of experts
-    // without queries are not formed (the staged gather reads every set)
+  auto route_tops = [&]() -> int {
+    rec.stage = 4;
+    return hip_status(launch_route_tops(*c, q, q_lm, expert, group, counts, st), "route");
+  };
+  if (first) {
     sel.live = counts;
     sel.live_groups = route_groups(*c);
-  }
-  if (combined && multi) {
-    rec.stage = 4;
-    TRY(hip_status(launch_route_tops(*c, q, q_lm, expert, group, counts, st), "route"));
+    if (multi) TRY(route_tops());
   }
   rec.stage = 1;
-  if (combined && !multi)
+  if (first && !multi)
     TRY(hip_status(launch_pivots_logits(*c, q, q_lm, k, sel, expert, counts, st), "select pivots"));
   if (fused && (multi || staged || direct))
     TRY(hip_status(launch_select_pivots(*c, q_lm, k, sel, st), "select pivots"));
@@ -170,6 +176,13 @@ int enqueue_experts(const mita_cfg_t *c, const void *q, const void *k, const voi
   TRY(hip_status(launch_scores(*c, q_lm, k, v, fused ? nullptr : S, v_lm, w + L.partial,
                                fused && !direct ? &sel : nullptr, st),
                  "scores"));
+  if (combined && direct) {
+    rec.stage = 4;
+    if (multi)
+      TRY(route_tops());
+    else
+      TRY(hip_status(launch_route_logits(*c, q, q_lm, expert, counts, st), "route"));
+  }
   rec.stage = 2;
   if (combined)
     TRY(hip_status(launch_select_place(*c, q_lm, k, sel, S, idx, w + L.partial, v_lm, multi ? group : expert, counts,

@@ -1653,12 +1653,6 @@ static hipError_t pivots_logits_t(const mita_cfg_t &c, const void *q, const void
   const int sample_x = rows4 ? (c.M + SP_ROWS - 1) / SP_ROWS : (c.M + 15) / 16;
   const int nS = sample_x * bh, nSp = NXCD * ((nS + NXCD - 1) / NXCD);
   const int nt = route_tiles(c), route_x = (nt + 3) / 4;
-  if (sb.idx) {  // direct selection: the sets have a launch of their own
-    hipLaunchKernelGGL((route_logits_kernel<T, D, false>), dim3((unsigned)route_x, (unsigned)bh), dim3(BLOCK),
-                       4 * (size_t)c.M * sizeof(uint32_t), st, (const T *)q, (const T *)q_lm, expert,
-                       (int32_t *)nullptr, counts, c.N, c.M, eff_scale(c), nt);
-    return launched("route_logits_kernel", st);
-  }
   hipLaunchKernelGGL((pivots_logits_kernel<T, D>), dim3((unsigned)(nSp + route_x * bh)), dim3(BLOCK),
                      4 * (size_t)c.M * sizeof(uint32_t), st, (const T *)q_lm, (const T *)k, sb.plo, sb.fail_cnt, sb.rank,
                      rows4, sample_x, nS, nSp, (const T *)q, expert, counts, c.N, c.M, eff_scale(c), nt, route_x);
@@ -1667,12 +1661,31 @@ static hipError_t pivots_logits_t(const mita_cfg_t &c, const void *q, const void
 
 hipError_t launch_pivots_logits(const mita_cfg_t &c, const void *q, const void *q_lm, const void *k,
                                 const SelectBufs &sb, int32_t *expert, int32_t *counts, hipStream_t st) {
-  if (sb.idx ? sb.ns != c.N : sb.ns != SEL_NS) return hipErrorInvalidValue;
+  if (sb.idx || sb.ns != SEL_NS) return hipErrorInvalidValue;
   if (c.dtype == MITA_F32)
     return c.d == 64 ? pivots_logits_t<float, 64>(c, q, q_lm, k, sb, expert, counts, st)
                      : pivots_logits_t<float, 128>(c, q, q_lm, k, sb, expert, counts, st);
   return c.d == 64 ? pivots_logits_t<bf16_t, 64>(c, q, q_lm, k, sb, expert, counts, st)
                    : pivots_logits_t<bf16_t, 128>(c, q, q_lm, k, sb, expert, counts, st);
+}
+
+template <typename T, int D>
+static hipError_t route_logits_t(const mita_cfg_t &c, const void *q, const void *q_lm, int32_t *expert, int32_t *counts,
+                                 hipStream_t st) {
+  const int nt = route_tiles(c);
+  hipLaunchKernelGGL((route_logits_kernel<T, D, false>), dim3((nt + 3) / 4, (unsigned)BH(c)), dim3(BLOCK),
+                     4 * (size_t)c.M * sizeof(uint32_t), st, (const T *)q, (const T *)q_lm, expert, (int32_t *)nullptr,
+                     counts, c.N, c.M, eff_scale(c), nt);
+  return launched("route_logits_kernel", st);
+}
+
+hipError_t launch_route_logits(const mita_cfg_t &c, const void *q, const void *q_lm, int32_t *expert, int32_t *counts,
+                               hipStream_t st) {
+  if (c.dtype == MITA_F32)
+    return c.d == 64 ? route_logits_t<float, 64>(c, q, q_lm, expert, counts, st)
+                     : route_logits_t<float, 128>(c, q, q_lm, expert, counts, st);
+  return c.d == 64 ? route_logits_t<bf16_t, 64>(c, q, q_lm, expert, counts, st)
+                   : route_logits_t<bf16_t, 128>(c, q, q_lm, expert, counts, st);
 }
 
 template <typename T, int D>
@@ -1682,7 +1695,8 @@ static hipError_t place_t(const mita_cfg_t &c, const void *q_lm, const void *k, 
   const int nt = route_tiles(c), bh = (int)BH(c);
   const int64_t rows = (int64_t)bh * c.M;
   const int scat_x = (nt + 4 * SCATTER_TPW - 1) / (4 * SCATTER_TPW);
-  const int nS = scat_x * bh, grid = std::max(nS, (int)std::min<int64_t>(rows, FALLBACK_WG));
+  // (direct selection lists no rows)
+  const int nS = scat_x * bh, grid = sb.idx ? nS : std::max(nS, (int)std::min<int64_t>(rows, FALLBACK_WG));
   const int G = route_groups(c);
   int ebits = 0;
   while ((1 << ebits) < G) ++ebits;

@@ -163,13 +163,13 @@ constexpr int SP_BYTES = SP_ROWS * SP_PITCH * 4;
 // sets are written too, in ascending token order: every key above the pivot
 // and, in token order, as many keys equal to it as the set still needs (the
 // order of the top-k: larger score first, lower index first among equal
-// scores); rows that are not live are left out.
+// scores).
 template <typename T, int D, bool SETS, int ROWS = SP_ROWS>
 __device__ __forceinline__ void sample_pivot_body(uint32_t (*keys)[SP_PITCH], int bx, int by,
                                                   const T *__restrict__ q_lm, const T *__restrict__ k,
                                                   uint32_t *__restrict__ plo, uint32_t *__restrict__ fail_cnt, int N,
-                                                  int M, int ns, int r, float scale, int32_t *__restrict__ idx, int kk,
-                                                  LiveRows live = LiveRows{}) {
+                                                  int M, int ns, int r, float scale, int32_t *__restrict__ idx,
+                                                  int kk) {
   const int64_t bh = by;
   const int lm0 = bx * ROWS, lmb = lm0 & ~15;  // the rows; their column block
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 4, p = lane & 15;
@@ -233,7 +233,7 @@ __device__ __forceinline__ void sample_pivot_body(uint32_t (*keys)[SP_PITCH], in
     for (int q = 0; q < ROWS; ++q) keys[q][j] = 0u;
   __syncthreads();
   // uniform for the wave; no workgroup barriers below
-  if (lm0 + w >= M || (SETS && !live(bh, lm0 + w, M))) return;
+  if (lm0 + w >= M) return;
   // lane l holds keys 4 l + 256 i + (0..3); rows of at most 256 or 512 samples
   // take fewer registers and steps
   auto row_pivot = [&](auto per_c) {

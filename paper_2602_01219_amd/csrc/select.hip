@@ -44,12 +44,12 @@ namespace mita {
 template <typename T, int D, int ROWS>
 __global__ __launch_bounds__(ROWS ? 64 * ROWS : 256) void sample_pivot_kernel(
     const T *__restrict__ q_lm, const T *__restrict__ k, uint32_t *__restrict__ plo, uint32_t *__restrict__ fail_cnt,
-    int N, int M, int r, float scale, int nbx, int nslots, int32_t *__restrict__ idx, LiveRows live) {
+    int N, int M, int r, float scale, int nbx, int nslots, int32_t *__restrict__ idx) {
   __shared__ __align__(16) std::conditional_t<ROWS != 0, uint32_t[ROWS ? ROWS : 1][SP_PITCH], PivotLds> sh;
   const int f = xcd_slot((int)blockIdx.x, (int)gridDim.x / NXCD);
   if (f >= nslots) return;  // the whole workgroup
   if constexpr (ROWS != 0)
-    sample_pivot_body<T, D, true, ROWS>(sh, f % nbx, f / nbx, q_lm, k, plo, fail_cnt, N, M, N, r, scale, idx, r, live);
+    sample_pivot_body<T, D, true, ROWS>(sh, f % nbx, f / nbx, q_lm, k, plo, fail_cnt, N, M, N, r, scale, idx, r);
   else
     pivots16_body<T, D>(sh, f % nbx, f / nbx, q_lm, k, plo, fail_cnt, N, M, r, scale);
 }
@@ -91,13 +91,12 @@ template <typename T, int D>
 static hipError_t sample_pivot_t(const mita_cfg_t &c, const void *q_lm, const void *k, const SelectBufs &sb,
                                  hipStream_t st) {
   constexpr int MANY = sizeof(T) == 2 ? 16 : 8;  // rows per workgroup (fp32 fragments need eight waves' registers)
-  const LiveRows live{sb.live, sb.live_groups};
 #define MITA_PIVOTS(ROWS, PER)                                                                                      \
   {                                                                                                                 \
     const int nbx = (c.M + PER - 1) / PER, nslots = nbx * (int)BH(c);                                               \
     hipLaunchKernelGGL((sample_pivot_kernel<T, D, ROWS>), dim3((unsigned)(NXCD * ((nslots + NXCD - 1) / NXCD))),    \
                        dim3(ROWS ? 64 * ROWS : 256), 0, st, (const T *)q_lm, (const T *)k, sb.plo, sb.fail_cnt, c.N, \
-                       c.M, sb.rank, eff_scale(c), nbx, nslots, sb.idx, live);                                      \
+                       c.M, sb.rank, eff_scale(c), nbx, nslots, sb.idx);                                            \
   }
   if (!sb.idx)
     MITA_PIVOTS(0, 16)

@@ -1,0 +1,49 @@
+"""The launches of a call, by the kernel names its timer records: which variant
+a size takes, at each side of the rules' lines. What the variants compute is
+tested elsewhere (test_gpu_forward_paths.py, test_gpu_parity.py)."""
+from __future__ import annotations
+
+import dataclasses
+
+import pytest
+import torch
+
+from paper_2602_01219_amd import mita
+
+pytestmark = pytest.mark.gpu
+
+
+def _launches(cfg, backward=False):
+    g = torch.Generator("cuda").manual_seed(3)
+    q, k, v = ((0.3 * torch.randn((cfg.B, cfg.H, cfg.N, cfg.d), device="cuda", generator=g)).to(cfg.torch_dtype)
+               for _ in range(3))
+    t = mita.Timer(1)
+    o = mita.forward(cfg, q, k, v, timer=None if backward else t)
+    if backward:
+        mita.backward(cfg, q, k, v, o, q, timer=t)
+    names = [n for n, _, _ in t.launches()[0]]
+    t.close()
+    return names
+
+
+def _cfg(H, N, M, k, **kw):
+    return mita.Config(B=1, H=H, N=N, d=kw.pop("d", 64), grid_h=1, grid_w=N, M=M, lm_h=1, lm_w=M, k=k, **kw)
+
+
+@pytest.mark.parametrize("s", [1, 2])
+@pytest.mark.parametrize("backward", [False, True])
+def test_direct_selection_routes_behind_the_scores(s, backward):
+    """N <= 1024 with more scores than the one-launch form takes: sets and
+    landmark values first, then the routing, the attention right behind it."""
+    if backward and s > 1:
+        pytest.skip("the backward has one expert per query")
+    names = _launches(_cfg(96, 1024, 49, 49, s=s), backward)
+    logits = "route_tops_kernel" if s > 1 else "route_logits_kernel"
+    assert names[1:6] == ["sample_pivot_kernel", "scores_kernel", "merge_kernel", logits, "topk_scatter_kernel"]
+
+
+@pytest.mark.parametrize("s", [1, 2])
+def test_listed_selection_routes_before_the_scores(s):
+    names = _launches(_cfg(4, 1025, 16, 49, s=s))
+    logits = names.index("route_tops_kernel" if s > 1 else "pivots_logits_kernel")
+    assert logits < names.index("scores_kernel") < names.index("topk_scatter_kernel")
