@@ -62,6 +62,22 @@ inline bool few_rows(const mita_cfg_t &c) {
   return (double)c.B * c.H * c.M * c.N * c.N * (c.d / 64) * (c.d / 64) <= 2.5e9;
 }
 
+// Pivots, by the blocks of 16 landmark rows. Below 64 blocks most CUs have none
+// and a row per wave is the shorter chain, though each wave scores a whole block
+// (launch without logits, d = 64: 12 against 14 us at 64 blocks, 16 against 14 at
+// 96; d = 128 15 against 18, 22 against 18).
+inline int64_t pivot_blocks(const mita_cfg_t &c) { return (c.M + 15) / 16 * ((int64_t)c.B * c.H); }
+inline bool few_pivots(const mita_cfg_t &c) { return pivot_blocks(c) <= 64; }
+// With the logits in the same launch: eight waves per workgroup where the chain
+// of a block counts, four where the logits do (bf16, d = 64, 4096 tokens, us with
+// eight and with four: 14.6 and 18.9 at 64 blocks, 16.5 and 18.7 at 96, 17.0 and
+// 19.8 at 128, 22.0 and 19.7 at 256; at 16384 tokens 23.5 and 24.3, 26.6 and 27.8,
+// 33.6 and 33.9, 56.4 and 48.9). Twice the bytes per row, half the blocks (d = 128,
+// 16384 tokens: 28.0 and 31.0 at 64, 35.6 and 33.8 at 96).
+inline bool pivots_wide(const mita_cfg_t &c) {
+  return pivot_blocks(c) * (c.d / 64) * (c.dtype == MITA_F32 ? 2 : 1) <= 128;
+}
+
 // Fused selection, before the score pass: sampled scores, per-row pivots;
 // zeroes the candidate and fallback counters.
 hipError_t launch_select_pivots(const mita_cfg_t &c, const void *q_lm, const void *k, const SelectBufs &sel,

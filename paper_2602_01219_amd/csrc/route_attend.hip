@@ -116,19 +116,20 @@ __device__ __forceinline__ int route_merge(float best, int arg) {
   return arg;
 }
 
-// Workgroup (bx, by) of the routing grid (4 waves, one 64-query tile
-// each); lms: RouteLds<T, D>::BYTES of LDS, cnt: 4 M words of LDS.
-template <typename T, int D, bool TILES = true>
+// Workgroup (bx, by) of the routing grid (NWV waves, one 64-query tile
+// each); lms: RouteLds<T, D>::BYTES of LDS, cnt: NWV M words of LDS.
+template <typename T, int D, bool TILES = true, int NWV = 4>
 __device__ __forceinline__ void route_logits_body(T *lms, uint32_t *cnt, int bx, int by, const T *__restrict__ q,
                                                   const T *__restrict__ q_lm, int32_t *__restrict__ expert,
                                                   int32_t *__restrict__ tile_cnt, int32_t *__restrict__ counts, int N,
                                                   int M, float scale, int ntiles) {
   constexpr int VE = RouteLds<T, D>::VE;
   constexpr int LSTR = RouteLds<T, D>::LSTR;
-  constexpr int NX = ROUTE_LB * (D / VE) / BLOCK;  // 16-byte landmark chunks per thread and step
+  constexpr int NTH = 64 * NWV;
+  constexpr int NX = ROUTE_LB * (D / VE) / NTH;  // 16-byte landmark chunks per thread and step
   const int64_t bh = by;
   const int w = threadIdx.x >> 6, lane = threadIdx.x & 63, g = lane >> 4, p = lane & 15;
-  const int tile = bx * 4 + w;
+  const int tile = bx * NWV + w;
   uint32_t *wc = cnt + w * M;
   for (int i = lane; i < M; i += 64) wc[i] = 0u;
   const T *lmb = q_lm + bh * (int64_t)M * D;
@@ -136,7 +137,7 @@ __device__ __forceinline__ void route_logits_body(T *lms, uint32_t *cnt, int bx,
   auto fetch = [&](int l0) {
 #pragma unroll
     for (int i = 0; i < NX; ++i) {
-      const int ch = (int)threadIdx.x + i * BLOCK, r = ch / (D / VE), cc = ch % (D / VE);
+      const int ch = (int)threadIdx.x + i * NTH, r = ch / (D / VE), cc = ch % (D / VE);
       x[i] = make_uint4(0, 0, 0, 0);
       if (l0 + r < M) x[i] = *reinterpret_cast<const uint4 *>(lmb + (int64_t)(l0 + r) * D + cc * VE);
     }
@@ -168,7 +169,7 @@ __device__ __forceinline__ void route_logits_body(T *lms, uint32_t *cnt, int bx,
     __syncthreads();
 #pragma unroll
     for (int i = 0; i < NX; ++i) {
-      const int ch = (int)threadIdx.x + i * BLOCK, r = ch / (D / VE), cc = ch % (D / VE);
+      const int ch = (int)threadIdx.x + i * NTH, r = ch / (D / VE), cc = ch % (D / VE);
       *reinterpret_cast<uint4 *>(lms + r * LSTR + cc * VE) = x[i];
     }
     __syncthreads();
@@ -694,34 +695,38 @@ __global__ __launch_bounds__(256) void route_scatter_kernel(const int32_t *__res
 // the selection, of experts without queries. Workgroups [0, nSp) take the nS
 // sample slots (spread over the XCDs by xcd_slot so that a head's blocks share
 // an L2; slots past nS exit), the rest the routing grid; LDS is one buffer that
-// either part lays out for itself. Three waves per SIMD (four spill: 84 against
-// 78 us at 256 heads of 2048 tokens, M = 128).
+// either part lays out for itself.
+// NWV = 4, many blocks of 16 landmark rows: three waves per SIMD (four spill: 84
+// against 78 us at 256 heads of 2048 tokens, M = 128). NWV = 8, few blocks
+// (pivots_wide): a block's chain of loads and histogram steps halves, and with
+// fewer still (few_pivots, by_rows) a wave takes one row.
 // ---------------------------------------------------------------------------
-template <typename T, int D>
-__global__ __launch_bounds__(BLOCK) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 2 ? 3 : 2)))
+template <typename T, int D, int NWV>
+__global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 2 : NWV == 8 ? 4 : 3)))
 void pivots_logits_kernel(const T *__restrict__ q_lm, const T *__restrict__ k, uint32_t *__restrict__ plo,
-                          uint32_t *__restrict__ fail_cnt, int r, bool rows4, int sample_x, int nS, int nSp,
+                          uint32_t *__restrict__ fail_cnt, int r, bool by_rows, int sample_x, int nS, int nSp,
                           const T *__restrict__ q, int32_t *__restrict__ expert, int32_t *__restrict__ counts, int N,
                           int M, float scale, int ntiles, int route_x) {
-  constexpr int BYTES = (int)sizeof(PivotLds) > RouteLds<T, D>::BYTES ? (int)sizeof(PivotLds) : RouteLds<T, D>::BYTES;
-  static_assert(BYTES >= SP_BYTES, "either pivot body fits");
+  constexpr int P = NWV == 8 ? 8 * SP_PITCH * 4 : (int)sizeof(PivotLds);
+  constexpr int BYTES = P > RouteLds<T, D>::BYTES ? P : RouteLds<T, D>::BYTES;
+  static_assert(BYTES >= (int)sizeof(PivotLds), "either pivot body fits");
   __shared__ __align__(16) char buf[BYTES];
-  extern __shared__ uint32_t cnt[];  // routing: [4][M]
+  extern __shared__ uint32_t cnt[];  // routing: [NWV][M]
   const int b = (int)blockIdx.x;
   if (b < nSp) {  // nSp = nS rounded up to whole XCD ranges (xcd_slot)
     const int f = xcd_slot(b, nSp / NXCD);
     if (f >= nS) return;
-    if (rows4)
-      sample_pivot_body<T, D, false>(reinterpret_cast<uint32_t(*)[SP_PITCH]>(buf), f % sample_x, f / sample_x, q_lm, k,
-                                     plo, fail_cnt, N, M, SEL_NS, r, scale, nullptr, 0);
+    if (NWV == 8 && by_rows)
+      sample_pivot_body<T, D, false, 8>(reinterpret_cast<uint32_t(*)[SP_PITCH]>(buf), f % sample_x, f / sample_x, q_lm,
+                                        k, plo, fail_cnt, N, M, SEL_NS, r, scale, nullptr, 0);
     else
-      pivots16_body<T, D>(*reinterpret_cast<PivotLds *>(buf), f % sample_x, f / sample_x, q_lm, k, plo, fail_cnt, N, M,
-                          r, scale);
+      pivots16_body<T, D, NWV>(*reinterpret_cast<PivotLds *>(buf), f % sample_x, f / sample_x, q_lm, k, plo, fail_cnt,
+                               N, M, r, scale);
     return;
   }
   const int i = b - nSp;
-  route_logits_body<T, D, false>(reinterpret_cast<T *>(buf), cnt, i % route_x, i / route_x, q, q_lm, expert, nullptr,
-                                 counts, N, M, scale, ntiles);
+  route_logits_body<T, D, false, NWV>(reinterpret_cast<T *>(buf), cnt, i % route_x, i / route_x, q, q_lm, expert,
+                                      nullptr, counts, N, M, scale, ntiles);
 }
 
 // ---------------------------------------------------------------------------
@@ -1648,14 +1653,22 @@ hipError_t launch_route(const mita_cfg_t &c, const void *q, const void *q_lm, in
 template <typename T, int D>
 static hipError_t pivots_logits_t(const mita_cfg_t &c, const void *q, const void *q_lm, const void *k,
                                   const SelectBufs &sb, int32_t *expert, int32_t *counts, hipStream_t st) {
-  const int bh = (int)BH(c);
-  const bool rows4 = (int64_t)(c.M + 15) / 16 * bh < PIVOT16_MIN;
-  const int sample_x = rows4 ? (c.M + SP_ROWS - 1) / SP_ROWS : (c.M + 15) / 16;
+  const int bh = (int)BH(c), nt = route_tiles(c);
+  const bool by_rows = few_pivots(c);
+  const int sample_x = by_rows ? (c.M + 7) / 8 : (c.M + 15) / 16;
   const int nS = sample_x * bh, nSp = NXCD * ((nS + NXCD - 1) / NXCD);
-  const int nt = route_tiles(c), route_x = (nt + 3) / 4;
-  hipLaunchKernelGGL((pivots_logits_kernel<T, D>), dim3((unsigned)(nSp + route_x * bh)), dim3(BLOCK),
-                     4 * (size_t)c.M * sizeof(uint32_t), st, (const T *)q_lm, (const T *)k, sb.plo, sb.fail_cnt, sb.rank,
-                     rows4, sample_x, nS, nSp, (const T *)q, expert, counts, c.N, c.M, eff_scale(c), nt, route_x);
+  auto run = [&](auto nwv_c) {
+    constexpr int NWV = decltype(nwv_c)::value;
+    const int route_x = (nt + NWV - 1) / NWV;
+    hipLaunchKernelGGL((pivots_logits_kernel<T, D, NWV>), dim3((unsigned)(nSp + route_x * bh)), dim3(64 * NWV),
+                       NWV * (size_t)c.M * sizeof(uint32_t), st, (const T *)q_lm, (const T *)k, sb.plo, sb.fail_cnt,
+                       sb.rank, by_rows, sample_x, nS, nSp, (const T *)q, expert, counts, c.N, c.M, eff_scale(c), nt,
+                       route_x);
+  };
+  if (pivots_wide(c))
+    run(std::integral_constant<int, 8>{});
+  else
+    run(std::integral_constant<int, 4>{});
   return launched("pivots_logits_kernel", st);
 }
 

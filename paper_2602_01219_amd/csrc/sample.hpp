@@ -139,19 +139,18 @@ __device__ __forceinline__ uint32_t pivot_of(const uint32_t (&v)[P], uint32_t *l
 }
 
 // ---------------------------------------------------------------------------
-// Sampled scores and pivots. Workgroup = 4 waves for 4 landmark rows of one
-// head: wave w scores the MFMA column block of 16 landmarks that holds them
-// against every fourth 64-key tile of the samples (the A fragments loaded
-// straight from the sampled key rows, the next tile's in flight; tile
-// arithmetic as in the score pass, so the same values) and keeps the four
+// Sampled scores and pivots. Workgroup = ROWS waves for ROWS landmark rows of
+// one head (4, 8 or 16): wave w scores the MFMA column block of 16 landmarks that
+// holds them against every ROWS-th 64-key tile of the samples (the A fragments
+// loaded straight from the sampled key rows, the next tile's in flight; tile
+// arithmetic as in the score pass, so the same values) and keeps the ROWS
 // rows' keys = score_key(fl(dot) * scale) in LDS; then wave w takes the pivot
 // of row w, its histogram and compaction slots in the first 384 words of its
 // row's keys once they are in registers (the wave's LDS accesses are in order).
-// Four workgroups score each column block: the products are cheap, and with
-// one row per wave and 16 KB of LDS the pivots run beside the routing (a
-// workgroup of 16 waves for all 16 rows held 66 KB). Where rows are many and
-// nothing runs beside them (few_rows), ROWS = 16 waves and rows do read the keys
-// once per block. Workgroup (0, 0) also zeroes the fallback counter.
+// Several workgroups score each column block: the products are cheap, and a row
+// per wave is the shortest chain. Where rows are many (few_rows), ROWS = 16 waves
+// and rows read the keys once per block. Workgroup (0, 0) also zeroes the fallback
+// counter.
 // ---------------------------------------------------------------------------
 constexpr int SP_ROWS = 4;            // landmark rows per workgroup
 constexpr int SP_PITCH = SEL_NS + 4;  // keys per LDS row: rows start 4 banks apart
@@ -210,7 +209,7 @@ __device__ __forceinline__ void sample_pivot_body(uint32_t (*keys)[SP_PITCH], in
       }
     }
   };
-  constexpr bool AHEAD = sizeof(T) == 2 && D == 64 && ROWS == 4;  // (registers for two tiles' fragments)
+  constexpr bool AHEAD = sizeof(T) == 2 && D == 64 && ROWS <= 8;  // (registers for two tiles' fragments)
   Frag<T> a[AHEAD ? 2 : 1][4][D / 32];
   const int j1 = min(ns, SEL_NS);
   if (AHEAD) {
@@ -280,26 +279,28 @@ __device__ __forceinline__ void sample_pivot_body(uint32_t (*keys)[SP_PITCH], in
 }
 
 // ---------------------------------------------------------------------------
-// The pivots alone, from SEL_NS samples of N > SEL_NS keys. Workgroup = 4 waves
-// for one MFMA column block of 16 landmark rows; wave w scores every fourth
+// The pivots alone, from SEL_NS samples of N > SEL_NS keys. Workgroup = NW waves
+// for one MFMA column block of 16 landmark rows; wave w scores every NW-th
 // 64-key tile, and the samples stay in registers as floats in key order (NaN
-// as -inf, -0 as +0): lane (g, p) of a wave holds 64 of row p. The exact r-th
+// as -inf, -0 as +0): lane (g, p) of a wave holds 256 / NW of row p. The exact r-th
 // largest of each row, by the steps of pivot_of over all 16 rows at once:
 // range, 256-bin histogram over it, the bin of rank r, that bin's few samples
 // ranked. Rows whose range is not finite or whose bin holds more than 64
 // samples bisect the 32 key bits over all samples instead.
 // The sampled keys are read once per 16 rows and the samples cross LDS only as
-// histogram counts: 21 KB per workgroup, so that the routing logits fit beside
-// it (16 rows of keys took 66 KB and 16 waves; with four rows per workgroup, at
-// 256 heads of 2048 tokens, M = 128, the launch with the logits took 159 us, 81
-// this way). Few rows (PIVOT16_MIN blocks) take four per workgroup all the same:
-// there the chain of one block counts, not the products.
+// histogram counts: 22 KB per workgroup, so that the routing logits fit beside
+// it (16 rows of keys took 66 KB; with four rows per workgroup, at 256 heads of
+// 2048 tokens, M = 128, the launch with the logits took 159 us, 81 this way).
+// What bounds a block is its chain: a round trip per tile of keys, a wave's tiles
+// one after another, then some twenty instructions per sample and lane. So more
+// waves where nothing else fills the CUs: without the logits sixteen (fp32
+// eight), 14 us at up to 256 blocks of d = 64 and 30 at 1024, 17.5 and 36 with
+// four.
 // ---------------------------------------------------------------------------
-constexpr int PIVOT16_MIN = 64;  // fewer 16-row blocks than this: a quarter of the CUs at most would work
 struct PivotLds {
   uint32_t hist[16][260];  // counts per bin; rows start 4 banks apart
   uint32_t slot[16][64];   // the keys of a row's bin
-  uint32_t red[4][2][16];  // the waves' key ranges per row
+  uint32_t red[16][2][16];  // the waves' key ranges per row
   uint32_t n[16];          // keys in slot
   uint32_t bin[16], above[16];
   uint32_t bad;            // some row bisects
@@ -307,17 +308,18 @@ struct PivotLds {
 
 __device__ __forceinline__ float canonical_score(float x) { return x != x ? -INFINITY : x + 0.f; }
 
-template <typename T, int D>
+template <typename T, int D, int NW = 4>
 __device__ __forceinline__ void pivots16_body(PivotLds &sh, int bx, int by, const T *__restrict__ q_lm,
                                               const T *__restrict__ k, uint32_t *__restrict__ plo,
                                               uint32_t *__restrict__ fail_cnt, int N, int M, int r, float scale) {
-  constexpr int NT = SEL_NS / (4 * TK);  // tiles per wave
-  static_assert(NT * 4 * TK == SEL_NS, "whole tiles");
+  constexpr int NT = SEL_NS / (NW * TK);  // tiles per wave
+  constexpr int RPW = 16 / NW;            // rows ranked per wave
+  static_assert(NT * NW * TK == SEL_NS && RPW * NW == 16 && NW >= 4, "whole tiles and rows");
   const int64_t bh = by;
   const int lm0 = bx * 16;
   const int tid = threadIdx.x, w = tid >> 6, lane = tid & 63, g = lane >> 4, p = lane & 15;
   if (bx == 0 && by == 0 && tid == 0) *fail_cnt = 0;
-  for (int i = tid; i < 16 * 260; i += 256) (&sh.hist[0][0])[i] = 0u;
+  for (int i = tid; i < 16 * 260; i += 64 * NW) (&sh.hist[0][0])[i] = 0u;
   if (tid < 16) sh.n[tid] = 0u;
   if (tid == 0) sh.bad = 0u;
   Frag<T> qf[D / 32];
@@ -330,22 +332,30 @@ __device__ __forceinline__ void pivots16_body(PivotLds &sh, int bx, int by, cons
   }
   const T *kb_ = k + bh * (int64_t)N * D;
   float x[NT][4][4];
+  // steps of KB 16-key blocks, the next step's fragments in flight while one is
+  // used (two steps take 64 registers)
+  constexpr int KB = 512 / (int)(sizeof(T) * D), NU = 4 * NT / KB;
+  Frag<T> a[2][KB][D / 32];
+  auto load = [&](Frag<T>(&f)[KB][D / 32], int u) {
 #pragma unroll
-  for (int t = 0; t < NT; ++t) {
-    Frag<T> a[4][D / 32];  // all loads of a tile issued before the first is used
+    for (int i = 0; i < KB; ++i) {
+      const int blk = u * KB + i;
+      const int64_t pos = sample_pos((blk / 4 * NW + w) * TK + blk % 4 * 16 + p, N, SEL_NS);
 #pragma unroll
-    for (int kb = 0; kb < 4; ++kb) {
-      const int64_t pos = sample_pos((4 * t + w) * TK + kb * 16 + p, N, SEL_NS);
-#pragma unroll
-      for (int ks = 0; ks < D / 32; ++ks) a[kb][ks].load(kb_ + pos * D + ks * 32 + g * 8);
+      for (int ks = 0; ks < D / 32; ++ks) f[i][ks].load(kb_ + pos * D + ks * 32 + g * 8);
     }
+  };
+  load(a[0], 0);
 #pragma unroll
-    for (int kb = 0; kb < 4; ++kb) {
+  for (int u = 0; u < NU; ++u) {
+    if (u + 1 < NU) load(a[(u + 1) & 1], u + 1);
+#pragma unroll
+    for (int i = 0; i < KB; ++i) {
       f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int ks = 0; ks < D / 32; ++ks) acc = mma(a[kb][ks], qf[ks], acc);
+      for (int ks = 0; ks < D / 32; ++ks) acc = mma(a[u & 1][i][ks], qf[ks], acc);
 #pragma unroll
-      for (int q = 0; q < 4; ++q) x[t][kb][q] = canonical_score(acc[q] * scale);
+      for (int q = 0; q < 4; ++q) x[(u * KB + i) / 4][(u * KB + i) % 4][q] = canonical_score(acc[q] * scale);
     }
   }
   // every sample once: f(x)
@@ -374,7 +384,7 @@ __device__ __forceinline__ void pivots16_body(PivotLds &sh, int bx, int by, cons
   }
   __syncthreads();
 #pragma unroll
-  for (int i = 0; i < 4; ++i) {
+  for (int i = 0; i < NW; ++i) {
     lo = fminf(lo, __uint_as_float(sh.red[i][0][p]));
     hi = fmaxf(hi, __uint_as_float(sh.red[i][1][p]));
   }
@@ -385,7 +395,7 @@ __device__ __forceinline__ void pivots16_body(PivotLds &sh, int bx, int by, cons
   if (ok) each([&](float v) { atomicAdd(&sh.hist[p][bin_of(v)], 1u); });
   if (w == 0 && g == 0 && !same && !ok) sh.bad = 1u;
   __syncthreads();
-  {
+  if (w < 4) {
     // wave w's lane group g: the bin of row 4 w + g that holds rank r, lane p
     // summing bins 255 - 16 p down to 240 - 16 p
     const int row = 4 * w + g;
@@ -427,18 +437,18 @@ __device__ __forceinline__ void pivots16_body(PivotLds &sh, int bx, int by, cons
         if (bin_of(v) == mybin) sh.slot[p][atomicAdd(&sh.n[p], 1u) & 63u] = ordered_key(v);
       });
     __syncthreads();
-    // wave w ranks the slots of rows 4 w .. 4 w + 3
-    for (int i = 0; i < 4; ++i) {
-      const int row = 4 * w + i;
+    // wave w ranks the slots of its RPW rows
+    for (int i = 0; i < RPW; ++i) {
+      const int row = RPW * w + i;
       if (lm0 + row >= M) break;  // uniform for the wave
-      const uint32_t n = sh.n[row];
+      const uint32_t n = (uint32_t)__builtin_amdgcn_readfirstlane((int)sh.n[row]);
       // (a row of one value: no slots)
       uint32_t key = ordered_key(__shfl(lo, row));
       if (n > 0u) {
         const uint32_t mine = (uint32_t)lane < n ? sh.slot[row][lane] : 0u;
         uint32_t rank = 0;
         for (uint32_t j = 0; j < n; ++j) {
-          const uint32_t other = sh.slot[row][j];
+          const uint32_t other = (uint32_t)__builtin_amdgcn_readlane((int)mine, (int)j);
           rank += other > mine || (other == mine && j < (uint32_t)lane) ? 1u : 0u;
         }
         const uint64_t m = __ballot((uint32_t)lane < n && rank == (uint32_t)r - 1u - sh.above[row]);
@@ -452,7 +462,7 @@ __device__ __forceinline__ void pivots16_body(PivotLds &sh, int bx, int by, cons
   // least r samples reach the result's higher bits with b set (counts of step
   // `bit` in hist row bit / 2, words 128 (bit & 1) + row of a fresh buffer)
   __syncthreads();
-  for (int i = tid; i < 16 * 260; i += 256) (&sh.hist[0][0])[i] = 0u;
+  for (int i = tid; i < 16 * 260; i += 64 * NW) (&sh.hist[0][0])[i] = 0u;
   __syncthreads();
   uint32_t t = 0;
   for (int bit = 31; bit >= 0; --bit) {

@@ -36,22 +36,26 @@
 
 namespace mita {
 
-// One workgroup per (16 landmarks, head) slot (ROWS 0: pivots16_body), or (ROWS
-// landmarks, head) with the sets (the sample is the whole row); slots spread
-// over the XCDs in contiguous ranges (xcd_slot): a head's landmark blocks share
-// an XCD, so its sampled key rows are fetched into one L2 instead of one per
-// block.
-template <typename T, int D, int ROWS>
-__global__ __launch_bounds__(ROWS ? 64 * ROWS : 256) void sample_pivot_kernel(
+template <typename T> constexpr int PIVOT16_WAVES = sizeof(T) == 2 ? 16 : 8;
+
+// One workgroup per (16 landmarks, head) slot (ROWS 0: pivots16_body) or (ROWS
+// landmarks, head) slot, with the sets if the sample is the whole row (SETS);
+// slots spread over the XCDs in contiguous ranges (xcd_slot): a head's landmark
+// blocks share an XCD, so its sampled key rows are fetched into one L2 instead
+// of one per block.
+template <typename T, int D, int ROWS, bool SETS>
+__global__ __launch_bounds__(ROWS ? 64 * ROWS : 64 * PIVOT16_WAVES<T>) void sample_pivot_kernel(
     const T *__restrict__ q_lm, const T *__restrict__ k, uint32_t *__restrict__ plo, uint32_t *__restrict__ fail_cnt,
     int N, int M, int r, float scale, int nbx, int nslots, int32_t *__restrict__ idx) {
+  static_assert(ROWS != 0 || !SETS, "sets come from rows of keys");
   __shared__ __align__(16) std::conditional_t<ROWS != 0, uint32_t[ROWS ? ROWS : 1][SP_PITCH], PivotLds> sh;
   const int f = xcd_slot((int)blockIdx.x, (int)gridDim.x / NXCD);
   if (f >= nslots) return;  // the whole workgroup
   if constexpr (ROWS != 0)
-    sample_pivot_body<T, D, true, ROWS>(sh, f % nbx, f / nbx, q_lm, k, plo, fail_cnt, N, M, N, r, scale, idx, r);
+    sample_pivot_body<T, D, SETS, ROWS>(sh, f % nbx, f / nbx, q_lm, k, plo, fail_cnt, N, M, SETS ? N : SEL_NS, r, scale,
+                                        idx, r);
   else
-    pivots16_body<T, D>(sh, f % nbx, f / nbx, q_lm, k, plo, fail_cnt, N, M, r, scale);
+    pivots16_body<T, D, PIVOT16_WAVES<T>>(sh, f % nbx, f / nbx, q_lm, k, plo, fail_cnt, N, M, r, scale);
 }
 
 template <typename T, int D, int CAP, bool MERGE>
@@ -91,19 +95,23 @@ template <typename T, int D>
 static hipError_t sample_pivot_t(const mita_cfg_t &c, const void *q_lm, const void *k, const SelectBufs &sb,
                                  hipStream_t st) {
   constexpr int MANY = sizeof(T) == 2 ? 16 : 8;  // rows per workgroup (fp32 fragments need eight waves' registers)
-#define MITA_PIVOTS(ROWS, PER)                                                                                      \
+#define MITA_PIVOTS(ROWS, PER, SETS)                                                                                \
   {                                                                                                                 \
     const int nbx = (c.M + PER - 1) / PER, nslots = nbx * (int)BH(c);                                               \
-    hipLaunchKernelGGL((sample_pivot_kernel<T, D, ROWS>), dim3((unsigned)(NXCD * ((nslots + NXCD - 1) / NXCD))),    \
-                       dim3(ROWS ? 64 * ROWS : 256), 0, st, (const T *)q_lm, (const T *)k, sb.plo, sb.fail_cnt, c.N, \
+    hipLaunchKernelGGL((sample_pivot_kernel<T, D, ROWS, SETS>), dim3((unsigned)(NXCD * ((nslots + NXCD - 1) / NXCD))), \
+                       dim3(64 * (ROWS ? ROWS : PIVOT16_WAVES<T>)), 0, st, (const T *)q_lm, (const T *)k, sb.plo, sb.fail_cnt, c.N, \
                        c.M, sb.rank, eff_scale(c), nbx, nslots, sb.idx);                                            \
   }
-  if (!sb.idx)
-    MITA_PIVOTS(0, 16)
-  else if (few_rows(c))
-    MITA_PIVOTS(SP_ROWS, SP_ROWS)
-  else
-    MITA_PIVOTS(MANY, MANY)
+  if (!sb.idx) {
+    if (few_pivots(c))
+      MITA_PIVOTS(SP_ROWS, SP_ROWS, false)
+    else
+      MITA_PIVOTS(0, 16, false)
+  } else if (few_rows(c)) {
+    MITA_PIVOTS(SP_ROWS, SP_ROWS, true)
+  } else {
+    MITA_PIVOTS(MANY, MANY, true)
+  }
 #undef MITA_PIVOTS
   return launched("sample_pivot_kernel", st);
 }
