@@ -141,8 +141,13 @@ hipError_t launch_select_finalize(const mita_cfg_t &c, const SelectBufs &sb, int
                      idx, sb.fail_cnt, sb.fail_list, c.k, sb.cap, nch, ml, po, (TT *)v_lm, c.M, eff_scale(c),      \
                      (int64_t)rows, live)
   const LiveRows live{sb.live, sb.live_groups};
-  // lists of at most SEL_NS entries over at most 64 chunks: one wave per row
-  const bool wave = sb.cap <= SEL_NS && nch <= 64;
+  // Lists of at most SEL_NS entries over at most 64 chunks: one wave per row,
+  // unless there are so few rows that a workgroup per row is resident at once and
+  // its shorter chain counts (us with a wave and with a workgroup, d = 64: 4096
+  // tokens 11.8 and 10.2 at 256 rows, 14.6 and 12.0 at 1536, 14.8 and 16.3 at 2048;
+  // 8192 tokens 15.4 and 9.9, 17.5 and 12.8, 17.8 and 17.3; 1100 tokens 9.3 and 9.6
+  // at 1024 rows, 9.6 and 11.0 at 1536).
+  const bool wave = sb.cap <= SEL_NS && nch <= 64 && rows > (nch >= 8 ? 1536u : 1024u);
 #define MITA_FINALIZE_CAP(TT, DD, MG)     \
   if (wave)                               \
     MITA_FINALIZE_WAVE(TT, DD, MG);       \

@@ -25,7 +25,7 @@ pytestmark = pytest.mark.gpu
 # and (cap above 1024) by a workgroup. M: one landmark, each side of a
 # 16-landmark block and of 64, experts without queries (clusters < M). The last
 # ones have too many scores for the direct launch.
-# (B, H) puts the pivots on each side of 64 sixteen-landmark blocks; 1023
+# (B, H) puts the finish on each side of 1024 and 1536 rows and the pivots on each side of 64 sixteen-landmark blocks; 1023
 # landmarks are the most LDS the launch with the logits takes.
 # N, landmark rows and columns, k, d, s, dtype, B, H, clusters
 CASES = [
@@ -38,6 +38,7 @@ CASES = [
     (257, 4, 4, 16, 64, 4, "f32", 1, 2, 3), (16384, 4, 4, 512, 64, 1, "bf16", 1, 2, 6), (9000, 4, 5, 800, 128, 1, "bf16", 1, 2, 6),
     (1000, 5, 10, 77, 64, 1, "f32", 4, 16, 9), (900, 1, 26, 900, 128, 1, "f32", 2, 16, 5), (1023, 3, 11, 64, 128, 2, "bf16", 2, 12, 5),
     (1000, 7, 7, 49, 64, 1, "bf16", 8, 12, 11), (1100, 31, 33, 30, 64, 1, "bf16", 1, 1, 50),
+    (1100, 4, 4, 40, 64, 1, "bf16", 5, 13, 7), (4096, 4, 4, 300, 128, 1, "bf16", 8, 12, 9), (4096, 4, 4, 300, 64, 2, "bf16", 1, 97, 9),
 ]
 
 

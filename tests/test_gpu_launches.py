@@ -47,3 +47,10 @@ def test_listed_selection_routes_before_the_scores(s):
     names = _launches(_cfg(4, 1025, 16, 49, s=s))
     logits = names.index("route_tops_kernel" if s > 1 else "pivots_logits_kernel")
     assert logits < names.index("scores_kernel") < names.index("topk_scatter_kernel")
+
+
+@pytest.mark.parametrize("N,H,finish", [(1100, 64, "finalize_kernel"), (1100, 65, "finalize_wave_kernel"),
+                                        (4096, 96, "finalize_kernel"), (4096, 97, "finalize_wave_kernel")])
+def test_few_rows_finish_by_workgroups(N, H, finish):
+    """Sixteen landmarks per head: 1024 and 1040 rows, 1536 and 1552."""
+    assert finish in _launches(_cfg(H, N, 16, 40))
