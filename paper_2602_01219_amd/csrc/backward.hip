@@ -1570,7 +1570,13 @@ static hipError_t bwd_t(const mita_cfg_t &c, const BwdBufs &b, hipStream_t st) {
       constexpr int NG = BWD16_GROUPS<D>;
       bool two = false;
       if constexpr (D == 64) {
-        two = c.k <= 64;  // two waves cover the block
+        // Two waves cover the block, unless there are few blocks of many queries:
+        // then a block's chain of stages counts, and the two other waves double
+        // the stage (us with two and with four waves, k = 49: 12 heads of 13818
+        // tokens, M = 16 112 and 83; 12 of 512, M = 16 11.6 and 11.0; 48 of 4096,
+        // M = 16 49.5 and 39.6, M = 64 57.0 and 60.8; 12 of 196, M = 16 9.8 and 9.9;
+        // 384 of 196 43.7 and 54.6).
+        two = c.k <= 64 && !(BH(c) * c.M <= 1024 && c.N >= 32 * c.M);
         if (two) {
           const dim3 g = routed_keys(KvTile<D, NG, 2>::KB);
           hipLaunchKernelGGL((bwd_kv16_kernel<D, KV_ROUTED, NG, 2>), g, dim3(128), 0, st, kv);

@@ -21,12 +21,13 @@ pytestmark = pytest.mark.gpu
 # grid, landmark grid, k, d, clusters: one key past a block (65 of 64 or 128
 # keys per block) and past the landmarks' two-wave block, exactly one block of
 # each, a single key and a single query stage, long experts (several stages
-# of 64 queries, with a remainder), more slots per token block than the kernel
+# of 64 queries, with a remainder), a block of at most 64 keys by four waves (32
+# queries per expert) and by two (fewer), more slots per token block than the kernel
 # keeps in LDS (k = N: every token in every expert's set), d = 128.
 # (The keys of an expert must not be all alike: dq sums dZ_j k_j with sum dZ_j =
 # 0, so the rounding of D = dO . o to bf16's o comes back times the keys' mean.)
 CASES = [(29, 37, 5, 13, 65, 64, 4), (16, 16, 8, 8, 64, 64, 4), (16, 24, 8, 16, 128, 64, 4), (1, 130, 1, 2, 1, 64, 2),
-         (40, 50, 2, 2, 129, 64, 64), (12, 12, 3, 3, 144, 64, 3), (20, 21, 4, 5, 200, 128, 4), (9, 15, 3, 3, 135, 128, 3)]
+         (40, 50, 2, 2, 129, 64, 64), (16, 40, 4, 5, 64, 64, 4), (16, 40, 3, 7, 37, 64, 4), (12, 12, 3, 3, 144, 64, 3), (20, 21, 4, 5, 200, 128, 4), (9, 15, 3, 3, 135, 128, 3)]
 
 
 def _workload(case):
