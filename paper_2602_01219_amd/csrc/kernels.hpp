@@ -68,15 +68,14 @@ inline bool few_rows(const mita_cfg_t &c) {
 // 96; d = 128 15 against 18, 22 against 18).
 inline int64_t pivot_blocks(const mita_cfg_t &c) { return (c.M + 15) / 16 * ((int64_t)c.B * c.H); }
 inline bool few_pivots(const mita_cfg_t &c) { return pivot_blocks(c) <= 64; }
-// With the logits in the same launch: eight waves per workgroup where the chain
-// of a block counts, four where the logits do (bf16, d = 64, 4096 tokens, us with
+// With the logits in the same launch, bf16 and d = 64: eight waves per workgroup
+// where the chain of a block counts, four where the logits do (4096 tokens, us with
 // eight and with four: 14.6 and 18.9 at 64 blocks, 16.5 and 18.7 at 96, 17.0 and
 // 19.8 at 128, 22.0 and 19.7 at 256; at 16384 tokens 23.5 and 24.3, 26.6 and 27.8,
-// 33.6 and 33.9, 56.4 and 48.9). Twice the bytes per row, half the blocks (d = 128,
-// 16384 tokens: 28.0 and 31.0 at 64, 35.6 and 33.8 at 96).
-inline bool pivots_wide(const mita_cfg_t &c) {
-  return pivot_blocks(c) * (c.d / 64) * (c.dtype == MITA_F32 ? 2 : 1) <= 128;
-}
+// 33.6 and 33.9, 56.4 and 48.9). Rows of 256 bytes and more take four: eight cost
+// registers, and with a row per wave 15.8 against 14.8 us at d = 128, 18.4 against
+// 15.8 in fp32.
+inline bool pivots_wide(const mita_cfg_t &c) { return c.d == 64 && c.dtype == MITA_BF16 && pivot_blocks(c) <= 128; }
 
 // Fused selection, before the score pass: sampled scores, per-row pivots;
 // zeroes the candidate and fallback counters.

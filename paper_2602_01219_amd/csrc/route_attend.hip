@@ -696,10 +696,10 @@ __global__ __launch_bounds__(256) void route_scatter_kernel(const int32_t *__res
 // sample slots (spread over the XCDs by xcd_slot so that a head's blocks share
 // an L2; slots past nS exit), the rest the routing grid; LDS is one buffer that
 // either part lays out for itself.
-// NWV = 4, many blocks of 16 landmark rows: three waves per SIMD (four spill: 84
-// against 78 us at 256 heads of 2048 tokens, M = 128). NWV = 8, few blocks
-// (pivots_wide): a block's chain of loads and histogram steps halves, and with
-// fewer still (few_pivots, by_rows) a wave takes one row.
+// With few blocks of 16 landmark rows (few_pivots, by_rows) a wave takes one row.
+// NWV = 4: three waves per SIMD (four spill: 84 against 78 us at 256 heads of 2048
+// tokens, M = 128). NWV = 8 (pivots_wide): a block's chain of loads and histogram
+// steps halves.
 // ---------------------------------------------------------------------------
 template <typename T, int D, int NWV>
 __global__ __launch_bounds__(64 * NWV) __attribute__((amdgpu_waves_per_eu(sizeof(T) == 4 ? 2 : NWV == 8 ? 4 : 3)))
@@ -707,18 +707,17 @@ void pivots_logits_kernel(const T *__restrict__ q_lm, const T *__restrict__ k, u
                           uint32_t *__restrict__ fail_cnt, int r, bool by_rows, int sample_x, int nS, int nSp,
                           const T *__restrict__ q, int32_t *__restrict__ expert, int32_t *__restrict__ counts, int N,
                           int M, float scale, int ntiles, int route_x) {
-  constexpr int P = NWV == 8 ? 8 * SP_PITCH * 4 : (int)sizeof(PivotLds);
+  constexpr int R = NWV * SP_PITCH * 4, P = R > (int)sizeof(PivotLds) ? R : (int)sizeof(PivotLds);
   constexpr int BYTES = P > RouteLds<T, D>::BYTES ? P : RouteLds<T, D>::BYTES;
-  static_assert(BYTES >= (int)sizeof(PivotLds), "either pivot body fits");
   __shared__ __align__(16) char buf[BYTES];
   extern __shared__ uint32_t cnt[];  // routing: [NWV][M]
   const int b = (int)blockIdx.x;
   if (b < nSp) {  // nSp = nS rounded up to whole XCD ranges (xcd_slot)
     const int f = xcd_slot(b, nSp / NXCD);
     if (f >= nS) return;
-    if (NWV == 8 && by_rows)
-      sample_pivot_body<T, D, false, 8>(reinterpret_cast<uint32_t(*)[SP_PITCH]>(buf), f % sample_x, f / sample_x, q_lm,
-                                        k, plo, fail_cnt, N, M, SEL_NS, r, scale, nullptr, 0);
+    if (by_rows)
+      sample_pivot_body<T, D, false, NWV>(reinterpret_cast<uint32_t(*)[SP_PITCH]>(buf), f % sample_x, f / sample_x,
+                                          q_lm, k, plo, fail_cnt, N, M, SEL_NS, r, scale, nullptr, 0);
     else
       pivots16_body<T, D, NWV>(*reinterpret_cast<PivotLds *>(buf), f % sample_x, f / sample_x, q_lm, k, plo, fail_cnt,
                                N, M, r, scale);
@@ -1655,20 +1654,23 @@ static hipError_t pivots_logits_t(const mita_cfg_t &c, const void *q, const void
                                   const SelectBufs &sb, int32_t *expert, int32_t *counts, hipStream_t st) {
   const int bh = (int)BH(c), nt = route_tiles(c);
   const bool by_rows = few_pivots(c);
-  const int sample_x = by_rows ? (c.M + 7) / 8 : (c.M + 15) / 16;
-  const int nS = sample_x * bh, nSp = NXCD * ((nS + NXCD - 1) / NXCD);
   auto run = [&](auto nwv_c) {
     constexpr int NWV = decltype(nwv_c)::value;
+    const int sample_x = by_rows ? (c.M + NWV - 1) / NWV : (c.M + 15) / 16;
+    const int nS = sample_x * bh, nSp = NXCD * ((nS + NXCD - 1) / NXCD);
     const int route_x = (nt + NWV - 1) / NWV;
     hipLaunchKernelGGL((pivots_logits_kernel<T, D, NWV>), dim3((unsigned)(nSp + route_x * bh)), dim3(64 * NWV),
                        NWV * (size_t)c.M * sizeof(uint32_t), st, (const T *)q_lm, (const T *)k, sb.plo, sb.fail_cnt,
                        sb.rank, by_rows, sample_x, nS, nSp, (const T *)q, expert, counts, c.N, c.M, eff_scale(c), nt,
                        route_x);
   };
-  if (pivots_wide(c))
-    run(std::integral_constant<int, 8>{});
-  else
-    run(std::integral_constant<int, 4>{});
+  if constexpr (sizeof(T) == 2 && D == 64) {
+    if (pivots_wide(c)) {
+      run(std::integral_constant<int, 8>{});
+      return launched("pivots_logits_kernel", st);
+    }
+  }
+  run(std::integral_constant<int, 4>{});
   return launched("pivots_logits_kernel", st);
 }
 

@@ -332,30 +332,35 @@ __device__ __forceinline__ void pivots16_body(PivotLds &sh, int bx, int by, cons
   }
   const T *kb_ = k + bh * (int64_t)N * D;
   float x[NT][4][4];
-  // steps of KB 16-key blocks, the next step's fragments in flight while one is
-  // used (two steps take 64 registers)
-  constexpr int KB = 512 / (int)(sizeof(T) * D), NU = 4 * NT / KB;
-  Frag<T> a[2][KB][D / 32];
-  auto load = [&](Frag<T>(&f)[KB][D / 32], int u) {
+  // a tile's loads are issued before the first is used, where registers allow
+  // with the next tile's in flight
+  constexpr bool AHEAD = sizeof(T) * D == 128;
+  Frag<T> a[AHEAD ? 2 : 1][4][D / 32];
+  auto load = [&](Frag<T>(&f)[4][D / 32], int t) {
 #pragma unroll
-    for (int i = 0; i < KB; ++i) {
-      const int blk = u * KB + i;
-      const int64_t pos = sample_pos((blk / 4 * NW + w) * TK + blk % 4 * 16 + p, N, SEL_NS);
+    for (int kb = 0; kb < 4; ++kb) {
+      const int64_t pos = sample_pos((NW * t + w) * TK + kb * 16 + p, N, SEL_NS);
 #pragma unroll
-      for (int ks = 0; ks < D / 32; ++ks) f[i][ks].load(kb_ + pos * D + ks * 32 + g * 8);
+      for (int ks = 0; ks < D / 32; ++ks) f[kb][ks].load(kb_ + pos * D + ks * 32 + g * 8);
     }
   };
-  load(a[0], 0);
+  if (AHEAD) load(a[0], 0);
 #pragma unroll
-  for (int u = 0; u < NU; ++u) {
-    if (u + 1 < NU) load(a[(u + 1) & 1], u + 1);
+  for (int t = 0; t < NT; ++t) {
+    if (!AHEAD)
+      load(a[0], t);
+    else if (t + 1 < NT)
+      load(a[(t + 1) & 1], t + 1);
+    // (else the loads sink to their uses, one wait each; with one tile per wave the
+    // many waves cover those, and the registers held would halve them)
+    if (NT > 1) __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-    for (int i = 0; i < KB; ++i) {
+    for (int kb = 0; kb < 4; ++kb) {
       f32x4 acc = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int ks = 0; ks < D / 32; ++ks) acc = mma(a[u & 1][i][ks], qf[ks], acc);
+      for (int ks = 0; ks < D / 32; ++ks) acc = mma(a[AHEAD ? t & 1 : 0][kb][ks], qf[ks], acc);
 #pragma unroll
-      for (int q = 0; q < 4; ++q) x[(u * KB + i) / 4][(u * KB + i) % 4][q] = canonical_score(acc[q] * scale);
+      for (int q = 0; q < 4; ++q) x[t][kb][q] = canonical_score(acc[q] * scale);
     }
   }
   // every sample once: f(x)
