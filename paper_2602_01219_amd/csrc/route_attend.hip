@@ -743,7 +743,11 @@ template <typename T, int D> struct DirectLds {
   static constexpr int V = S16 ? 4 * DmaTile<D, TK32, 4>::BYTES
                                : 2 * (TileDims<T, D>::K_ELEMS + TileDims<T, D>::V_ELEMS) * (int)sizeof(T);
   static constexpr int A = SP_BYTES > RouteLds<T, D>::BYTES ? SP_BYTES : RouteLds<T, D>::BYTES;
-  template <bool VALUES> static constexpr int bytes() { return VALUES && V > A ? V : A; }
+  // the two tiles of score16_chunk are LDS objects of their own: the compiler
+  // waits for a tile in flight before it reads the other half of one array
+  static constexpr int V0 = S16 ? V / 2 : V;
+  template <bool VALUES> static constexpr int bytes() { return VALUES && V0 > A ? V0 : A; }
+  template <bool VALUES> static constexpr int bytes1() { return VALUES && S16 ? V / 2 : 16; }
 };
 struct DirectRoute {
   uint32_t cnt[SEL_NS];  // expert sizes, then each expert's next position (M <= N)
@@ -834,6 +838,7 @@ __global__ __launch_bounds__(BLOCK) void direct_kernel(const T *__restrict__ q, 
                                                        float scale, int sample_x, int nS, int nSp, int nV, int nch) {
   using DL = DirectLds<T, D>;
   __shared__ __align__(16) char buf[DL::template bytes<VALUES>()];
+  __shared__ __align__(16) char buf1[DL::template bytes1<VALUES>()];
   __shared__ DirectRoute route;
   const int b = (int)blockIdx.x;
   if (b < nSp) {
@@ -849,7 +854,7 @@ __global__ __launch_bounds__(BLOCK) void direct_kernel(const T *__restrict__ q, 
     const SelectArgs none{};
     for (int ch = 0; ch < nch; ++ch) {
       if constexpr (DL::S16) {
-        score16_chunk<D, 1, 4, false, false>(buf, buf + DL::V / 2, q_lm, k, v, nullptr, part_ml, part_o, none, N, M,
+        score16_chunk<D, 1, 4, false, false>(buf, buf1, q_lm, k, v, nullptr, part_ml, part_o, none, N, M,
                                              scale, ch, nch, lb, bh);
       } else {
         T *Ks = reinterpret_cast<T *>(buf), *Vt = Ks + 2 * TileDims<T, D>::K_ELEMS;
