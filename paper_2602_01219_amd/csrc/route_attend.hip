@@ -1244,16 +1244,29 @@ __global__ __launch_bounds__(BLOCK) void attend_kernel(const T *__restrict__ q, 
 // four waves per SIMD, whose LDS reads per MFMA are twice as many. Four waves
 // on one tile (128 queries, half the fetches) leave more waves without
 // queries: 1170 us there, and 95 -> 104 us at 16384 tokens, d = 64.
-// d = 128 takes one group per wave and four waves where an expert has fewer than
-// 64 queries on average (most groups are empty, and two waves issue a tile's
-// loads more slowly than four: 49.4 against 53.9 us at 512 heads of 196 tokens,
-// M = 16; 70.4 against 73.4 at 16 heads of 4096, M = 256; with 128 queries 86.8
-// against 77.9 at 16 heads of 8192, M = 64), or where the row list leaves three
-// workgroups per CU (k = 2100: 101 against 112 us).
+// d = 128 takes one group per wave and four waves, whose loads and chains overlap
+// more, where
+//  - an expert has fewer than 64 queries on average: most groups are empty (49.4
+//    against 53.9 us at 512 heads of 196 tokens, M = 16; 70.4 against 73.4 at 16
+//    heads of 4096, M = 256; with 128 queries 86.8 against 77.9 at 16 heads of 8192,
+//    M = 64);
+//  - the row list leaves three workgroups per CU (k = 2100: 101 against 112 us);
+//  - the grid leaves fewer than two workgroups per CU (one head of 8192 tokens, M =
+//    32, k = 500 18.8 against 22.3 us; four of 4096, M = 64, k = 250 18.5 against
+//    20.0; two of 16384, M = 64 23.5 against 22.7);
+//  - the list is short: a workgroup is mostly prologue. With the grid beyond one
+//    round of the chip, below some 192 rows (42 heads of 12347, M = 10, k = 96 115.0
+//    against 118.7 us, k = 200 150.7 against 153.0, k = 300 178.7 against 176.1), else
+//    below 96 (16 heads of 3000, M = 9, k = 64 17.6 against 17.5, k = 120 21.0 against
+//    19.3).
 static bool att16_two(const mita_cfg_t &c, int nlist) {
   if (c.d == 64) return true;
-  const bool busy = !c.use_routed || route_items(c) >= (int64_t)ATT_TQ * route_groups(c);
-  return busy && 4 * (attend16_tiles_lds<128>() + 4 * (size_t)nlist) <= LDS_BYTES;
+  const int64_t items = route_items(c), groups = c.use_routed ? route_groups(c) : 0;
+  if (items < (int64_t)ATT_TQ * groups) return false;
+  if (4 * (attend16_tiles_lds<128>() + 4 * (size_t)nlist) > LDS_BYTES) return false;
+  // workgroups: a tile per 64 queries, and half a tile more per group
+  const int64_t tiles = BH(c) * (items / ATT_TQ + groups / 2);
+  return tiles >= 512 && nlist >= (tiles < 1000 ? 96 : 192);
 }
 #define ATTEND16_OCCUPANCY __attribute__((amdgpu_waves_per_eu(D == 64 ? 4 : NG == 2 ? 2 : 4)))
 

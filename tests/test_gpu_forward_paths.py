@@ -25,8 +25,9 @@ pytestmark = pytest.mark.gpu
 # and (cap above 1024) by a workgroup. M: one landmark, each side of a
 # 16-landmark block and of 64, experts without queries (clusters < M). The last
 # ones have too many scores for the direct launch.
-# (B, H) puts the finish on each side of 1024 and 1536 rows and the pivots on each side of 64 sixteen-landmark blocks; 1023
-# landmarks are the most LDS the launch with the logits takes.
+# (B, H) puts the finish on each side of 1024 and 1536 rows and the pivots on each
+# side of 64 sixteen-landmark blocks; 1023 landmarks are the most LDS the launch
+# with the logits takes.
 # N, landmark rows and columns, k, d, s, dtype, B, H, clusters
 CASES = [
     (1, 1, 1, 1, 64, 1, "f32", 1, 1, 1), (63, 1, 3, 5, 64, 1, "bf16", 1, 3, 3), (196, 4, 4, 196, 64, 1, "bf16", 2, 2, 9),
@@ -58,3 +59,27 @@ def test_forward_equals_stored_scores(case):
         o = mita.forward(dataclasses.replace(cfg, staged_gather=staged), q, K, v)
         log(f"  staged {staged}: {int((o != ref).sum())} elements differ")
         assert torch.isfinite(o).all() and torch.equal(o, ref)
+
+
+# More heads take other launches: d = 128 at 4000 tokens, two query groups per wave
+# of the attention with 8 heads but not with 7 (512 tiles) and, with a list of 160
+# rows, not with 16 (1000 tiles); d = 64, eight waves per block of pivots with up to
+# 128 heads, a workgroup per finished row with up to 96; N <= 1024, one launch
+# for everything before the attention with up to 49 heads.
+# N, M, k, d, s, dtype, fewer heads, more heads
+LINES = [(4000, 8, 152, 128, 1, "bf16", 7, 8), (4000, 8, 152, 128, 1, "bf16", 15, 16), (4000, 8, 152, 128, 2, "bf16", 3, 16),
+         (4000, 8, 500, 128, 1, "bf16", 7, 16), (4096, 16, 100, 64, 1, "bf16", 96, 129), (1000, 50, 64, 64, 1, "bf16", 49, 51),
+         (2000, 16, 100, 64, 1, "f32", 60, 66)]
+
+
+@pytest.mark.parametrize("case", LINES, ids=["n%d_m%d_k%d_d%d_s%d_%s_h%d_%d" % c for c in LINES])
+def test_heads_do_not_depend_on_the_launch(case):
+    """A head's output is the same bits among fewer and among more heads."""
+    N, M, k, d, s, dtype, few, many = case
+    wl = synth.Workload(name="lines", B=1, H=many, grid_h=1, grid_w=N, d=d, lm_h=1, lm_w=M, k=k, dtype=dtype, clusters=M,
+                        std=0.5, cluster_map="iid", seed=N + k)
+    cfg = dataclasses.replace(mita.Config.from_workload(wl), s=s)
+    q, K, v = inputs_to_dev(synth.generate(wl))
+    o = mita.forward(cfg, q, K, v)
+    part = mita.forward(dataclasses.replace(cfg, H=few), *(x[:, :few].contiguous() for x in (q, K, v)))
+    assert torch.isfinite(o).all() and torch.equal(o[:, :few], part)
