@@ -87,12 +87,9 @@ def kernel_work(name: str, wl, plan: dict, staged: bool, s: int = 1, launched=()
         # sampled scores with pivots, and the routing logits
         "pivots_logits_kernel": (BH * ns * d * e + lmt + 4 * rows + tens + lmt + 4 * BH * N,
                                  2 * M * ns * d * BH + 2 * N * M * d * BH),
-        # (direct selection, N <= 1024 and s = 1: this launch forms the sets,
-        # the landmark values and the routing)
-        "scores_kernel": (tens * (2 + sh) + lmt * (1 + sh) + 4 * rows * k + 4 * BH * N,
-                          2 * M * N * d * BH * (2 + sh))
-                         if ns == N and s == 1 and "route_logits_kernel" not in launched else
-                         (tens * (1 + sh) + lmt + 4 * BH * M * N * stored_s, 2 * M * N * d * BH * (1 + sh)),
+        "scores_kernel": (tens * (1 + sh) + lmt + 4 * BH * M * N * stored_s, 2 * M * N * d * BH * (1 + sh)),
+        # few scores, N <= 1024 and s = 1: the sets, the landmark values and the routing
+        "direct_kernel": (tens * (2 + sh) + lmt * (1 + sh) + 4 * rows * k + 4 * BH * N, 2 * M * N * d * BH * (2 + sh)),
         "merge_kernel": (BH * nch * M * (d + 2) * 4 + lmt, 0),
         "finalize_kernel": (4 * rows * k + lmt * sh, 0),
         "topk_scatter_kernel": (8 * BH * N + 8 * BH * (M + 1), 0),

@@ -1786,7 +1786,7 @@ static hipError_t direct_t(const mita_cfg_t &c, const void *q, const void *q_lm,
   else
     MITA_DIRECT(false);
 #undef MITA_DIRECT
-  return launched("scores_kernel", st);  // (the score pass of these shapes: the timer keeps its name)
+  return launched("direct_kernel", st);
 }
 
 hipError_t launch_direct(const mita_cfg_t &c, const void *q, const void *q_lm, const void *k, const void *v,

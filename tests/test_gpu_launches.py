@@ -54,3 +54,13 @@ def test_listed_selection_routes_before_the_scores(s):
 def test_few_rows_finish_by_workgroups(N, H, finish):
     """Sixteen landmarks per head: 1024 and 1040 rows, 1536 and 1552."""
     assert finish in _launches(_cfg(H, N, 16, 40))
+
+
+def test_launches_by_name():
+    """Every kernel of a call under its own name."""
+    assert _launches(_cfg(6, 196, 16, 49)) == ["pool_small_kernel", "direct_kernel", "attend16_kernel"]
+    assert _launches(_cfg(2, 4096, 16, 300, d=128)) == ["pool_kernel", "pivots_logits_kernel", "scores16_kernel",
+                                                        "finalize_kernel", "topk_scatter_kernel", "attend16_kernel"]
+    assert _launches(_cfg(2, 2048, 16, 100, s=2, dtype="f32")) == [
+        "pool_kernel", "route_tops_kernel", "sample_pivot_kernel", "scores_kernel", "finalize_kernel",
+        "topk_scatter_kernel", "attend_kernel", "combine_kernel"]
