@@ -24,10 +24,10 @@
 //   P = exp2(S^T * scale * log2 e - lse), dZ = P (dP - D), D = dO . o
 //   dQ += dZ K,  dK += dZ^T Q,  dV += P^T dO        (scale applied at the end)
 // All products run on MFMA (16x16 tiles over 32-long reduction steps) from
-// LDS copies laid out so that every operand is read as 8 consecutive
-// elements: Q and dO row-major (and, for bf16 at d = 64, transposed; else
-// their columns are read element by element), the key tile row-major and
-// transposed, P and dZ as [key][query] and dZ as [query][key].
+// LDS copies laid out so that most operands are read as 8 consecutive
+// elements: Q and dO row-major (in the fp32 passes that need their columns those
+// are read element by element), the key tile row-major and transposed, P and dZ
+// as [key][query] and dZ as [query][key].
 // The keys' gradients of the MiTA attention come from key-owned kernels
 // (bwd_kv_kernel in fp32), where a workgroup owns a block of keys and streams
 // the queries that attend them, so that dK and dV stay in registers: a routed
@@ -56,29 +56,16 @@ constexpr int BWD_CHUNK = 512;  // keys per workgroup of the landmark-value back
 
 template <typename T, int D> struct BwdLds {
   static constexpr int PAD = 16 / (int)sizeof(T);
-  static constexpr bool TRANS = sizeof(T) == 2 && D == 64;  // transposed copies of Q and dO
   static constexpr int QS = D + PAD;        // [query][d]
-  static constexpr int TS = BWD_TQ + PAD;   // [d][query]
   static constexpr int KS = D + PAD;        // [key][d]
   static constexpr int KTS = BWD_TK + PAD;  // [d][key]
   static constexpr int PS = BWD_TQ + PAD;   // [key][query]
   static constexpr int ZS = BWD_TK + PAD;   // [query][key]
-  static constexpr int NQ = BWD_TQ * QS, NQT = TRANS ? D * TS : 1, NK = BWD_TK * KS, NKT = D * KTS,
-                       NP = BWD_TK * PS, NZ = BWD_TQ * ZS;
+  static constexpr int NQ = BWD_TQ * QS, NK = BWD_TK * KS, NKT = D * KTS, NP = BWD_TK * PS, NZ = BWD_TQ * ZS;
 };
 
 // 8 elements base[(r0 + i) * stride + col], i < 8 (a column of a row-major tile).
-template <typename T> __device__ __forceinline__ Frag<T> load_col(const T *base, int stride, int r0, int col);
-template <> __device__ __forceinline__ Frag<bf16_t> load_col(const bf16_t *base, int stride, int r0, int col) {
-  uint32_t w[4];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-    w[i] = (uint32_t)base[(r0 + 2 * i) * stride + col].bits | ((uint32_t)base[(r0 + 2 * i + 1) * stride + col].bits << 16);
-  Frag<bf16_t> f;
-  f.v = make_uint4(w[0], w[1], w[2], w[3]);
-  return f;
-}
-template <> __device__ __forceinline__ Frag<float> load_col(const float *base, int stride, int r0, int col) {
+__device__ __forceinline__ Frag<float> load_col(const float *base, int stride, int r0, int col) {
   Frag<float> f;
   f.a = make_float4(base[r0 * stride + col], base[(r0 + 1) * stride + col], base[(r0 + 2) * stride + col],
                     base[(r0 + 3) * stride + col]);
@@ -117,14 +104,11 @@ template <typename T, int D, int MODE, bool SHARED, bool ROUTED>
 __global__ __launch_bounds__(256) void bwd_kernel(BwdArgs a) {
   using L = BwdLds<T, D>;
   constexpr int VE = 16 / (int)sizeof(T);
-  constexpr bool TRANS = L::TRANS;
-  // the key-side tiles ([key][query] P and dZ, transposed Q and dO) serve
-  // the LMV mode's dK and dV only
+  // the key-side tiles ([key][query] P and dZ) serve the LMV mode's dK and dV
+  // only (fp32)
   constexpr bool KEYS = MODE == BWD_LMV;
   __shared__ __align__(16) T Qs[L::NQ];
   __shared__ __align__(16) T dOs[L::NQ];
-  __shared__ __align__(16) T QT[KEYS ? L::NQT : 1];
-  __shared__ __align__(16) T dOT[KEYS ? L::NQT : 1];
   __shared__ __align__(16) T Ks[L::NK];
   __shared__ __align__(16) T Vs[L::NK];
   __shared__ __align__(16) T KT[L::NKT];
@@ -185,14 +169,6 @@ __global__ __launch_bounds__(256) void bwd_kernel(BwdArgs a) {
       }
       *reinterpret_cast<uint4 *>(Qs + row * L::QS + cc * VE) = xq;
       *reinterpret_cast<uint4 *>(dOs + row * L::QS + cc * VE) = xd;
-      if constexpr (TRANS && KEYS) {
-        const T *tq = reinterpret_cast<const T *>(&xq), *td = reinterpret_cast<const T *>(&xd);
-#pragma unroll
-        for (int i = 0; i < VE; ++i) {
-          QT[(cc * VE + i) * L::TS + row] = tq[i];
-          dOT[(cc * VE + i) * L::TS + row] = td[i];
-        }
-      }
     }
     // D: four threads per query, D / 4 dimensions each, in fp32 (the upstream
     // gradient of the landmark values in its own fp32)
@@ -399,10 +375,7 @@ __global__ __launch_bounds__(256) void bwd_kernel(BwdArgs a) {
       for (int qs = 0; qs < 2; ++qs) {
         Frag<T> A, B;
         A.load((isv ? Pkq : Zkq) + (16 * kb + p) * L::PS + 32 * qs + 8 * g);
-        if constexpr (TRANS && KEYS)
-          B.load((isv ? dOT : QT) + (16 * db + p) * L::TS + 32 * qs + 8 * g);
-        else
-          B = load_col<T>(isv ? dOs : Qs, L::QS, 32 * qs + 8 * g, 16 * db + p);
+        B = load_col(isv ? dOs : Qs, L::QS, 32 * qs + 8 * g, 16 * db + p);
         acc = mma(A, B, acc);
       }
       // rows: key 16 kb + 4 g + r of the tile; column: dim 16 db + p
@@ -473,7 +446,11 @@ constexpr int BWD16_LMV_CHUNK = 2048;  // most keys per workgroup of the landmar
 template <int D> constexpr int BWD16_GROUPS = D == 64 ? 2 : 1;
 // query groups per wave of the dQ pass: at d = 128 two waves per SIMD instead of
 // four, but half the LDS reads per MFMA (16 heads of 4096 tokens, M = 64,
-// k = 256: 80 -> 60 us; the landmark mode has too few workgroups to gain)
+// k = 256: 80 -> 60 us; the landmark mode has too few workgroups to gain). Over one
+// to 64 heads of 196 to 16384 tokens, M = 16 to 1000, k = 16 to 7500 it takes 0.71
+// to 1.0 of one group's time, also where experts have few queries (384 heads of
+// 196, M = 16: 79 against 103) and lists are long; up to 1.05 of it where there is
+// less than one workgroup per CU (one head of 4096, M = 16, k = 1000: 52.3, 50.5).
 constexpr int BWD16_DQ_GROUPS = 2;
 template <int D> constexpr size_t bwd16_tiles_lds() { return 4 * (size_t)DmaTile<D, BWD16_TK>::BYTES; }
 
@@ -862,22 +839,19 @@ __global__ __launch_bounds__(256 / NG) __attribute__((amdgpu_waves_per_eu(D == 1
 // ---------------------------------------------------------------------------
 constexpr int BWD_KB = 64;
 
-template <typename T, int D> struct KvLds {
-  static constexpr int PAD = 16 / (int)sizeof(T);
-  static constexpr bool TRANS = sizeof(T) == 2 && D == 64;
-  static constexpr int QS = D + PAD, TS = BWD_TQ + PAD, WS = BWD_TQ + PAD;
-  static constexpr int NQ = BWD_TQ * QS, NQT = TRANS ? D * TS : 1, NW = 4 * 16 * WS;
+template <int D> struct KvLds {
+  static constexpr int PAD = 4;
+  static constexpr int QS = D + PAD, WS = BWD_TQ + PAD;
+  static constexpr int NQ = BWD_TQ * QS, NW = 4 * 16 * WS;
 };
 
-template <typename T, int D, bool ROUTED>
+template <int D, bool ROUTED>
 __global__ __launch_bounds__(256) void bwd_kv_kernel(KvArgs a) {
-  using L = KvLds<T, D>;
+  using T = float;
+  using L = KvLds<D>;
   constexpr int VE = 16 / (int)sizeof(T);
-  constexpr bool TRANS = L::TRANS;
   __shared__ __align__(16) T Qs[L::NQ];
   __shared__ __align__(16) T dOs[L::NQ];
-  __shared__ __align__(16) T QT[L::NQT];
-  __shared__ __align__(16) T dOT[L::NQT];
   __shared__ __align__(16) T Pw[L::NW];
   __shared__ __align__(16) T Zw[L::NW];
   __shared__ float lse_s[BWD_TQ], D_s[BWD_TQ];
@@ -955,14 +929,6 @@ __global__ __launch_bounds__(256) void bwd_kv_kernel(KvArgs a) {
       }
       *reinterpret_cast<uint4 *>(Qs + row * L::QS + cc * VE) = xq;
       *reinterpret_cast<uint4 *>(dOs + row * L::QS + cc * VE) = xd;
-      if constexpr (TRANS) {
-        const T *tq = reinterpret_cast<const T *>(&xq), *td = reinterpret_cast<const T *>(&xd);
-#pragma unroll
-        for (int i = 0; i < VE; ++i) {
-          QT[(cc * VE + i) * L::TS + row] = tq[i];
-          dOT[(cc * VE + i) * L::TS + row] = td[i];
-        }
-      }
     }
     __syncthreads();
     // P and dZ of (key 16 w + 4 g + r, query 16 qb + p) into the wave's LDS area
@@ -985,8 +951,8 @@ __global__ __launch_bounds__(256) void bwd_kv_kernel(KvArgs a) {
         const int key = 16 * w + 4 * g + r;
         const bool ok = qok && key < nkeys;
         const float pr = ok ? __builtin_amdgcn_exp2f(s[r] * sl2 - lq) : 0.f;
-        pw[(4 * g + r) * L::WS + qq] = from_f32<T>(pr);
-        zw[(4 * g + r) * L::WS + qq] = from_f32<T>(pr * (dp[r] - dq));
+        pw[(4 * g + r) * L::WS + qq] = pr;
+        zw[(4 * g + r) * L::WS + qq] = pr * (dp[r] - dq);
       }
     }
     __syncthreads();
@@ -997,16 +963,10 @@ __global__ __launch_bounds__(256) void bwd_kv_kernel(KvArgs a) {
       for (int qs = 0; qs < 2; ++qs) {
         Frag<T> A, B;
         A.load(zw + p * L::WS + 32 * qs + 8 * g);
-        if constexpr (TRANS)
-          B.load(QT + (16 * db + p) * L::TS + 32 * qs + 8 * g);
-        else
-          B = load_col<T>(Qs, L::QS, 32 * qs + 8 * g, 16 * db + p);
+        B = load_col(Qs, L::QS, 32 * qs + 8 * g, 16 * db + p);
         dk[db] = mma(A, B, dk[db]);
         A.load(pw + p * L::WS + 32 * qs + 8 * g);
-        if constexpr (TRANS)
-          B.load(dOT + (16 * db + p) * L::TS + 32 * qs + 8 * g);
-        else
-          B = load_col<T>(dOs, L::QS, 32 * qs + 8 * g, 16 * db + p);
+        B = load_col(dOs, L::QS, 32 * qs + 8 * g, 16 * db + p);
         dv[db] = mma(A, B, dv[db]);
       }
     }
@@ -1503,8 +1463,6 @@ static hipError_t bwd_t(const mita_cfg_t &c, const BwdBufs &b, hipStream_t st) {
   kv.q_lm = b.q_lm;
   kv.v_lm = b.v_lm;
   kv.idx = b.idx;
-  kv.perm = b.perm;
-  kv.offsets = b.offsets;
   kv.q_lse = b.q_lse;
   kv.q_D = b.q_D;
   kv.perm = c.use_routed ? b.perm : nullptr;
@@ -1549,7 +1507,7 @@ static hipError_t bwd_t(const mita_cfg_t &c, const BwdBufs &b, hipStream_t st) {
       }
     } else {
       const dim3 g = shared_keys(BWD_KB, 512);
-      hipLaunchKernelGGL((bwd_kv_kernel<T, D, false>), g, dim3(256), 0, st, kv);
+      hipLaunchKernelGGL((bwd_kv_kernel<D, false>), g, dim3(256), 0, st, kv);
     }
     if ((err = launched("bwd_kv_shared_kernel", st)) != hipSuccess) return err;
     const int64_t mrows = BH(c) * c.M;
@@ -1588,7 +1546,7 @@ static hipError_t bwd_t(const mita_cfg_t &c, const BwdBufs &b, hipStream_t st) {
       }
     } else {
       const dim3 g = routed_keys(BWD_KB);
-      hipLaunchKernelGGL((bwd_kv_kernel<T, D, true>), g, dim3(256), 0, st, kv);
+      hipLaunchKernelGGL((bwd_kv_kernel<D, true>), g, dim3(256), 0, st, kv);
     }
     if ((err = launched("bwd_kv_kernel", st)) != hipSuccess) return err;
     const int per_head = c.M * c.k;

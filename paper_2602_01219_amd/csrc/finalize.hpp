@@ -1,7 +1,6 @@
 // finalize.hpp - the finish of the fused top-k selection for one landmark
-// row (Eq. top-k): exact top-k from the row's candidate lists, the row's
-// landmark-value merge; used by the finalize kernel and by the launch that
-// runs it together with the routing logits.
+// row (Eq. top-k): exact top-k from the row's candidate lists, and the row's
+// landmark-value merge, by a workgroup or by a wave.
 #pragma once
 #include "cdna4.hpp"
 #include "flash.hpp"

@@ -885,14 +885,4 @@ __device__ __forceinline__ float merge_landmark_value_1(const float2 *__restrict
   return LandmarkMerge1<D>::combine(gm, gl, ga);
 }
 
-
-template <typename T, int D>
-__device__ __forceinline__ void merge_landmark_value(const float2 *__restrict__ part_ml,
-                                                     const float *__restrict__ part_o, T *__restrict__ v_lm,
-                                                     int64_t bh, int lm, int M, int nch, float (*red)[3][D]) {
-  LandmarkMerge<T, D> m;
-  m.prefetch(part_ml, part_o, bh, lm, M, nch);
-  m.finish(part_ml, part_o, v_lm, bh, lm, M, nch, red);
-}
-
 }  // namespace mita

@@ -117,7 +117,9 @@ __device__ __forceinline__ int route_merge(float best, int arg) {
 }
 
 // Workgroup (bx, by) of the routing grid (NWV waves, one 64-query tile
-// each); lms: RouteLds<T, D>::BYTES of LDS, cnt: NWV M words of LDS.
+// each); lms: RouteLds<T, D>::BYTES of LDS, cnt: NWV M words of LDS. (The query
+// loads and the merge are written out: with route_load or route_merge in their
+// place the compiler of ROCm 7.2.0 crashes on the fp32 instance.)
 template <typename T, int D, bool TILES = true, int NWV = 4>
 __device__ __forceinline__ void route_logits_body(T *lms, uint32_t *cnt, int bx, int by, const T *__restrict__ q,
                                                   const T *__restrict__ q_lm, int32_t *__restrict__ expert,

@@ -21,8 +21,9 @@
 //      is out of range goes to a fallback list. Where the routing came first,
 //      rows of experts without queries are only counted, not stored or
 //      selected: nothing reads their sets.
-//   5. fallback rows: the score pass recomputes the full score row and the
-//      exact top-k kernel selects from it.
+//   5. fallback rows: the row is scored in full with the score pass's products
+//      (score_row in the forward's placement launch; scores_rows_kernel with the
+//      staged gather) and the exact top-k selects from it.
 // The sets equal those of the exact top-k over the stored score rows.
 #include "cdna4.hpp"
 #include "flash.hpp"
@@ -36,6 +37,7 @@
 
 namespace mita {
 
+// waves per workgroup of pivots16_body without the logits (fp32: its registers)
 template <typename T> constexpr int PIVOT16_WAVES = sizeof(T) == 2 ? 16 : 8;
 
 // One workgroup per (16 landmarks, head) slot (ROWS 0: pivots16_body) or (ROWS
